@@ -91,6 +91,38 @@ __device__ __forceinline__ int pair_class(int istar, int jstar) { return istar +
 
 constexpr double PI_D = 3.14159265358979323846;
 
+// FP32 transcendentals, each issued at raised wave priority. A SIMD issues the ordinary FP32
+// instructions of two waves side by side (measured 104-115 lanes per clock per CU for a stream of
+// them, against 59 with a scalar-register source), but a transcendental, four times as long, leaves
+// the other slot idle unless a second wave's transcendental fills it. With the priority raised
+// around it, a wave that reaches one is picked at once and they pair up: the 15 instructions of a
+// contact-law pair issue at 94 lanes per clock per CU at four waves per SIMD and 98 at eight (81
+// and 83 without; 99 is what the parts allow: 14 at 115 and one at 32). The chip answers with a
+// lower clock (2.09 against 2.22 GHz in k_force_sym<4>), so at N = 262,144 the evaluation gains 3.6 %
+// (10.95 -> 10.55 ms; eqs. (4)-(6) 14.67 -> 14.34), at 40,009 under eqs. (4)-(6) 5 %, and
+// k_force_f32 at N = 131,072, at two waves per SIMD, 13 % (8.12 -> 7.07 ms). s_setprio after the
+// transcendental is also the wait state that its first use needs.
+__device__ __forceinline__ float rsq_p(float x)
+{
+    float w;
+    asm("s_setprio 1\n\tv_rsq_f32 %0, %1\n\ts_setprio 0" : "=v"(w) : "v"(x));
+    return w;
+}
+
+__device__ __forceinline__ float sqrt_p(float x)
+{
+    float w;
+    asm("s_setprio 1\n\tv_sqrt_f32 %0, %1\n\ts_setprio 0" : "=v"(w) : "v"(x));
+    return w;
+}
+
+__device__ __forceinline__ float rcp_p(float x)
+{
+    float w;
+    asm("s_setprio 1\n\tv_rcp_f32 %0, %1\n\ts_setprio 0" : "=v"(w) : "v"(x));
+    return w;
+}
+
 // ------------------------------------------------------------------ sorted layout
 
 __device__ __forceinline__ int find_tile_sys(const Launch &L, int u)
@@ -204,7 +236,7 @@ __device__ __forceinline__ void interact4_f32(const float4 &X, const float4 &Y, 
         const float dy = ys[q] - yi;
         const float dz = zs[q] - zi;
         const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps)));
-        const float w = __builtin_amdgcn_rsqf(r2);
+        const float w = rsq_p(r2);
         const float w3 = (w * w) * w;
         const float s = FAR ? w3 : fminf(w3, fmaf(nc2, w, c1));
         ax = fmaf(s, dx, ax);
@@ -327,8 +359,9 @@ void k_force_f32(Launch L)
 // meets element (l - s) mod 64 of each group: its position is read from LDS once at that
 // rotating offset and paired with the lane's KR i elements, and the j accumulator travels with
 // it, one lane per step: in short bands by a DPP wave rotation fused into the first row's update
-// a_j <- rotate(a_j) - s (r_j - r_i), in tall ones through the LDS crossbar after the group's
-// last row (see sym_tile); the rows add their terms in row order. After 64 steps and the last
+// a_j <- rotate(a_j) + s (r_j - r_i), in tall ones through the LDS crossbar after the group's
+// last row (see sym_tile); the rows add their terms in row order, and the sums change sign when
+// they are stored (an added term takes the short form of the fused multiply-add). After 64 steps and the last
 // move every lane holds the summed reaction of the wave's 64 KR i elements on its own j. The
 // waves' sums are added in wave order and stored once per (group, tile): a band of KR rows
 // stores 1/KR of the reaction blocks of single rows. Tiles inside the band are split by row:
@@ -407,14 +440,14 @@ __device__ __forceinline__ float pair_s(float r2, float dx, float dy, float dz, 
 {
 #pragma clang fp contract(off)
     if constexpr (LAW == 0) {
-        const float w = __builtin_amdgcn_rsqf(r2);
+        const float w = rsq_p(r2);
         const float w3 = (w * w) * w;
         return NEAR ? fminf(w3, fmaf(K.nc2, w, K.c1)) : w3;
     } else {
-        const float r = __builtin_amdgcn_sqrtf(r2);
+        const float r = sqrt_p(r2);
         const float t = r + K.eps;
         const float t2 = t * t;
-        float s = __builtin_amdgcn_rcpf(t2 * r);
+        float s = rcp_p(t2 * r);
         if constexpr (NEAR) {
             const float w = t2 * s;
             const float dot = fmaf(vj.x - vi.x, dx, fmaf(vj.y - vi.y, dy, (vj.z - vi.z) * dz));
@@ -473,8 +506,8 @@ __device__ __forceinline__ void sym_tile(const float4 *__restrict__ sj,
                                          int lane, int nact)
 {
     // The j sums move one lane per step (lane l takes lane l - 1's sums). With one row per band
-    // the move folds into row 0's update, a_j <- rotate(a_j) - p with p = s d kept as an operand
-    // of its own (a VOP2 subtraction with a DPP source; a fused multiply-add cannot take one).
+    // the move folds into row 0's update, a_j <- rotate(a_j) + p with p = s d kept as an operand
+    // of its own (a VOP2 addition with a DPP source; a fused multiply-add cannot take one).
     // The other rows add s d to both sums with fused multiply-adds: two instructions per
     // component instead of three. In taller bands (four rows under the contact law, two or more
     // under eqs. (4)-(6)) the sums of each j group move through the LDS crossbar (ds_bpermute)
@@ -508,16 +541,16 @@ __device__ __forceinline__ void sym_tile(const float4 *__restrict__ sj,
                     B.ax[r] += px;
                     B.ay[r] += py;
                     B.az[r] += pz;
-                    ajx[g] = wave_ror1(ajx[g]) - px;
-                    ajy[g] = wave_ror1(ajy[g]) - py;
-                    ajz[g] = wave_ror1(ajz[g]) - pz;
+                    ajx[g] = wave_ror1(ajx[g]) + px;
+                    ajy[g] = wave_ror1(ajy[g]) + py;
+                    ajz[g] = wave_ror1(ajz[g]) + pz;
                 } else {
                     B.ax[r] = fmaf(s, dx, B.ax[r]);
                     B.ay[r] = fmaf(s, dy, B.ay[r]);
                     B.az[r] = fmaf(s, dz, B.az[r]);
-                    ajx[g] = fmaf(-s, dx, ajx[g]);
-                    ajy[g] = fmaf(-s, dy, ajy[g]);
-                    ajz[g] = fmaf(-s, dz, ajz[g]);
+                    ajx[g] = fmaf(s, dx, ajx[g]);
+                    ajy[g] = fmaf(s, dy, ajy[g]);
+                    ajz[g] = fmaf(s, dz, ajz[g]);
                 }
                 // contact law: keep each pair's instructions together. Left free, the scheduler
                 // gathers the twelve rotated updates of a step at its end, and back-to-back DPP
@@ -537,9 +570,9 @@ __device__ __forceinline__ void sym_tile(const float4 *__restrict__ sj,
     for (int g = 0; g < 4; ++g) {
         // element l's sum back in lane l: one more rotation after the last step (the crossbar
         // form did it already)
-        rwx[g * 64 + lane] = XBAR ? ajx[g] : wave_ror1(ajx[g]);
-        rwy[g * 64 + lane] = XBAR ? ajy[g] : wave_ror1(ajy[g]);
-        rwz[g * 64 + lane] = XBAR ? ajz[g] : wave_ror1(ajz[g]);
+        rwx[g * 64 + lane] = XBAR ? -ajx[g] : -wave_ror1(ajx[g]);
+        rwy[g * 64 + lane] = XBAR ? -ajy[g] : -wave_ror1(ajy[g]);
+        rwz[g * 64 + lane] = XBAR ? -ajz[g] : -wave_ror1(ajz[g]);
     }
 }
 
