@@ -79,7 +79,7 @@ struct SysDesc {
     float *tbox;          // ntiles * 8: min xyz, pad, max xyz, pad of each j tile
     void *part;         // j-split partial sums, nsplit * 3 * nalloc values (nsplit > 1 only)
     double *red;        // n_ounits * RED_STRIDE doubles
-    double *pe_part;    // n_peunits doubles
+    double *pe_part;    // potential-energy partials, n_peunits doubles
     int32_t *l1_log;    // L1_LOG_CAP * 4 int32
     DiagOut *diag;
     int32_t n, n1;
@@ -87,7 +87,7 @@ struct SysDesc {
     int32_t iblock, n_iblocks;  // i elements per block (BT * ki) and block count
     int32_t n_units, n_ounits;  // force units (n_iblocks * nsplit) and O(N) units (ceil(n / BT))
     int32_t unit_begin, ounit_begin;  // prefix offsets in the launch's segment table
-    int32_t n_peunits, pad;
+    int32_t n_peunits, pe_ch;         // potential energy: units (tile row, chunk), tiles per chunk
     int32_t npad, p1, nalloc, ntiles;  // sorted layout (see above)
     int32_t tunit_begin, pad2;         // prefix offset of this system's tiles in the launch
     // symmetric kernels (FP32 Kahan and FP64 modes): work units (band g, chunk c) and reaction
@@ -135,7 +135,7 @@ hipError_t launch_kick_stats(const Launch &L, int mode, int do_kick, hipStream_t
 hipError_t launch_finalize_step(const Launch &L, int do_growth, hipStream_t s);
 hipError_t launch_l1_classify(const Launch &L, int mode, int init, hipStream_t s);
 hipError_t launch_finalize_l1(const Launch &L, int init, hipStream_t s);
-hipError_t launch_diag(const Launch &L, int mode, int with_pe, hipStream_t s);
+hipError_t launch_diag(const Launch &L, int mode, int with_pe, int n_peunits, hipStream_t s);
 hipError_t launch_retention(const Launch &L, int mode, hipStream_t s);
 hipError_t launch_valu_probe(int op, float *sink, int blocks, int iters, hipStream_t s);
 hipError_t launch_copy_table(SysDesc *dst, const TableChunk &c, hipStream_t s);

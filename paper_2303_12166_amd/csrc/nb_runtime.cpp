@@ -49,6 +49,7 @@ struct TileCfg {
     int npad, p1, nalloc, ntiles;
     int sym, ch;            // symmetric kernel (Kahan and FP64 modes) and its tiles per chunk
     int rows;               // tile rows per band of the symmetric kernel (1, 2 or 4)
+    int pe_ch, n_peunits;   // potential energy: tiles per chunk, (tile row, chunk) units
     size_t react_floats;    // reaction partials of the symmetric kernel (elements of the mode's type)
 };
 
@@ -100,6 +101,15 @@ void finish_split(TileCfg &c, int mode, int ns, int rows)
     c.n_units = units > INT32_MAX ? -1 : (int)units;
 }
 
+// Chunks of the potential-energy sum: about 8192 (tile row, chunk) units, half of them empty
+// (below the diagonal), from 128 tiles on; one tile each below.
+void pe_split(TileCfg &c)
+{
+    const int64_t T = c.ntiles;
+    c.pe_ch = (int)std::max<int64_t>(1, std::min(T, (T * T + 8191) / 8192));
+    c.n_peunits = (int)(T * ((T + c.pe_ch - 1) / c.pe_ch));
+}
+
 // Sorted layout and work split of a system; a function of (n, n1, mode, law), the overrides and
 // the workspace budget only.
 TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
@@ -113,6 +123,7 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
     c.nalloc = (int)round_up(std::max(c.npad, 1), c.iblock);
     c.n_iblocks = c.npad > 0 ? c.nalloc / c.iblock : 0;
     c.n_ounits = (int)((n + BT - 1) / BT);
+    pe_split(c);
     int ns = 1, rows = 1;
     size_t budget = 0;
     if (mode != NB_FP32_PLAIN && c.ntiles > 0) {
@@ -167,7 +178,7 @@ Layout layout_for(int mode, int law, const TileCfg &c)
     L.desc = take(sizeof(SysDesc));
     L.diag = take(sizeof(DiagOut));
     L.red = take((size_t)std::max(c.n_ounits, 1) * RED_STRIDE * sizeof(double));
-    L.pe = take((size_t)std::max(c.n_ounits, 1) * sizeof(double));
+    L.pe = take((size_t)c.n_peunits * sizeof(double));
     L.log = take((size_t)L1_LOG_CAP * 4 * sizeof(int32_t));
     L.xs = take((size_t)c.nalloc * elem);
     L.ys = take((size_t)c.nalloc * elem);
@@ -590,7 +601,8 @@ void fill_desc(SysDesc &d, const nb_params *p, const nb_buffers *b, const TileCf
     d.n_ounits = cfg.n_ounits;
     d.unit_begin = 0;
     d.ounit_begin = 0;
-    d.n_peunits = cfg.n_ounits;
+    d.n_peunits = cfg.n_peunits;
+    d.pe_ch = cfg.pe_ch;
 }
 
 // Initial device state of a system: FP64 masters and the derived FP32 force constants.
@@ -1006,7 +1018,7 @@ int nb_diagnostics(nb_system *s, int32_t with_pe, nb_diag *out, void *stream)
 {
     if (!s || !out || !on_own_device(s)) return NB_E_INVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    NB_TRY(launch_diag(single_launch(s), s->p.mode, with_pe ? 1 : 0, st));
+    NB_TRY(launch_diag(single_launch(s), s->p.mode, with_pe ? 1 : 0, s->cfg.n_peunits, st));
     DiagOut d;
     DevState ds;
     NB_TRY(hipMemcpyAsync(&d, s->d_diag, sizeof d, hipMemcpyDeviceToHost, st));
