@@ -18,8 +18,14 @@ constexpr int SYM_PAPER_WAVES[3] = {6, 5, 4};  // eqs. (4)-(6): at one row a few
 constexpr int BT = 256;          // threads per block, every kernel
 constexpr int TJ = 256;          // j elements staged in LDS per tile (one per thread)
 constexpr int MAX_BAND = 4;      // tallest band of the FP32 symmetric kernel (tile rows per lane)
-constexpr int RED_STRIDE = 32;   // doubles per O(N)-unit partial record
-constexpr int RED_STEP = 0;      // record slots [0, 16): per-step sums (COMs, flags, L1 counts)
+constexpr int RED_STRIDE = 32;   // doubles per O(N)-unit partial record of the read-backs
+constexpr int REC_STRIDE = 8;    // doubles per record of a step (position sums, non-finite count)
+constexpr int COM_FUSE_UNITS = 256;  // largest system (in units of 256 elements) whose records
+                                     // every workgroup of k_advance sums for itself
+// i elements per workgroup of the one-sided force kernel
+constexpr int os_ib(bool fp64) { return fp64 ? 4 : 8; }
+constexpr int KERNEL_CLASSES = 4;    // force kernels of a launch: one-sided, bands of 1, 2, 4 rows
+constexpr int ADV_INIT = 2;      // k_advance: record the sides at creation
 constexpr int RED_DIAG = 16;     // record slots [16, 32): diagnostics sums
 constexpr int RED_RET = 26;      // record slots [26, 31): retention sums (after the diagnostics)
 constexpr int L1_LOG_CAP = 4096; // rows of the per-step L1 log
@@ -79,6 +85,7 @@ struct SysDesc {
     float *tbox;          // ntiles * 8: min xyz, pad, max xyz, pad of each j tile
     void *part;         // j-split partial sums, nsplit * 3 * nalloc values (nsplit > 1 only)
     double *red;        // n_ounits * RED_STRIDE doubles
+    double *rec;        // records of a step, n_rec (at creation n_ounits) * REC_STRIDE doubles
     double *pe_part;    // potential-energy partials, n_peunits doubles
     int32_t *l1_log;    // L1_LOG_CAP * 4 int32
     DiagOut *diag;
@@ -86,6 +93,8 @@ struct SysDesc {
     int32_t nsplit, jchunk;     // j chunks per i-block and chunk length (multiple of TJ)
     int32_t iblock, n_iblocks;  // i elements per block (BT * ki) and block count
     int32_t n_units, n_ounits;  // force units (n_iblocks * nsplit) and O(N) units (ceil(n / BT))
+    int32_t n_rec, one_sided;   // records of a step; 1 for the one-sided force kernel, whose units
+                                // are its workgroups
     int32_t unit_begin, ounit_begin;  // prefix offsets in the launch's segment table
     int32_t n_peunits, pe_ch;         // potential energy: units (tile row, chunk), tiles per chunk
     int32_t npad, p1, nalloc, ntiles;  // sorted layout (see above)
@@ -108,9 +117,11 @@ struct Launch {
     int32_t total_ounits;  // O(N) units: 256 elements in element order
     int32_t total_tunits;  // tiles: 256 slots in sorted order
     int32_t law;           // element law of every system in the launch (NB_LAW_*)
-    // FP32 Kahan mode: the table is ordered by band height; systems with bands of 1, 2 and 4 rows
-    // own the force units [0, band_end[0]), [band_end[0], band_end[1]), [band_end[1], band_end[2])
-    int32_t band_end[3];
+    int32_t ounit_base;    // first O(N) unit of the systems outside the one-sided force kernel
+    int32_t any_big;       // a system has more than COM_FUSE_UNITS units
+    // the table is ordered by force kernel: one-sided systems, then bands of 1, 2 and 4 rows (the
+    // plain and FP64 kernels count as 1); they own the force units up to band_end[0] .. band_end[3]
+    int32_t band_end[KERNEL_CLASSES];
 };
 
 // Segment-table entries written on the device from the systems' own one-entry tables (each
@@ -128,13 +139,11 @@ hipError_t launch_init_state(DevState *st, const DevState &init, hipStream_t s);
 hipError_t launch_fill_sorted(void *xs, void *ys, void *zs, int nalloc, int mode, bool sentinel,
                               hipStream_t s);
 hipError_t launch_gather(const Launch &L, int mode, hipStream_t s);
-hipError_t launch_forces(const Launch &L, int mode, int max_blocks, hipStream_t s);
+hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks, hipStream_t s);
 hipError_t launch_combine(const Launch &L, int mode, hipStream_t s);
-hipError_t launch_kick_drift(const Launch &L, int mode, hipStream_t s);
 hipError_t launch_kick_stats(const Launch &L, int mode, int do_kick, hipStream_t s);
 hipError_t launch_finalize_step(const Launch &L, int do_growth, hipStream_t s);
-hipError_t launch_l1_classify(const Launch &L, int mode, int init, hipStream_t s);
-hipError_t launch_finalize_l1(const Launch &L, int init, hipStream_t s);
+hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, hipStream_t s);
 hipError_t launch_diag(const Launch &L, int mode, int with_pe, int n_peunits, hipStream_t s);
 hipError_t launch_retention(const Launch &L, int mode, hipStream_t s);
 hipError_t launch_valu_probe(int op, float *sink, int blocks, int iters, hipStream_t s);

@@ -1208,37 +1208,46 @@ template <>
 __device__ __forceinline__ float dt_of<float>(const DevState *st) { return st->dt_f; }
 template <>
 __device__ __forceinline__ double dt_of<double>(const DevState *st) { return st->dt; }
-
-// v += a dt/2; x += v dt
 template <typename T>
-__global__ __launch_bounds__(BT) void k_kick_drift(Launch L)
+__device__ __forceinline__ T gm_of(const DevState *st);
+template <>
+__device__ __forceinline__ float gm_of<float>(const DevState *st) { return st->gm_f; }
+template <>
+__device__ __forceinline__ double gm_of<double>(const DevState *st) { return st->gm_d; }
+
+// Per-unit record of a step: each star's position sums and the count of non-finite elements.
+__device__ __forceinline__ void add_stats(double (&v)[7], double px, double py, double pz,
+                                          double wx, double wy, double wz, bool star2)
 {
-    for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, true)];
-        const int i = (u - S.ounit_begin) * BT + threadIdx.x;
-        if (i >= S.n) continue;
-        const T h = h_of<T>(S.st), dt = dt_of<T>(S.st);
-        T *x = static_cast<T *>(S.x), *y = static_cast<T *>(S.y), *z = static_cast<T *>(S.z);
-        T *vx = static_cast<T *>(S.vx), *vy = static_cast<T *>(S.vy), *vz = static_cast<T *>(S.vz);
-        const T *ax = static_cast<const T *>(S.ax), *ay = static_cast<const T *>(S.ay),
-                *az = static_cast<const T *>(S.az);
-        const T nvx = vx[i] + h * ax[i], nvy = vy[i] + h * ay[i], nvz = vz[i] + h * az[i];
-        vx[i] = nvx;
-        vy[i] = nvy;
-        vz[i] = nvz;
-        x[i] = x[i] + dt * nvx;
-        y[i] = y[i] + dt * nvy;
-        z[i] = z[i] + dt * nvz;
-    }
+    const int o = star2 ? 3 : 0;
+    v[o + 0] = px;
+    v[o + 1] = py;
+    v[o + 2] = pz;
+    const bool fin = isfinite(px) && isfinite(py) && isfinite(pz) && isfinite(wx) &&
+                     isfinite(wy) && isfinite(wz);
+    v[6] = fin ? 0.0 : 1.0;
+}
+
+// The step that the second kick completes: its number, and its L1 counts cleared for k_advance,
+// whose workgroups add to them. Called by one thread of a system.
+__device__ __forceinline__ void begin_counts(const SysDesc &S)
+{
+    DevState *st = S.st;
+    const int64_t step = st->step + 1;
+    st->step = step;
+    st->n_past = st->fwd = st->bwd = 0;
+    int32_t *row = S.l1_log + 4 * (size_t)(step % L1_LOG_CAP);
+    row[0] = (int32_t)step;
+    row[1] = row[2] = row[3] = 0;
 }
 
 // Optional second kick v += a dt/2, then per-unit FP64 sums of each star's positions and the
-// count of non-finite elements.
+// count of non-finite elements. Systems of the one-sided force kernel do this there.
 template <typename T>
 __global__ __launch_bounds__(BT) void k_kick_stats(Launch L, int do_kick)
 {
     __shared__ double lds[7][BT / 64];
-    for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
+    for (int u = L.ounit_base + blockIdx.x; u < L.total_ounits; u += gridDim.x) {
         const SysDesc &S = L.sys[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
@@ -1256,139 +1265,425 @@ __global__ __launch_bounds__(BT) void k_kick_stats(Launch L, int do_kick)
                 vy[i] = wy;
                 vz[i] = wz;
             }
-            const double px = static_cast<const T *>(S.x)[i];
-            const double py = static_cast<const T *>(S.y)[i];
-            const double pz = static_cast<const T *>(S.z)[i];
-            const int o = i >= S.n1 ? 3 : 0;
-            v[o + 0] = px;
-            v[o + 1] = py;
-            v[o + 2] = pz;
-            const bool fin = isfinite(px) && isfinite(py) && isfinite(pz) &&
-                             isfinite((double)wx) && isfinite((double)wy) && isfinite((double)wz);
-            v[6] = fin ? 0.0 : 1.0;
+            add_stats(v, static_cast<const T *>(S.x)[i], static_cast<const T *>(S.y)[i],
+                      static_cast<const T *>(S.z)[i], wx, wy, wz, i >= S.n1);
         }
         block_sum<7>(v, lds);
         if (threadIdx.x == 0) {
-            double *r = S.red + (size_t)local * RED_STRIDE + RED_STEP;
+            double *r = S.rec + (size_t)local * REC_STRIDE;
             for (int k = 0; k < 7; ++k) r[k] = v[k];
+            if (do_kick && local == 0) begin_counts(S);
         }
     }
 }
 
-// One block per system: star centres, L1 plane, non-finite flag and (optionally) the donor
-// growth update with the derived force constants.
+// ------------------------------------------------------------------ one-sided force kernel
+//
+// Small systems (FP32 Kahan and FP64 modes; see the runtime's one_sided rule): every ordered pair, in
+// element order, with nothing between the drift and the second kick but this kernel. A workgroup
+// takes os_ib elements i of one star, all of them in every lane's registers, and its 256 lanes
+// share out the j: lane t takes j = t, t + 256, ..., so a j is read once per workgroup, straight
+// from memory, for os_ib pairs. Each lane's sums (at most n / 256 terms per element) are added
+// across the wave by a halving exchange and across the waves in order; the elements then take
+// their second kick and the workgroup stores its record of the step. The symmetric kernels need
+// half the pairs, but also a sorted copy, reactions, a combine and the kick as kernels of their
+// own, and one 256 x 256 tile pair takes a wave about 5000 instructions one after the other:
+// 2,048 elements are 45 such units on 256 CUs. Ten steps of 2,048 elements: 539 us with the
+// symmetric kernel and its passes, 139 us with this one and k_advance; 7,001: 610 and 315; FP64,
+// 4,096: 602 and 293.
+// The law is taken in its near form for every pair (the far form gives the same bits).
+
+template <typename T>
+struct OneSidedLaw;
+template <>
+struct OneSidedLaw<float> {
+    LawF k;
+    __device__ __forceinline__ void load(const DevState *st, int cls) { k = law_f(st, cls); }
+};
+template <>
+struct OneSidedLaw<double> {
+    LawD k;
+    __device__ __forceinline__ void load(const DevState *st, int cls) { k = law_d(st, cls); }
+};
+
+template <int LAW>
+__device__ __forceinline__ float one_sided_s(float dx, float dy, float dz, const float4 &vj,
+                                             const float4 &vi, const LawF &K)
+{
+    const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, 1.0e-24f)));
+    return pair_s<LAW, true>(r2, dx, dy, dz, vj, vi, K);
+}
+
+template <int LAW>
+__device__ __forceinline__ double one_sided_s(double dx, double dy, double dz, const double4 &vj,
+                                              const double4 &vi, const LawD &K)
+{
+    const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, 1.0e-200)));
+    return pair_s64<LAW>(r2, rsqrt_f64(r2), dx, dy, dz, vj.x - vi.x, vj.y - vi.y, vj.z - vi.z, K);
+}
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
+
+template <typename T>
+struct Vec4;
+template <>
+struct Vec4<float> {
+    using type = float4;
+};
+template <>
+struct Vec4<double> {
+    using type = double4;
+};
+
+// Sums NV values per lane over the wave, NV a power of two times 3 with the element index first:
+// halves the elements a lane holds at each of the first steps. On return lane l holds element
+// l / (64 / IB)'s three sums, summed over all lanes.
+template <typename T, int IB>
+__device__ __forceinline__ void wave_reduce(T (&a)[IB][3], T (&out)[3], int lane)
+{
+    int width = 32;
+#pragma unroll
+    for (int half = IB / 2; half >= 1; half /= 2) {
+        const bool upper = (lane & width) != 0;
+#pragma unroll
+        for (int k = 0; k < half; ++k) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const T keep = upper ? a[k + half][d] : a[k][d];
+                const T give = upper ? a[k][d] : a[k + half][d];
+                a[k][d] = keep + __shfl_xor(give, width, 64);
+            }
+        }
+        width /= 2;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        T v = a[0][d];
+        for (int w = width; w >= 1; w /= 2) v += __shfl_xor(v, w, 64);
+        out[d] = v;
+    }
+}
+
+template <typename T, int LAW>
+__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
+{
+    constexpr int IB = os_ib(sizeof(T) == 8);
+    using V4 = typename Vec4<T>::type;
+    __shared__ T part[BT / 64][IB][3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int u = L.unit_base + blockIdx.x;
+    const SysDesc &S = L.sys[find_sys(L, u, false)];
+    const int local = u - S.unit_begin;
+    const int n = S.n, n1 = S.n1;
+    const DevState *st = S.st;
+    const T *__restrict__ X = static_cast<const T *>(S.x);
+    const T *__restrict__ Y = static_cast<const T *>(S.y);
+    const T *__restrict__ Z = static_cast<const T *>(S.z);
+    const T *__restrict__ VX = static_cast<const T *>(do_kick ? S.vxs : S.vx);
+    const T *__restrict__ VY = static_cast<const T *>(do_kick ? S.vys : S.vy);
+    const T *__restrict__ VZ = static_cast<const T *>(do_kick ? S.vzs : S.vz);
+    // star 1's elements take the first ceil(n1 / IB) workgroups
+    const int b1 = (n1 + IB - 1) / IB;
+    const int istar = local >= b1 ? 1 : 0;
+    const int i0 = istar ? n1 + (local - b1) * IB : local * IB;
+    const int iend = istar ? n : n1;
+    T xi[IB], yi[IB], zi[IB], acc[IB][3];
+    V4 vi[IB];
+#pragma unroll
+    for (int k = 0; k < IB; ++k) {
+        const int i = min(i0 + k, iend - 1);
+        xi[k] = X[i];
+        yi[k] = Y[i];
+        zi[k] = Z[i];
+        vi[k] = V4{};
+        if constexpr (LAW != 0) vi[k] = V4{VX[i], VY[i], VZ[i], 0};
+        acc[k][0] = acc[k][1] = acc[k][2] = 0;
+    }
+    OneSidedLaw<T> Ka, Kb;
+    Ka.load(st, istar);
+    Kb.load(st, istar + 1);
+    // UN j of the lane are fetched while the previous ones are worked on
+    constexpr int UN = sizeof(T) == 4 ? 4 : 2;
+    T px[UN], py[UN], pz[UN];
+    V4 pv[UN];
+    auto fetch = [&](int j0) {
+#pragma unroll
+        for (int q = 0; q < UN; ++q) {
+            const int j = min(j0 + q * BT + tid, n - 1);
+            px[q] = X[j];
+            py[q] = Y[j];
+            pz[q] = Z[j];
+            pv[q] = V4{};
+            if constexpr (LAW != 0) pv[q] = V4{VX[j], VY[j], VZ[j], 0};
+        }
+    };
+    fetch(0);
+#pragma unroll 1
+    for (int j0 = 0; j0 < n; j0 += UN * BT) {
+        T xj[UN], yj[UN], zj[UN];
+        V4 vj[UN];
+#pragma unroll
+        for (int q = 0; q < UN; ++q) {
+            xj[q] = px[q];
+            yj[q] = py[q];
+            zj[q] = pz[q];
+            vj[q] = pv[q];
+        }
+        if (j0 + UN * BT < n) fetch(j0 + UN * BT);
+#pragma unroll
+        for (int q = 0; q < UN; ++q) {
+            const int j = j0 + q * BT + tid;
+            if (j >= n) break;
+            const auto K = j >= n1 ? Kb.k : Ka.k;
+#pragma unroll
+            for (int k = 0; k < IB; ++k) {
+                const T dx = xj[q] - xi[k], dy = yj[q] - yi[k], dz = zj[q] - zi[k];
+                T s = one_sided_s<LAW>(dx, dy, dz, vj[q], vi[k], K);
+                // the self pair: d = 0 makes its term 0 under the contact law; the overlap term
+                // of eqs. (4)-(6) is of order 1 / eps there
+                if constexpr (LAW != 0) s = j - i0 == k ? (T)0 : s;
+                acc[k][0] = fma_t(s, dx, acc[k][0]);
+                acc[k][1] = fma_t(s, dy, acc[k][1]);
+                acc[k][2] = fma_t(s, dz, acc[k][2]);
+            }
+        }
+    }
+    T sum[3];
+    wave_reduce<T, IB>(acc, sum, lane);
+    constexpr int LPE = 64 / IB;  // lanes that hold one element's sums
+    if (lane % LPE == 0) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) part[wave][lane / LPE][d] = sum[d];
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    // lane k < IB finishes element i0 + k
+    const int i = i0 + lane;
+    const bool mine = lane < IB && i < iend;
+    double v[7] = {0, 0, 0, 0, 0, 0, 0};
+    if (mine) {
+        T t[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            t[d] = part[0][lane][d];
+#pragma unroll
+            for (int w = 1; w < BT / 64; ++w) t[d] += part[w][lane][d];
+        }
+        const T gm = gm_of<T>(st);
+        const T ax = gm * t[0], ay = gm * t[1], az = gm * t[2];
+        static_cast<T *>(S.ax)[i] = ax;
+        static_cast<T *>(S.ay)[i] = ay;
+        static_cast<T *>(S.az)[i] = az;
+        if (do_kick) {
+            const T h = h_of<T>(st);
+            T *vx = static_cast<T *>(S.vx), *vy = static_cast<T *>(S.vy),
+              *vz = static_cast<T *>(S.vz);
+            const T wx = vx[i] + h * ax, wy = vy[i] + h * ay, wz = vz[i] + h * az;
+            vx[i] = wx;
+            vy[i] = wy;
+            vz[i] = wz;
+            add_stats(v, X[i], Y[i], Z[i], wx, wy, wz, istar != 0);
+        }
+    }
+    if (!do_kick) return;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+#pragma unroll
+        for (int w = IB / 2; w >= 1; w /= 2) v[k] += __shfl_xor(v[k], w, 64);
+    }
+    if (lane == 0) {
+        double *r = S.rec + (size_t)local * REC_STRIDE;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) r[k] = v[k];
+        if (local == 0) begin_counts(S);
+    }
+}
+
+// ------------------------------------------------------------------ between two evaluations
+
+// Star centres and L1 plane.
+struct Plane {
+    double com1[3], com2[3], e[3], xi_cut;
+    int ok;
+};
+
+// The system's records summed by one workgroup, in the same order wherever it is done.
+__device__ __forceinline__ void sum_records(const SysDesc &S, int n_rec, double (&v)[7],
+                                            double (*lds)[BT / 64])
+{
+    for (int k = 0; k < 7; ++k) v[k] = 0.0;
+    for (int u = threadIdx.x; u < n_rec; u += BT) {
+        const double *r = S.rec + (size_t)u * REC_STRIDE;
+        for (int k = 0; k < 7; ++k) v[k] += r[k];
+    }
+    block_sum<7>(v, lds);
+}
+
+__device__ __forceinline__ void plane_of(const SysDesc &S, const double (&v)[7], Plane &p)
+{
+    const int n1 = S.n1, n2 = S.n - S.n1;
+    for (int d = 0; d < 3; ++d) {
+        p.com1[d] = n1 > 0 ? v[d] / (double)n1 : 0.0;
+        p.com2[d] = n2 > 0 ? v[3 + d] / (double)n2 : 0.0;
+        p.e[d] = p.com2[d] - p.com1[d];
+    }
+    const double dist = sqrt(p.e[0] * p.e[0] + p.e[1] * p.e[1] + p.e[2] * p.e[2]);
+    p.ok = (n1 > 0 && n2 > 0 && dist > 0.0) ? 1 : 0;
+    for (int d = 0; d < 3; ++d) p.e[d] = p.ok ? p.e[d] / dist : 0.0;
+    p.xi_cut = S.st->xi_l1 * dist;
+}
+
+// Records the plane and the non-finite count, and (optionally) applies the donor growth update
+// with the derived force constants. Called by one thread of a system.
+__device__ __forceinline__ void finish_step(const SysDesc &S, const Plane &p, double nonfinite,
+                                            int do_growth)
+{
+    DevState *st = S.st;
+    for (int d = 0; d < 3; ++d) {
+        st->com1[d] = p.com1[d];
+        st->com2[d] = p.com2[d];
+        st->e[d] = p.e[d];
+    }
+    st->xi_cut = p.xi_cut;
+    st->plane_ok = p.ok;
+    st->nonfinite = (int32_t)nonfinite;
+    if (do_growth && st->growth_on && !st->growth_stopped) {
+        const double R2 = st->R2_0 * st->D2 / st->D2_0;
+        if (R2 <= st->rL_a) {
+            st->D2 = st->D2 * (1.0 + st->growth_rate);
+            const double Ds[3] = {st->D1, 0.5 * (st->D1 + st->D2), st->D2};
+            for (int k = 0; k < 3; ++k) {
+                const double D = Ds[k];
+                st->c1d[k] = 11.0 / (D * D * D);
+                st->c2d[k] = 10.0 / (D * D);
+                st->c1f[k] = (float)st->c1d[k];
+                st->c2f[k] = (float)st->c2d[k];
+                st->far2f[k] = (float)(D * D * (1.0 + (double)FAR_MARGIN));
+                st->lD_f[k] = (float)D;
+            }
+        } else {
+            st->growth_stopped = 1;
+        }
+    }
+}
+
+// Systems above COM_FUSE_UNITS units: one workgroup each sums the records and finishes the step
+// (every workgroup of k_advance doing so would read n / 256 records n / 256 times).
 __global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int do_growth)
 {
     __shared__ double lds[7][BT / 64];
     for (int s = blockIdx.x; s < L.n_sys; s += gridDim.x) {
         const SysDesc &S = L.sys[s];
-        double v[7] = {0, 0, 0, 0, 0, 0, 0};
-        for (int u = threadIdx.x; u < S.n_ounits; u += BT) {
-            const double *r = S.red + (size_t)u * RED_STRIDE + RED_STEP;
-            for (int k = 0; k < 7; ++k) v[k] += r[k];
-        }
-        block_sum<7>(v, lds);
+        if (S.n_ounits <= COM_FUSE_UNITS) continue;
+        double v[7];
+        sum_records(S, S.n_ounits, v, lds);
         if (threadIdx.x == 0) {
-            DevState *st = S.st;
-            const int n1 = S.n1, n2 = S.n - S.n1;
-            double c1[3], c2[3], e[3];
-            for (int d = 0; d < 3; ++d) {
-                c1[d] = n1 > 0 ? v[d] / (double)n1 : 0.0;
-                c2[d] = n2 > 0 ? v[3 + d] / (double)n2 : 0.0;
-                e[d] = c2[d] - c1[d];
-                st->com1[d] = c1[d];
-                st->com2[d] = c2[d];
-            }
-            const double dist = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
-            const int ok = (n1 > 0 && n2 > 0 && dist > 0.0) ? 1 : 0;
-            for (int d = 0; d < 3; ++d) st->e[d] = ok ? e[d] / dist : 0.0;
-            st->xi_cut = st->xi_l1 * dist;
-            st->plane_ok = ok;
-            st->nonfinite = (int32_t)v[6];
-            if (do_growth && st->growth_on && !st->growth_stopped) {
-                const double R2 = st->R2_0 * st->D2 / st->D2_0;
-                if (R2 <= st->rL_a) {
-                    st->D2 = st->D2 * (1.0 + st->growth_rate);
-                    const double Ds[3] = {st->D1, 0.5 * (st->D1 + st->D2), st->D2};
-                    for (int k = 0; k < 3; ++k) {
-                        const double D = Ds[k];
-                        st->c1d[k] = 11.0 / (D * D * D);
-                        st->c2d[k] = 10.0 / (D * D);
-                        st->c1f[k] = (float)st->c1d[k];
-                        st->c2f[k] = (float)st->c2d[k];
-                        st->far2f[k] = (float)(D * D * (1.0 + (double)FAR_MARGIN));
-                        st->lD_f[k] = (float)D;
-                    }
-                } else {
-                    st->growth_stopped = 1;
-                }
-            }
+            Plane p;
+            plane_of(S, v, p);
+            finish_step(S, p, v[6], do_growth);
         }
         __syncthreads();
     }
 }
 
-// Donor elements: side of the L1 plane, crossings since the previous call.
+// One pass over the elements between two force evaluations. `finish`: ends the step whose second
+// kick wrote the records (ADV_INIT: only records the sides at creation) -- star centres, L1
+// plane, growth, and the donor elements' side of the plane with the crossings since the last
+// step. `kick`: begins the next step, v += a dt/2, x += v dt. One kernel of a step in place of
+// four: each had a few microseconds of launch and drain, most of a small system's step
+// (65,536 elements: 784 -> 762 us a step). Up to COM_FUSE_UNITS units every workgroup sums the system's
+// records itself, in one order, and its first one records the result; the counts are whole
+// numbers added atomically to what begin_counts cleared, so their order does not matter.
 template <typename T>
-__global__ __launch_bounds__(BT) void k_l1_classify(Launch L, int init)
+__global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
 {
-    __shared__ double lds[3][BT / 64];
+    __shared__ double lds[7][BT / 64];
+    __shared__ Plane pl;
+    __shared__ int cnt[3][BT / 64];
     for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
         const SysDesc &S = L.sys[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
-        double v[3] = {0, 0, 0};
-        const DevState *st = S.st;
-        if (i < S.n && i >= S.n1) {
-            const double px = static_cast<const T *>(S.x)[i];
-            const double py = static_cast<const T *>(S.y)[i];
-            const double pz = static_cast<const T *>(S.z)[i];
-            const double xi = (px - st->com1[0]) * st->e[0] + (py - st->com1[1]) * st->e[1] +
-                              (pz - st->com1[2]) * st->e[2];
-            const int past = (st->plane_ok && xi < st->xi_cut) ? 1 : 0;
-            const int prev = S.side[i];
-            v[0] = past;
-            if (!init) {
-                v[1] = (past && !prev) ? 1.0 : 0.0;
-                v[2] = (!past && prev) ? 1.0 : 0.0;
-            }
-            S.side[i] = (int8_t)past;
+        T *x = static_cast<T *>(S.x), *y = static_cast<T *>(S.y), *z = static_cast<T *>(S.z);
+        T px = 0, py = 0, pz = 0;
+        if (i < S.n) {
+            px = x[i];
+            py = y[i];
+            pz = z[i];
         }
-        block_sum<3>(v, lds);
-        if (threadIdx.x == 0) {
-            double *r = S.red + (size_t)local * RED_STRIDE + RED_STEP + 8;
-            for (int k = 0; k < 3; ++k) r[k] = v[k];
-        }
-    }
-}
-
-__global__ __launch_bounds__(BT) void k_finalize_l1(Launch L, int init)
-{
-    __shared__ double lds[3][BT / 64];
-    for (int s = blockIdx.x; s < L.n_sys; s += gridDim.x) {
-        const SysDesc &S = L.sys[s];
-        double v[3] = {0, 0, 0};
-        for (int u = threadIdx.x; u < S.n_ounits; u += BT) {
-            const double *r = S.red + (size_t)u * RED_STRIDE + RED_STEP + 8;
-            for (int k = 0; k < 3; ++k) v[k] += r[k];
-        }
-        block_sum<3>(v, lds);
-        if (threadIdx.x == 0) {
+        if (finish) {
             DevState *st = S.st;
-            st->n_past = (int32_t)v[0];
-            st->fwd = (int32_t)v[1];
-            st->bwd = (int32_t)v[2];
-            if (!init) {
-                const int64_t step = st->step + 1;
-                st->step = step;
-                int32_t *row = S.l1_log + 4 * (size_t)(step % L1_LOG_CAP);
-                row[0] = (int32_t)step;
-                row[1] = st->n_past;
-                row[2] = st->fwd;
-                row[3] = st->bwd;
+            if (S.n_ounits <= COM_FUSE_UNITS) {
+                double v[7];
+                sum_records(S, finish == ADV_INIT ? S.n_ounits : S.n_rec, v, lds);
+                if (threadIdx.x == 0) {
+                    plane_of(S, v, pl);
+                    if (local == 0) finish_step(S, pl, v[6], finish != ADV_INIT);
+                }
+            } else if (threadIdx.x == 0) {
+                for (int d = 0; d < 3; ++d) {
+                    pl.com1[d] = st->com1[d];
+                    pl.e[d] = st->e[d];
+                }
+                pl.xi_cut = st->xi_cut;
+                pl.ok = st->plane_ok;
+            }
+            __syncthreads();
+            bool past = false, fwd = false, bwd = false;
+            if (i < S.n && i >= S.n1) {
+                const double xi = ((double)px - pl.com1[0]) * pl.e[0] +
+                                  ((double)py - pl.com1[1]) * pl.e[1] +
+                                  ((double)pz - pl.com1[2]) * pl.e[2];
+                past = pl.ok && xi < pl.xi_cut;
+                if (finish != ADV_INIT) {
+                    const bool prev = S.side[i] != 0;
+                    fwd = past && !prev;
+                    bwd = !past && prev;
+                }
+                S.side[i] = past ? 1 : 0;
+            }
+            const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+            const int c0 = __popcll(__ballot(past)), c1 = __popcll(__ballot(fwd)),
+                      c2 = __popcll(__ballot(bwd));
+            if (lane == 0) {
+                cnt[0][wave] = c0;
+                cnt[1][wave] = c1;
+                cnt[2][wave] = c2;
+            }
+            __syncthreads();
+            if (threadIdx.x < 3) {
+                const int k = threadIdx.x;
+                const int c = cnt[k][0] + cnt[k][1] + cnt[k][2] + cnt[k][3];
+                if (c != 0) {
+                    atomicAdd(k == 0 ? &st->n_past : (k == 1 ? &st->fwd : &st->bwd), c);
+                    if (finish != ADV_INIT)
+                        atomicAdd(S.l1_log + 4 * (size_t)(st->step % L1_LOG_CAP) + 1 + k, c);
+                }
             }
         }
-        __syncthreads();
+        if (kick && i < S.n) {
+            const T h = h_of<T>(S.st), dt = dt_of<T>(S.st);
+            T *vx = static_cast<T *>(S.vx), *vy = static_cast<T *>(S.vy),
+              *vz = static_cast<T *>(S.vz);
+            const T nvx = vx[i] + h * static_cast<const T *>(S.ax)[i];
+            const T nvy = vy[i] + h * static_cast<const T *>(S.ay)[i];
+            const T nvz = vz[i] + h * static_cast<const T *>(S.az)[i];
+            vx[i] = nvx;
+            vy[i] = nvy;
+            vz[i] = nvz;
+            x[i] = px + dt * nvx;
+            y[i] = py + dt * nvy;
+            z[i] = pz + dt * nvz;
+            if (S.one_sided && S.vxs) {
+                // the one-sided force kernel kicks its own elements while others read the
+                // half-step velocities of eqs. (4)-(6)
+                static_cast<T *>(S.vxs)[i] = nvx;
+                static_cast<T *>(S.vys)[i] = nvy;
+                static_cast<T *>(S.vzs)[i] = nvz;
+            }
+        }
+        __syncthreads();  // pl and cnt are rewritten by the next unit
     }
 }
 
@@ -1738,7 +2033,7 @@ hipError_t launch_gather(const Launch &L, int mode, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_forces(const Launch &L, int mode, int max_blocks, hipStream_t s)
+hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks, hipStream_t s)
 {
     if (L.total_units == 0) return hipSuccess;
     if (L.law != 0 && L.law != 1) return hipErrorInvalidValue;
@@ -1747,35 +2042,42 @@ hipError_t launch_forces(const Launch &L, int mode, int max_blocks, hipStream_t 
         return dim3(grid_for(max_blocks > 0 ? std::min(units, max_blocks) : units));
     };
     Launch R = L;
-    R.unit_base = 0;
-    if (mode == 0) {
-        if (L.law != 0) return hipErrorInvalidValue;  // eqs. (4)-(6) have no plain FP32 kernel
-        hipLaunchKernelGGL(k_force_f32, grid(L.total_units), dim3(BT), 0, s, R);
-        return hipGetLastError();
-    }
-    if (mode == 2) {
-        if (L.law == 0) {
-            hipLaunchKernelGGL(k_force_sym64<0>, grid(L.total_units), dim3(BT), 0, s, R);
-        } else {
-            hipLaunchKernelGGL(k_force_sym64<1>, grid(L.total_units), dim3(BT), 0, s, R);
-        }
-        return hipGetLastError();
-    }
-    // FP32 Kahan: one launch per band height present in the table
     int begin = 0;
-    for (int b = 0; b < 3; ++b) {
+    for (int b = 0; b < KERNEL_CLASSES; ++b) {
         const int end = L.band_end[b];
         if (end <= begin) continue;
         R.unit_base = begin;
         R.total_units = end;
-        const dim3 g = grid(end - begin), blk(BT);
-        switch (b * 2 + L.law) {
-        case 0: hipLaunchKernelGGL(k_force_sym<1>, g, blk, 0, s, R); break;
-        case 1: hipLaunchKernelGGL(k_force_sym_paper<1>, g, blk, 0, s, R); break;
-        case 2: hipLaunchKernelGGL(k_force_sym<2>, g, blk, 0, s, R); break;
-        case 3: hipLaunchKernelGGL(k_force_sym_paper<2>, g, blk, 0, s, R); break;
-        case 4: hipLaunchKernelGGL(k_force_sym<4>, g, blk, 0, s, R); break;
-        default: hipLaunchKernelGGL(k_force_sym_paper<4>, g, blk, 0, s, R); break;
+        const dim3 g = b == 0 ? dim3(end - begin) : grid(end - begin), blk(BT);
+        if (b == 0) {
+            // one-sided: one workgroup per unit whatever the launch shape
+            if (mode == 0) return hipErrorInvalidValue;
+            switch ((mode == 2 ? 2 : 0) + L.law) {
+            case 0: hipLaunchKernelGGL((k_force_one_sided<float, 0>), g, blk, 0, s, R, do_kick); break;
+            case 1: hipLaunchKernelGGL((k_force_one_sided<float, 1>), g, blk, 0, s, R, do_kick); break;
+            case 2: hipLaunchKernelGGL((k_force_one_sided<double, 0>), g, blk, 0, s, R, do_kick); break;
+            default: hipLaunchKernelGGL((k_force_one_sided<double, 1>), g, blk, 0, s, R, do_kick); break;
+            }
+        } else if (mode == 0) {
+            if (L.law != 0 || b != 1) return hipErrorInvalidValue;  // no eqs. (4)-(6), no bands
+            hipLaunchKernelGGL(k_force_f32, g, blk, 0, s, R);
+        } else if (mode == 2) {
+            if (b != 1) return hipErrorInvalidValue;
+            if (L.law == 0) {
+                hipLaunchKernelGGL(k_force_sym64<0>, g, blk, 0, s, R);
+            } else {
+                hipLaunchKernelGGL(k_force_sym64<1>, g, blk, 0, s, R);
+            }
+        } else {
+            // FP32 Kahan: one launch per band height present in the table
+            switch (b * 2 + L.law) {
+            case 2: hipLaunchKernelGGL(k_force_sym<1>, g, blk, 0, s, R); break;
+            case 3: hipLaunchKernelGGL(k_force_sym_paper<1>, g, blk, 0, s, R); break;
+            case 4: hipLaunchKernelGGL(k_force_sym<2>, g, blk, 0, s, R); break;
+            case 5: hipLaunchKernelGGL(k_force_sym_paper<2>, g, blk, 0, s, R); break;
+            case 6: hipLaunchKernelGGL(k_force_sym<4>, g, blk, 0, s, R); break;
+            default: hipLaunchKernelGGL(k_force_sym_paper<4>, g, blk, 0, s, R); break;
+            }
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1798,58 +2100,44 @@ hipError_t launch_combine(const Launch &L, int mode, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_kick_drift(const Launch &L, int mode, hipStream_t s)
-{
-    if (L.total_ounits == 0) return hipSuccess;
-    const dim3 g(grid_for(L.total_ounits)), b(BT);
-    if (mode == 2) {
-        hipLaunchKernelGGL(k_kick_drift<double>, g, b, 0, s, L);
-    } else {
-        hipLaunchKernelGGL(k_kick_drift<float>, g, b, 0, s, L);
-    }
-    return hipGetLastError();
-}
-
 hipError_t launch_kick_stats(const Launch &L, int mode, int do_kick, hipStream_t s)
 {
-    if (L.total_ounits == 0) return hipSuccess;
-    const dim3 g(grid_for(L.total_ounits)), b(BT);
+    // systems of the one-sided force kernel kick there; at creation (no kick) every system is here
+    Launch R = L;
+    if (!do_kick) R.ounit_base = 0;
+    if (R.total_ounits <= R.ounit_base) return hipSuccess;
+    const dim3 g(grid_for(R.total_ounits - R.ounit_base)), b(BT);
     if (mode == 2) {
-        hipLaunchKernelGGL(k_kick_stats<double>, g, b, 0, s, L, do_kick);
+        hipLaunchKernelGGL(k_kick_stats<double>, g, b, 0, s, R, do_kick);
     } else {
-        hipLaunchKernelGGL(k_kick_stats<float>, g, b, 0, s, L, do_kick);
+        hipLaunchKernelGGL(k_kick_stats<float>, g, b, 0, s, R, do_kick);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_finalize_step(const Launch &L, int do_growth, hipStream_t s)
 {
+    if (!L.any_big) return hipSuccess;
     hipLaunchKernelGGL(k_finalize_step, dim3(grid_for(L.n_sys)), dim3(BT), 0, s, L, do_growth);
     return hipGetLastError();
 }
 
-hipError_t launch_l1_classify(const Launch &L, int mode, int init, hipStream_t s)
+hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, hipStream_t s)
 {
     if (L.total_ounits == 0) return hipSuccess;
     const dim3 g(grid_for(L.total_ounits)), b(BT);
     if (mode == 2) {
-        hipLaunchKernelGGL(k_l1_classify<double>, g, b, 0, s, L, init);
+        hipLaunchKernelGGL(k_advance<double>, g, b, 0, s, L, finish, kick);
     } else {
-        hipLaunchKernelGGL(k_l1_classify<float>, g, b, 0, s, L, init);
+        hipLaunchKernelGGL(k_advance<float>, g, b, 0, s, L, finish, kick);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_finalize_l1(const Launch &L, int init, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_finalize_l1, dim3(grid_for(L.n_sys)), dim3(BT), 0, s, L, init);
     return hipGetLastError();
 }
 
 // one system
 hipError_t launch_diag(const Launch &L, int mode, int with_pe, int n_peunits, hipStream_t s)
 {
-    if (L.n_sys != 1 || (L.total_ounits > 0 && n_peunits < 1)) return hipErrorInvalidValue;
+    if (L.n_sys != 1) return hipErrorInvalidValue;
     if (L.total_ounits > 0) {
         const dim3 g(grid_for(L.total_ounits)), b(BT);
         if (mode == 2) {
@@ -1859,7 +2147,7 @@ hipError_t launch_diag(const Launch &L, int mode, int with_pe, int n_peunits, hi
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (with_pe) {
+        if (with_pe && n_peunits > 0) {
             // the pair sum reads the sorted positions of the current state
             e = launch_gather(L, mode, s);
             if (e != hipSuccess) return e;

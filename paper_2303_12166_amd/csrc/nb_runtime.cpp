@@ -49,6 +49,7 @@ struct TileCfg {
     int npad, p1, nalloc, ntiles;
     int sym, ch;            // symmetric kernel (Kahan and FP64 modes) and its tiles per chunk
     int rows;               // tile rows per band of the symmetric kernel (1, 2 or 4)
+    int one_sided, n_rec;   // one-sided force kernel; records of a step
     int pe_ch, n_peunits;   // potential energy: tiles per chunk, (tile row, chunk) units
     size_t react_floats;    // reaction partials of the symmetric kernel (elements of the mode's type)
 };
@@ -68,8 +69,11 @@ struct Layout;
 Layout layout_for(int mode, int law, const TileCfg &c);
 size_t layout_total(int mode, int law, const TileCfg &c);
 
+// Largest systems of the one-sided force kernel, by FP64 mode and element law.
+constexpr int64_t ONE_SIDED_MAX[2][2] = {{8192, 8192}, {8192, 8192}};
+
 // The work split fields of c for ns requested chunks and bands of `rows` tile rows.
-void finish_split(TileCfg &c, int mode, int ns, int rows)
+void finish_split(TileCfg &c, int64_t n, int64_t n1, int mode, int law, int ns, int rows)
 {
     c.rows = mode == NB_FP32_KAHAN ? rows : 1;  // bands of several rows: FP32 Kahan kernel only
     c.sym = 0;
@@ -92,8 +96,21 @@ void finish_split(TileCfg &c, int mode, int ns, int rows)
         // makes nb_scratch_bytes and nb_create report NB_E_NOMEM
         c.n_units = units > INT32_MAX ? -1 : (int)units;
         c.react_floats = (size_t)3 * TJ * (size_t)react_tiles;
+        c.one_sided = 0;
+        c.n_rec = c.n_ounits;
+        if (c.rows == 1 && c.ch == 1 && n <= ONE_SIDED_MAX[mode == NB_FP64][law]) {
+            // the finest split of a small system: evaluated one-sided
+            c.one_sided = 1;
+            c.sym = 0;
+            c.react_floats = 0;
+            const int64_t ib = os_ib(mode == NB_FP64);
+            c.n_units = (int)((n1 + ib - 1) / ib + (n - n1 + ib - 1) / ib);
+            c.n_rec = c.n_units;
+        }
         return;
     }
+    c.one_sided = 0;
+    c.n_rec = c.n_ounits;
     // chunk c covers tiles [c ntiles / nsplit, (c + 1) ntiles / nsplit)
     c.nsplit = c.ntiles > 0 ? std::max(1, std::min(ns, c.ntiles)) : 1;
     c.jchunk = c.ntiles > 0 ? (c.ntiles + c.nsplit - 1) / c.nsplit * TJ : TJ;
@@ -122,7 +139,7 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
     c.ntiles = c.npad / TJ;
     c.nalloc = (int)round_up(std::max(c.npad, 1), c.iblock);
     c.n_iblocks = c.npad > 0 ? c.nalloc / c.iblock : 0;
-    c.n_ounits = (int)((n + BT - 1) / BT);
+    c.n_ounits = (int)std::max<int64_t>(1, (n + BT - 1) / BT);  // an empty system steps too
     pe_split(c);
     int ns = 1, rows = 1;
     size_t budget = 0;
@@ -144,14 +161,14 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
         }
         budget = g_budget;
     }
-    finish_split(c, mode, ns, rows);
+    finish_split(c, n, n1, mode, law, ns, rows);
     // over the workspace budget: taller bands first (FP32 Kahan), then fewer, longer chunks,
     // until the layout fits or cannot shrink further
     while (budget > 0 && c.sym && c.n_units >= 0 && layout_total(mode, law, c) > budget) {
         if (mode == NB_FP32_KAHAN && c.rows < MAX_BAND) {
-            finish_split(c, mode, c.nsplit, c.rows * 2);
+            finish_split(c, n, n1, mode, law, c.nsplit, c.rows * 2);
         } else if (c.nsplit > 1) {
-            finish_split(c, mode, c.nsplit / 2, c.rows);
+            finish_split(c, n, n1, mode, law, c.nsplit / 2, c.rows);
         } else {
             break;
         }
@@ -160,9 +177,12 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
 }
 
 struct Layout {
-    size_t state, desc, diag, red, pe, log, xs, ys, zs, vxs, vys, vzs, perm, tbox, units, react,
+    size_t state, desc, diag, red, rec, pe, log, xs, ys, zs, vxs, vys, vzs, perm, tbox, units, react,
         part, total;
 };
+
+// Whether the force kernel leaves partial sums for a combine.
+bool needs_partials(const TileCfg &c) { return !c.one_sided && (c.nsplit > 1 || c.sym); }
 
 Layout layout_for(int mode, int law, const TileCfg &c)
 {
@@ -178,6 +198,7 @@ Layout layout_for(int mode, int law, const TileCfg &c)
     L.desc = take(sizeof(SysDesc));
     L.diag = take(sizeof(DiagOut));
     L.red = take((size_t)std::max(c.n_ounits, 1) * RED_STRIDE * sizeof(double));
+    L.rec = take((size_t)std::max(std::max(c.n_ounits, c.n_rec), 1) * REC_STRIDE * sizeof(double));
     L.pe = take((size_t)c.n_peunits * sizeof(double));
     L.log = take((size_t)L1_LOG_CAP * 4 * sizeof(int32_t));
     L.xs = take((size_t)c.nalloc * elem);
@@ -192,7 +213,7 @@ Layout layout_for(int mode, int law, const TileCfg &c)
     L.units = take(c.sym ? (size_t)c.n_units * 2 * sizeof(int32_t) : 0);
     L.react = take(c.sym ? c.react_floats * elem : 0);
     L.part = off;
-    if (c.nsplit > 1 || c.sym) take((size_t)c.nsplit * 3 * (size_t)c.nalloc * elem);
+    if (needs_partials(c)) take((size_t)c.nsplit * 3 * (size_t)c.nalloc * elem);
     L.total = off;
     return L;
 }
@@ -395,7 +416,7 @@ int hip_status(hipError_t e) { return e == hipSuccess ? NB_OK : NB_E_HIP; }
         if (e_ != hipSuccess) return NB_E_HIP; \
     } while (0)
 
-int launch_force_timed(const Launch &L, int mode, hipStream_t st, bool need_combine,
+int launch_force_timed(const Launch &L, int mode, int do_kick, hipStream_t st, bool need_combine,
                        bool allow_timing = true)
 {
     NB_TRY(launch_gather(L, mode, st));
@@ -414,7 +435,7 @@ int launch_force_timed(const Launch &L, int mode, hipStream_t st, bool need_comb
             return NB_E_HIP;
         }
     }
-    const hipError_t e = launch_forces(L, mode, g_force_grid.load(), st);
+    const hipError_t e = launch_forces(L, mode, do_kick, g_force_grid.load(), st);
     if (timed) {
         if (e != hipSuccess || hipEventRecord(b, st) != hipSuccess) {
             (void)hipEventDestroy(a);
@@ -429,23 +450,45 @@ int launch_force_timed(const Launch &L, int mode, hipStream_t st, bool need_comb
     return NB_OK;
 }
 
+// k_advance ends one step and begins the next, so a call of n_steps runs it n_steps + 1 times.
 int run_steps(const Launch &L, int mode, int n_steps, bool need_combine, hipStream_t st,
               bool allow_timing = true)
 {
     for (int k = 0; k < n_steps; ++k) {
-        NB_TRY(launch_kick_drift(L, mode, st));
-        int rc = launch_force_timed(L, mode, st, need_combine, allow_timing);
+        NB_TRY(launch_advance(L, mode, k > 0 ? 1 : 0, 1, st));
+        int rc = launch_force_timed(L, mode, 1, st, need_combine, allow_timing);
         if (rc != NB_OK) return rc;
         NB_TRY(launch_kick_stats(L, mode, 1, st));
         NB_TRY(launch_finalize_step(L, 1, st));
-        NB_TRY(launch_l1_classify(L, mode, 0, st));
-        NB_TRY(launch_finalize_l1(L, 0, st));
     }
+    if (n_steps > 0) NB_TRY(launch_advance(L, mode, 1, 0, st));
     return NB_OK;
 }
 
-// Index of a band height in Launch::band_end.
-int band_index(int rows) { return rows >= 4 ? 2 : (rows == 2 ? 1 : 0); }
+// Index of a system's force kernel in Launch::band_end.
+int kernel_class(const TileCfg &c)
+{
+    return c.one_sided ? 0 : (c.rows >= 4 ? 3 : (c.rows == 2 ? 2 : 1));
+}
+
+// Prefix offsets of the next table entry (system s) and the launch totals after it.
+void table_append(Launch &L, const nb_system *s, int32_t &unit_begin, int32_t &ounit_begin,
+                  int32_t &tunit_begin)
+{
+    unit_begin = L.total_units;
+    ounit_begin = L.total_ounits;
+    tunit_begin = L.total_tunits;
+    L.total_units += s->cfg.n_units;
+    L.total_ounits += s->cfg.n_ounits;
+    const int b = kernel_class(s->cfg);
+    for (int k = b; k < KERNEL_CLASSES; ++k) L.band_end[k] = L.total_units;
+    if (b == 0) {
+        L.ounit_base = L.total_ounits;  // the sorted copy is not used
+    } else {
+        L.total_tunits += s->cfg.ntiles;
+    }
+    if (s->cfg.n_ounits > COM_FUSE_UNITS) L.any_big = 1;
+}
 
 Launch single_launch(const nb_system *s)
 {
@@ -453,11 +496,8 @@ Launch single_launch(const nb_system *s)
     L.sys = s->d_desc;
     L.n_sys = 1;
     L.law = s->p.law;
-    L.total_units = s->cfg.n_units;
-    L.total_ounits = s->cfg.n_ounits;
-    L.total_tunits = s->cfg.ntiles;
-    const int b = band_index(s->cfg.rows);
-    for (int k = 0; k < 3; ++k) L.band_end[k] = k >= b ? L.total_units : 0;
+    int32_t begin;
+    table_append(L, s, begin, begin, begin);
     return L;
 }
 
@@ -504,31 +544,17 @@ int check_system_list(nb_system *const *sys, int32_t n_sys)
     return NB_OK;
 }
 
-// Table order of a multi-system launch: by band height (so each height's force units are one
-// range), in the given order within a height. Writes n_sys indices into `order`. The order
+// Table order of a multi-system launch: by force kernel (so each kernel's force units are one
+// range), in the given order within a kernel. Writes n_sys indices into `order`. The order
 // decides only which workgroup runs which unit, never a system's arithmetic.
 void table_order(nb_system *const *sys, int32_t n_sys, int *order)
 {
     int k = 0;
-    for (int b = 0; b < 3; ++b) {
+    for (int b = 0; b < KERNEL_CLASSES; ++b) {
         for (int i = 0; i < n_sys; ++i) {
-            if (band_index(sys[i]->cfg.rows) == b) order[k++] = i;
+            if (kernel_class(sys[i]->cfg) == b) order[k++] = i;
         }
     }
-}
-
-// Prefix offsets of table entry `pos` (system s) and the launch totals after it.
-void table_append(Launch &L, const nb_system *s, int32_t &unit_begin, int32_t &ounit_begin,
-                  int32_t &tunit_begin)
-{
-    unit_begin = L.total_units;
-    ounit_begin = L.total_ounits;
-    tunit_begin = L.total_tunits;
-    L.total_units += s->cfg.n_units;
-    L.total_ounits += s->cfg.n_ounits;
-    L.total_tunits += s->cfg.ntiles;
-    const int b = band_index(s->cfg.rows);
-    for (int k = b; k < 3; ++k) L.band_end[k] = L.total_units;
 }
 
 // Segment table of several systems: each system's units follow the previous system's.
@@ -544,7 +570,7 @@ Launch build_table(nb_system *const *sys, int32_t n_sys, std::vector<SysDesc> &t
         const nb_system *s = sys[order[k]];
         table[k] = s->desc;
         table_append(L, s, table[k].unit_begin, table[k].ounit_begin, table[k].tunit_begin);
-        combine = combine || s->cfg.nsplit > 1 || s->cfg.sym;
+        combine = combine || needs_partials(s->cfg);
     }
     L.n_sys = n_sys;
     L.law = sys[0]->p.law;
@@ -567,7 +593,7 @@ void fill_desc(SysDesc &d, const nb_params *p, const nb_buffers *b, const TileCf
     d.ay = b->ay;
     d.az = b->az;
     d.side = static_cast<int8_t *>(b->side);
-    d.part = (cfg.nsplit > 1 || cfg.sym) ? base + lay.part : nullptr;
+    d.part = needs_partials(cfg) ? base + lay.part : nullptr;
     d.units = cfg.sym ? reinterpret_cast<int32_t *>(base + lay.units) : nullptr;
     d.react = cfg.sym ? reinterpret_cast<float *>(base + lay.react) : nullptr;
     d.ch = cfg.ch;
@@ -589,6 +615,9 @@ void fill_desc(SysDesc &d, const nb_params *p, const nb_buffers *b, const TileCf
     d.ntiles = cfg.ntiles;
     d.tunit_begin = 0;
     d.red = reinterpret_cast<double *>(base + lay.red);
+    d.rec = reinterpret_cast<double *>(base + lay.rec);
+    d.n_rec = cfg.n_rec;
+    d.one_sided = cfg.one_sided;
     d.pe_part = reinterpret_cast<double *>(base + lay.pe);
     d.l1_log = reinterpret_cast<int32_t *>(base + lay.log);
     d.n = (int32_t)p->n;
@@ -817,11 +846,10 @@ int nb_create(const nb_params *p, const nb_buffers *b, void *stream, nb_system *
         Launch L = single_launch(s);
         if (launch_kick_stats(L, p->mode, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (launch_finalize_step(L, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
-        if (launch_l1_classify(L, p->mode, 1, st) != hipSuccess) { rc = NB_E_HIP; break; }
-        if (launch_finalize_l1(L, 1, st) != hipSuccess) { rc = NB_E_HIP; break; }
+        if (launch_advance(L, p->mode, ADV_INIT, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (launch_gather(L, p->mode, st) != hipSuccess) { rc = NB_E_HIP; break; }
-        if (launch_forces(L, p->mode, g_force_grid.load(), st) != hipSuccess) { rc = NB_E_HIP; break; }
-        if ((cfg.nsplit > 1 || cfg.sym) && launch_combine(L, p->mode, st) != hipSuccess) {
+        if (launch_forces(L, p->mode, 0, g_force_grid.load(), st) != hipSuccess) { rc = NB_E_HIP; break; }
+        if (needs_partials(cfg) && launch_combine(L, p->mode, st) != hipSuccess) {
             rc = NB_E_HIP;
             break;
         }
@@ -838,8 +866,8 @@ int nb_create(const nb_params *p, const nb_buffers *b, void *stream, nb_system *
 int nb_forces(nb_system *s, void *stream)
 {
     if (!s || !on_own_device(s)) return NB_E_INVAL;
-    return launch_force_timed(single_launch(s), s->p.mode, static_cast<hipStream_t>(stream),
-                              s->cfg.nsplit > 1 || s->cfg.sym);
+    return launch_force_timed(single_launch(s), s->p.mode, 0, static_cast<hipStream_t>(stream),
+                              needs_partials(s->cfg));
 }
 
 int nb_step(nb_system *const *sys, int32_t n_sys, int32_t n_steps, void *stream)
@@ -850,8 +878,7 @@ int nb_step(nb_system *const *sys, int32_t n_sys, int32_t n_steps, void *stream)
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int mode = sys[0]->p.mode;
     if (n_sys == 1) {
-        return run_steps(single_launch(sys[0]), mode, n_steps,
-                         sys[0]->cfg.nsplit > 1 || sys[0]->cfg.sym, st);
+        return run_steps(single_launch(sys[0]), mode, n_steps, needs_partials(sys[0]->cfg), st);
     }
     int device = 0;
     NB_TRY(hipGetDevice(&device));
@@ -930,7 +957,7 @@ int nb_step_static(nb_system *const *sys, int32_t n_sys, int32_t n_steps, void *
             const nb_system *s = sys[order[first + k]];
             c.src[k] = s->d_desc;
             table_append(L, s, c.unit_begin[k], c.ounit_begin[k], c.tunit_begin[k]);
-            combine = combine || s->cfg.nsplit > 1 || s->cfg.sym;
+            combine = combine || needs_partials(s->cfg);
         }
         NB_TRY(launch_copy_table(table, c, st));
     }
@@ -1018,7 +1045,9 @@ int nb_diagnostics(nb_system *s, int32_t with_pe, nb_diag *out, void *stream)
 {
     if (!s || !out || !on_own_device(s)) return NB_E_INVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    NB_TRY(launch_diag(single_launch(s), s->p.mode, with_pe ? 1 : 0, s->cfg.n_peunits, st));
+    Launch L = single_launch(s);
+    L.total_tunits = s->cfg.ntiles;  // the potential energy reads the sorted copy
+    NB_TRY(launch_diag(L, s->p.mode, with_pe ? 1 : 0, s->cfg.n_peunits, st));
     DiagOut d;
     DevState ds;
     NB_TRY(hipMemcpyAsync(&d, s->d_diag, sizeof d, hipMemcpyDeviceToHost, st));

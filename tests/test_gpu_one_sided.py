@@ -1,0 +1,110 @@
+"""The one-sided force kernel of small systems (the finest split of at most a few thousand elements,
+FP32 Kahan and FP64 modes) and the pass between two evaluations.
+
+Sizes at the edges of a workgroup's elements (8 in FP32, 4 in FP64), of the 256 lanes that share
+the j and of the largest such system, one star empty or of one element, both element laws:
+forces against the oracle at the bars of the other kernels (1e-5 FP32; 1e-12 FP64, 1e-11 under
+eqs. 4-6), against the symmetric kernel of the same system (a coarser split), and in a batch with
+systems of the other kernels bitwise as alone.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_common import force_error, print_case, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+BAR = {("kahan", "contact"): 1e-5, ("kahan", "paper"): 1e-5, ("fp64", "contact"): 1e-12,
+       ("fp64", "paper"): 1e-11}
+
+
+def _system(nb, ic, mode, law):
+    kw = synth.paper_law_params(ic) if law == "paper" else {}
+    return nb.System.from_ic(ic, mode=mode, **kw), kw
+
+
+def _oracle(ic, kw, D2=None):
+    p, v = ic.f32_as_f64()
+    D2 = ic.D2 if D2 is None else D2
+    if kw:
+        return oracle.accel_paper(p, v, ic.n1, ic.G, ic.m, ic.D1, D2, kw["eps"], kw["gamma"],
+                                  kw["beta"])
+    return oracle.accel(p, ic.n1, ic.G, ic.m, ic.D1, D2)
+
+
+@pytest.mark.parametrize("mode,law", list(BAR))
+@pytest.mark.parametrize("n,q", [(1, 0.5), (2, 1.0), (9, 0.5), (17, 0.07), (255, 0.3),
+                                 (258, 0.004), (1023, 1.0), (1025, 0.6), (3077, 0.8),
+                                 (8192, 0.3)])
+def test_forces_match_oracle(n, q, mode, law):
+    nb = require_gpu()
+    ic = synth.with_velocity_noise(synth.make_binary(n, q, seed=n), 0.05, 3)
+    print_case("one-sided forces", n, q, mode, law)
+    M, W = nb.MODES[mode], nb.LAWS[law]
+    nb.nb_tile_override(n, n, M, 4096, 1, law=W)  # one tile per chunk
+    try:
+        s, kw = _system(nb, ic, mode, law)
+        need = nb.nb_scratch_bytes(s.params)
+        nb.nb_tile_override(n, n, M, 1, 1, law=W)  # one chunk: the symmetric kernel from two tiles on
+        t, _ = _system(nb, ic, mode, law)
+        coarse = nb.nb_scratch_bytes(t.params)
+    finally:
+        nb.nb_tile_override(n, n, M, 0, 1, law=W)
+    if n > 256:
+        assert need < coarse  # no reactions, no partial sums
+    a, b = s.accelerations(), t.accelerations()
+    s.forces()
+    assert np.array_equal(s.accelerations(), a)
+    s.close()
+    t.close()
+    ref = _oracle(ic, kw)
+    assert force_error(a, ref) <= BAR[mode, law]
+    assert force_error(a, b.astype(np.float64)) <= 2 * BAR[mode, law]
+
+
+@pytest.mark.parametrize("mode,law", list(BAR))
+def test_batch_with_other_kernels_equals_alone(mode, law):
+    """One-sided systems with larger ones (bands, a system of many units) and an empty one in one
+    table: bitwise as alone, through nb_step, a graph and nb_step_static, over calls of one and
+    of several steps; the run follows the oracle's counts."""
+    nb = require_gpu()
+    sizes = [(700, 0.9), (9000, 0.5), (2048, 0.5), (30000, 0.3), (5003, 0.2), (66000, 0.4)]
+    if mode == "fp64":
+        sizes = sizes[:4]
+    print_case("one-sided in a batch", mode, law)
+
+    def make():
+        return [_system(nb, synth.with_velocity_noise(synth.make_binary(n, q, seed=n, R2=0.45),
+                                                      2.0, 5), mode, law)[0] for n, q in sizes]
+
+    alone, mix, graph, sta = make(), make(), make(), make()
+    empty = nb.System(np.zeros((0, 3)), np.zeros((0, 3)), 0, G=1.0, m=1.0, dt=1e-4, D1=0.1, D2=0.1,
+                      q=0.5, mode=mode, **({"law": "paper", "gamma": 1.0} if law == "paper" else {}))
+    for s in alone:
+        s.step(1)
+        s.step(5)
+    nb.step_many([empty] + mix, 1)
+    nb.step_many(mix + [empty], 5)
+    g = nb.nb_graph_create([s.handle for s in graph], 3, graph[0].stream)
+    for _ in range(2):
+        nb.nb_graph_launch(g, graph[0].stream)
+        graph[0].synchronize()
+    nb.nb_graph_destroy(g)
+    nb.nb_step_static([s.handle for s in sta], 6, sta[0].stream)
+    assert empty.diagnostics()["step"] == 6
+    crossings = 0
+    for k, (n, q) in enumerate(sizes):
+        log = alone[k].l1_log()
+        crossings += int(log[:, 2:].sum())
+        assert log[:, 0].tolist() == list(range(1, 7))
+        for other in (mix, graph, sta):
+            for f in ("positions", "velocities", "accelerations", "sides", "l1_log"):
+                assert np.array_equal(getattr(other[k], f)(), getattr(alone[k], f)()), (n, f)
+            d, e = other[k].diagnostics(), alone[k].diagnostics()
+            assert all(np.array_equal(d[key], e[key]) for key in d), n
+    assert crossings > 0
+    for s in alone + mix + graph + sta + [empty]:
+        s.close()
