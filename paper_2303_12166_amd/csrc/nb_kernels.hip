@@ -35,12 +35,36 @@ namespace nbk {
 
 // ------------------------------------------------------------------ helpers
 
+// Pointers that a kernel reads from its segment table are global memory: without the address space
+// every access would be a flat one, which also waits on the LDS counter. The table itself, and in
+// the force kernels a system's state, unit list and boxes, do not change during a launch: read
+// as constants they come through the scalar cache into scalar registers, where a plain uniform
+// load in a loop with stores is a vector load into vector registers, read again in every round
+// (ten steps of 3,001 elements under eqs. (4)-(6) 814 -> 758 us, two of 40,009 942 -> 897, ten of
+// 2,048 under the contact law 138 -> 132; the eqs. (4)-(6) kernels spill less).
+template <typename T>
+using Glob = __attribute__((address_space(1))) T;
+template <typename T>
+__device__ __forceinline__ Glob<T> *glob(const void *p)
+{
+    return (Glob<T> *)const_cast<void *>(p);
+}
+
+template <typename T>
+using Const = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ Const<T> *cst(const T *p)
+{
+    return (Const<T> *)p;
+}
+using SysRef = Const<SysDesc> &;
+
 __device__ __forceinline__ int find_sys(const Launch &L, int u, bool ounit)
 {
     int lo = 0, hi = L.n_sys - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
-        int b = ounit ? L.sys[mid].ounit_begin : L.sys[mid].unit_begin;
+        int b = ounit ? cst(L.sys)[mid].ounit_begin : cst(L.sys)[mid].unit_begin;
         if (b <= u) {
             lo = mid;
         } else {
@@ -130,7 +154,7 @@ __device__ __forceinline__ int find_tile_sys(const Launch &L, int u)
     int lo = 0, hi = L.n_sys - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
-        if (L.sys[mid].tunit_begin <= u) {
+        if (cst(L.sys)[mid].tunit_begin <= u) {
             lo = mid;
         } else {
             hi = mid - 1;
@@ -184,22 +208,22 @@ __global__ __launch_bounds__(BT) void k_gather(Launch L)
     __shared__ float lds[6][BT / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_tile_sys(L, u)];
+        SysRef S = cst(L.sys)[find_tile_sys(L, u)];
         const int tile = u - S.tunit_begin;
         const int slot = tile * TJ + threadIdx.x;
-        const int idx = S.perm[slot];
+        const int idx = glob<const int32_t>(S.perm)[slot];
         float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
         if (idx >= 0) {
-            const T x = static_cast<const T *>(S.x)[idx];
-            const T y = static_cast<const T *>(S.y)[idx];
-            const T z = static_cast<const T *>(S.z)[idx];
-            static_cast<T *>(S.xs)[slot] = x;
-            static_cast<T *>(S.ys)[slot] = y;
-            static_cast<T *>(S.zs)[slot] = z;
+            const T x = glob<const T>(S.x)[idx];
+            const T y = glob<const T>(S.y)[idx];
+            const T z = glob<const T>(S.z)[idx];
+            glob<T>(S.xs)[slot] = x;
+            glob<T>(S.ys)[slot] = y;
+            glob<T>(S.zs)[slot] = z;
             if (S.vxs) {
-                static_cast<T *>(S.vxs)[slot] = static_cast<const T *>(S.vx)[idx];
-                static_cast<T *>(S.vys)[slot] = static_cast<const T *>(S.vy)[idx];
-                static_cast<T *>(S.vzs)[slot] = static_cast<const T *>(S.vz)[idx];
+                glob<T>(S.vxs)[slot] = glob<const T>(S.vx)[idx];
+                glob<T>(S.vys)[slot] = glob<const T>(S.vy)[idx];
+                glob<T>(S.vzs)[slot] = glob<const T>(S.vz)[idx];
             }
             v[0] = float_below(x);
             v[1] = float_below(y);
@@ -232,7 +256,7 @@ __global__ __launch_bounds__(BT) void k_gather(Launch L)
                 r = lds[q][0];
                 for (int w = 1; w < BT / 64; ++w) r = q < 3 ? fminf(r, lds[q][w]) : fmaxf(r, lds[q][w]);
             }
-            S.tbox[(size_t)tile * 8 + k] = r;
+            glob<float>(S.tbox)[(size_t)tile * 8 + k] = r;
         }
         __syncthreads();
     }
@@ -270,19 +294,19 @@ __device__ __forceinline__ float4 lds4(const float *p) { return *reinterpret_cas
 
 // One force unit of the plain mode: i-block `ib` (256 sorted slots, one per lane) against j
 // chunk `c` (a run of whole tiles), one running FP32 sum per element in tile order.
-__device__ __forceinline__ void force_unit_f32(const SysDesc &S, int ib, int c,
+__device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c,
                                                float (*sh)[3][TJ])
 {
     const int tid = threadIdx.x;
-    const float *__restrict__ XS = static_cast<const float *>(S.xs);
-    const float *__restrict__ YS = static_cast<const float *>(S.ys);
-    const float *__restrict__ ZS = static_cast<const float *>(S.zs);
-    const DevState *st = S.st;
+    auto *__restrict__ XS = glob<const float>(S.xs);
+    auto *__restrict__ YS = glob<const float>(S.ys);
+    auto *__restrict__ ZS = glob<const float>(S.zs);
+    auto *st = cst(S.st);
 
     const int slot = ib * BT + tid;
     const float xi = XS[slot], yi = YS[slot], zi = ZS[slot];
     float ax = 0.0f, ay = 0.0f, az = 0.0f;
-    const bool real = S.perm[slot] >= 0;
+    const bool real = glob<const int32_t>(S.perm)[slot] >= 0;
     float lo[3], hi[3];
     lo[0] = wave_min(real ? xi : INFINITY);
     lo[1] = wave_min(real ? yi : INFINITY);
@@ -316,7 +340,7 @@ __device__ __forceinline__ void force_unit_f32(const SysDesc &S, int ib, int c,
             pz = ZS[(t + 1) * TJ + tid];
         }
         const bool jstar = t * TJ >= S.p1;
-        const float *bx = S.tbox + (size_t)t * 8;
+        auto *bx = cst(S.tbox) + (size_t)t * 8;
         const float gx = fmaxf(0.0f, fmaxf(bx[0] - hi[0], lo[0] - bx[4]));
         const float gy = fmaxf(0.0f, fmaxf(bx[1] - hi[1], lo[1] - bx[5]));
         const float gz = fmaxf(0.0f, fmaxf(bx[2] - hi[2], lo[2] - bx[6]));
@@ -338,15 +362,15 @@ __device__ __forceinline__ void force_unit_f32(const SysDesc &S, int ib, int c,
     }
     __syncthreads();  // the next unit of this block reuses both LDS buffers
 
-    const int idx = S.perm[slot];
+    const int idx = glob<const int32_t>(S.perm)[slot];
     if (idx < 0) return;
     if (S.nsplit == 1) {
         const float gm = st->gm_f;
-        static_cast<float *>(S.ax)[idx] = gm * ax;
-        static_cast<float *>(S.ay)[idx] = gm * ay;
-        static_cast<float *>(S.az)[idx] = gm * az;
+        glob<float>(S.ax)[idx] = gm * ax;
+        glob<float>(S.ay)[idx] = gm * ay;
+        glob<float>(S.az)[idx] = gm * az;
     } else {
-        float *P = static_cast<float *>(S.part);
+        auto *P = glob<float>(S.part);
         const size_t na = S.nalloc;
         const size_t b = (size_t)c * 3 * na + slot;
         P[b] = ax;
@@ -361,7 +385,7 @@ void k_force_f32(Launch L)
     __shared__ __attribute__((aligned(16))) float sh[2][3][TJ];
     for (int u = L.unit_base + blockIdx.x; u < L.total_units; u += gridDim.x) {
         const int s = find_sys(L, u, false);
-        const SysDesc &S = L.sys[s];
+        SysRef S = cst(L.sys)[s];
         const int local = u - S.unit_begin;
         const int ib = local / S.nsplit;
         const int c = local - ib * S.nsplit;
@@ -430,7 +454,8 @@ __device__ __forceinline__ LawF law_uniform(LawF K)
     return K;
 }
 
-__device__ __forceinline__ LawF law_f(const DevState *st, int cls)
+template <typename St>
+__device__ __forceinline__ LawF law_f(St st, int cls)
 {
     LawF K;
     K.c1 = st->c1f[cls];
@@ -609,7 +634,7 @@ __device__ __forceinline__ size_t react_group_offset(int g, int ntiles, int kr)
 
 // Whether a tile lies at least D from every i of the wave (its bounding box against the wave's),
 // for the larger of the band's thresholds.
-__device__ __forceinline__ bool far_tile(const float *bx, const float (&lo)[3],
+__device__ __forceinline__ bool far_tile(Const<float> *bx, const float (&lo)[3],
                                          const float (&hi)[3], float far2)
 {
     const float gx = fmaxf(0.0f, fmaxf(bx[0] - hi[0], lo[0] - bx[4]));
@@ -621,17 +646,17 @@ __device__ __forceinline__ bool far_tile(const float *bx, const float (&lo)[3],
 
 // One work unit of the symmetric kernel: band `grp` against chunk c of its tiles (see above).
 template <int LAW, int KR>
-__device__ void force_unit_sym(const SysDesc &S, int grp, int c, float4 *sj, float4 *sv,
+__device__ void force_unit_sym(SysRef S, int grp, int c, float4 *sj, float4 *sv,
                                float (*rw)[3][TJ])
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float *__restrict__ XS = static_cast<const float *>(S.xs);
-    const float *__restrict__ YS = static_cast<const float *>(S.ys);
-    const float *__restrict__ ZS = static_cast<const float *>(S.zs);
-    const float *__restrict__ VXS = static_cast<const float *>(S.vxs);
-    const float *__restrict__ VYS = static_cast<const float *>(S.vys);
-    const float *__restrict__ VZS = static_cast<const float *>(S.vzs);
-    const DevState *st = S.st;
+    auto *__restrict__ XS = glob<const float>(S.xs);
+    auto *__restrict__ YS = glob<const float>(S.ys);
+    auto *__restrict__ ZS = glob<const float>(S.zs);
+    auto *__restrict__ VXS = glob<const float>(S.vxs);
+    auto *__restrict__ VYS = glob<const float>(S.vys);
+    auto *__restrict__ VZS = glob<const float>(S.vzs);
+    auto *st = cst(S.st);
     const int T = S.ntiles;
     const int g0 = KR * grp;               // first tile row of the band
     const int nv = min(KR, T - g0);        // rows of the band inside the system (the last is short)
@@ -649,7 +674,7 @@ __device__ void force_unit_sym(const SysDesc &S, int grp, int c, float4 *sj, flo
         B.ax[r] = B.ay[r] = B.az[r] = 0.0f;
         B.v[r] = make_float4(0.f, 0.f, 0.f, 0.f);
         if constexpr (LAW != 0) B.v[r] = make_float4(VXS[slot], VYS[slot], VZS[slot], 0.0f);
-        if (r < nv && S.perm[slot] >= 0) {
+        if (r < nv && glob<const int32_t>(S.perm)[slot] >= 0) {
             lo[0] = fminf(lo[0], B.x[r]);
             lo[1] = fminf(lo[1], B.y[r]);
             lo[2] = fminf(lo[2], B.z[r]);
@@ -678,7 +703,7 @@ __device__ void force_unit_sym(const SysDesc &S, int grp, int c, float4 *sj, flo
     for (int r = 0; r < KR; ++r) sumx[r] = sumy[r] = sumz[r] = cx[r] = cy[r] = cz[r] = 0.0f;
     const int t0 = g0 + c * S.ch;
     const int t1 = min(T, t0 + S.ch);
-    float *R = S.react;
+    auto *R = glob<float>(S.react);
     const size_t roff = react_group_offset(grp, T, KR);
     const size_t rlen = (size_t)(T - g0 - 1) * TJ;
     float px = 0.f, py = 0.f, pz = 0.f, qx = 0.f, qy = 0.f, qz = 0.f;
@@ -713,7 +738,7 @@ __device__ void force_unit_sym(const SysDesc &S, int grp, int c, float4 *sj, flo
         const float far2 = jstar ? far2b : far2a;
         const int k = t - g0;  // tile t is row k of the band when k < KR
         if (k >= KR) {
-            if (far_tile(S.tbox + (size_t)t * 8, lo, hi, far2)) {
+            if (far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi, far2)) {
                 sym_tile<false, LAW, KR, false>(sj, sv, B, K, rw[wave][0], rw[wave][1],
                                                 rw[wave][2], lane, KR);
             } else {
@@ -751,13 +776,13 @@ __device__ void force_unit_sym(const SysDesc &S, int grp, int c, float4 *sj, flo
         }
         __syncthreads();  // sj, sv and rw are rewritten by the next tile
     }
-    float *P = static_cast<float *>(S.part);
+    auto *P = glob<float>(S.part);
     const size_t na = S.nalloc;
 #pragma unroll
     for (int r = 0; r < KR; ++r) {
         if (r >= nv) continue;
         const int slot = (g0 + r) * TJ + tid;
-        if (S.perm[slot] < 0) continue;
+        if (glob<const int32_t>(S.perm)[slot] < 0) continue;
         const size_t b = (size_t)c * 3 * na + slot;
         P[b] = sumx[r] - cx[r];
         P[b + na] = sumy[r] - cy[r];
@@ -770,9 +795,9 @@ __device__ __forceinline__ void force_sym_units(const Launch &L, float4 *sj, flo
                                                 float (*rw)[3][TJ])
 {
     for (int u = L.unit_base + blockIdx.x; u < L.total_units; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, false)];
-        const int2 gc = reinterpret_cast<const int2 *>(S.units)[u - S.unit_begin];
-        force_unit_sym<LAW, KR>(S, gc.x, gc.y, sj, sv, rw);
+        SysRef S = cst(L.sys)[find_sys(L, u, false)];
+        const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
+        force_unit_sym<LAW, KR>(S, gc[0], gc[1], sj, sv, rw);
     }
 }
 
@@ -808,14 +833,14 @@ void k_force_sym_paper(Launch L)
 constexpr int COMBINE_SEGS = 4;
 
 template <int KR>
-__device__ __forceinline__ void combine_tile(const SysDesc &S, int J, int e, int k,
+__device__ __forceinline__ void combine_tile(SysRef S, int J, int e, int k,
                                              float (*part)[COMBINE_SEGS][TJ])
 {
     const int T = S.ntiles;
     const int slot = J * TJ + e;
-    const int idx = S.perm[slot];
-    const float *P = static_cast<const float *>(S.part);
-    const float *R = S.react;
+    const int idx = glob<const int32_t>(S.perm)[slot];
+    auto *P = glob<const float>(S.part);
+    auto *R = glob<const float>(S.react);
     const size_t na = S.nalloc;
     const int own = J / KR;                           // the element's own band
     const int cj = (T - KR * own + S.ch - 1) / S.ch;  // its chunk count
@@ -882,10 +907,10 @@ __device__ __forceinline__ void combine_tile(const SysDesc &S, int J, int e, int
             for (int q = 1; q < COMBINE_SEGS; ++q) kahan_add(s, c, part[d][q][e]);
             out[d] = s - c;
         }
-        const float gm = S.st->gm_f;
-        static_cast<float *>(S.ax)[idx] = gm * out[0];
-        static_cast<float *>(S.ay)[idx] = gm * out[1];
-        static_cast<float *>(S.az)[idx] = gm * out[2];
+        const float gm = glob<DevState>(S.st)->gm_f;
+        glob<float>(S.ax)[idx] = gm * out[0];
+        glob<float>(S.ay)[idx] = gm * out[1];
+        glob<float>(S.az)[idx] = gm * out[2];
     }
     __syncthreads();  // part is rewritten by the block's next tile
 }
@@ -895,7 +920,7 @@ __global__ __launch_bounds__(BT * COMBINE_SEGS) void k_combine_sym(Launch L)
     __shared__ float part[3][COMBINE_SEGS][TJ];
     const int e = threadIdx.x % TJ, k = threadIdx.x / TJ;
     for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_tile_sys(L, u)];
+        SysRef S = cst(L.sys)[find_tile_sys(L, u)];
         const int J = u - S.tunit_begin;
         switch (S.rows) {
         case 1: combine_tile<1>(S, J, e, k, part); break;
@@ -935,7 +960,8 @@ struct LawD {
     double D, c1, c2, eps, gc, gcb;
 };
 
-__device__ __forceinline__ LawD law_d(const DevState *st, int cls)
+template <typename St>
+__device__ __forceinline__ LawD law_d(St st, int cls)
 {
     LawD K;
     K.D = cls == 0 ? st->D1 : (cls == 2 ? st->D2 : 0.5 * (st->D1 + st->D2));
@@ -1015,17 +1041,17 @@ __device__ __forceinline__ double pair_s64_at(const double (*sj)[TJ], const doub
 }
 
 template <int LAW>
-__device__ void force_unit_sym64(const SysDesc &S, int I, int c, double (*sj)[TJ],
+__device__ void force_unit_sym64(SysRef S, int I, int c, double (*sj)[TJ],
                                  double (*sv)[TJ], double (*rw)[3][TJ])
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double *__restrict__ XS = static_cast<const double *>(S.xs);
-    const double *__restrict__ YS = static_cast<const double *>(S.ys);
-    const double *__restrict__ ZS = static_cast<const double *>(S.zs);
-    const double *__restrict__ VXS = static_cast<const double *>(S.vxs);
-    const double *__restrict__ VYS = static_cast<const double *>(S.vys);
-    const double *__restrict__ VZS = static_cast<const double *>(S.vzs);
-    const DevState *st = S.st;
+    auto *__restrict__ XS = glob<const double>(S.xs);
+    auto *__restrict__ YS = glob<const double>(S.ys);
+    auto *__restrict__ ZS = glob<const double>(S.zs);
+    auto *__restrict__ VXS = glob<const double>(S.vxs);
+    auto *__restrict__ VYS = glob<const double>(S.vys);
+    auto *__restrict__ VZS = glob<const double>(S.vzs);
+    auto *st = cst(S.st);
     const int T = S.ntiles;
     const int slot = I * TJ + tid;
     I64 Ist{XS[slot], YS[slot], ZS[slot], 0.0, 0.0, 0.0};
@@ -1038,7 +1064,7 @@ __device__ void force_unit_sym64(const SysDesc &S, int I, int c, double (*sj)[TJ
     double ax = 0.0, ay = 0.0, az = 0.0;
     const int t0 = I + c * S.ch;
     const int t1 = min(T, t0 + S.ch);
-    double *R = reinterpret_cast<double *>(S.react);
+    auto *R = glob<double>(S.react);
     const size_t roff = react_group_offset(I, T, 1);
     const size_t rlen = (size_t)(T - I - 1) * TJ;
     for (int t = t0; t < t1; ++t) {
@@ -1095,8 +1121,8 @@ __device__ void force_unit_sym64(const SysDesc &S, int I, int c, double (*sj)[TJ
         }
         __syncthreads();  // sj, sv and rw are rewritten by the next tile
     }
-    if (S.perm[slot] >= 0) {
-        double *P = static_cast<double *>(S.part);
+    if (glob<const int32_t>(S.perm)[slot] >= 0) {
+        auto *P = glob<double>(S.part);
         const size_t na = S.nalloc;
         const size_t b = (size_t)c * 3 * na + slot;
         P[b] = ax;
@@ -1112,9 +1138,9 @@ __global__ __launch_bounds__(BT) void k_force_sym64(Launch L)
     __shared__ double sv[LAW == 0 ? 1 : 3][TJ];
     __shared__ double rw[4][3][TJ];
     for (int u = L.unit_base + blockIdx.x; u < L.total_units; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, false)];
-        const int2 ic = reinterpret_cast<const int2 *>(S.units)[u - S.unit_begin];
-        force_unit_sym64<LAW>(S, ic.x, ic.y, sj, sv, rw);
+        SysRef S = cst(L.sys)[find_sys(L, u, false)];
+        const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
+        force_unit_sym64<LAW>(S, gc[0], gc[1], sj, sv, rw);
     }
 }
 
@@ -1124,13 +1150,13 @@ __global__ __launch_bounds__(BT) void k_combine_sym64(Launch L)
 {
     const int e = threadIdx.x;
     for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_tile_sys(L, u)];
+        SysRef S = cst(L.sys)[find_tile_sys(L, u)];
         const int J = u - S.tunit_begin;
         const int T = S.ntiles;
         const int slot = J * TJ + e;
-        const int idx = S.perm[slot];
+        const int idx = glob<const int32_t>(S.perm)[slot];
         if (idx < 0) continue;
-        const double *P = static_cast<const double *>(S.part);
+        auto *P = glob<const double>(S.part);
         const double *R = reinterpret_cast<const double *>(S.react);
         const size_t na = S.nalloc;
         const int cj = (T - J + S.ch - 1) / S.ch;  // the chunk count of the element's own row
@@ -1160,10 +1186,10 @@ __global__ __launch_bounds__(BT) void k_combine_sym64(Launch L)
             }
             out[d] = sum;
         }
-        const double gm = S.st->gm_d;
-        static_cast<double *>(S.ax)[idx] = gm * out[0];
-        static_cast<double *>(S.ay)[idx] = gm * out[1];
-        static_cast<double *>(S.az)[idx] = gm * out[2];
+        const double gm = glob<DevState>(S.st)->gm_d;
+        glob<double>(S.ax)[idx] = gm * out[0];
+        glob<double>(S.ay)[idx] = gm * out[1];
+        glob<double>(S.az)[idx] = gm * out[2];
     }
 }
 
@@ -1174,12 +1200,12 @@ __global__ __launch_bounds__(BT) void k_combine_sym64(Launch L)
 __global__ __launch_bounds__(BT) void k_combine_f32(Launch L)
 {
     for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_tile_sys(L, u)];
+        SysRef S = cst(L.sys)[find_tile_sys(L, u)];
         if (S.nsplit == 1) continue;
         const int slot = (u - S.tunit_begin) * TJ + threadIdx.x;
-        const int idx = S.perm[slot];
+        const int idx = glob<const int32_t>(S.perm)[slot];
         if (idx < 0) continue;
-        const float *P = static_cast<const float *>(S.part);
+        auto *P = glob<const float>(S.part);
         const size_t na = S.nalloc;
         float out[3];
         for (int d = 0; d < 3; ++d) {
@@ -1187,33 +1213,42 @@ __global__ __launch_bounds__(BT) void k_combine_f32(Launch L)
             for (int c = 0; c < S.nsplit; ++c) sum += P[(size_t)c * 3 * na + d * na + slot];
             out[d] = sum;
         }
-        const float gm = S.st->gm_f;
-        static_cast<float *>(S.ax)[idx] = gm * out[0];
-        static_cast<float *>(S.ay)[idx] = gm * out[1];
-        static_cast<float *>(S.az)[idx] = gm * out[2];
+        const float gm = glob<DevState>(S.st)->gm_f;
+        glob<float>(S.ax)[idx] = gm * out[0];
+        glob<float>(S.ay)[idx] = gm * out[1];
+        glob<float>(S.az)[idx] = gm * out[2];
     }
 }
 
 // ------------------------------------------------------------------ leap-frog and L1 plane
 
-template <typename T>
-__device__ __forceinline__ T h_of(const DevState *st);
-template <>
-__device__ __forceinline__ float h_of<float>(const DevState *st) { return st->h_f; }
-template <>
-__device__ __forceinline__ double h_of<double>(const DevState *st) { return st->h_d; }
-template <typename T>
-__device__ __forceinline__ T dt_of(const DevState *st);
-template <>
-__device__ __forceinline__ float dt_of<float>(const DevState *st) { return st->dt_f; }
-template <>
-__device__ __forceinline__ double dt_of<double>(const DevState *st) { return st->dt; }
-template <typename T>
-__device__ __forceinline__ T gm_of(const DevState *st);
-template <>
-__device__ __forceinline__ float gm_of<float>(const DevState *st) { return st->gm_f; }
-template <>
-__device__ __forceinline__ double gm_of<double>(const DevState *st) { return st->gm_d; }
+template <typename T, typename St>
+__device__ __forceinline__ T h_of(St st)
+{
+    if constexpr (sizeof(T) == 4) {
+        return st->h_f;
+    } else {
+        return st->h_d;
+    }
+}
+template <typename T, typename St>
+__device__ __forceinline__ T dt_of(St st)
+{
+    if constexpr (sizeof(T) == 4) {
+        return st->dt_f;
+    } else {
+        return st->dt;
+    }
+}
+template <typename T, typename St>
+__device__ __forceinline__ T gm_of(St st)
+{
+    if constexpr (sizeof(T) == 4) {
+        return st->gm_f;
+    } else {
+        return st->gm_d;
+    }
+}
 
 // Per-unit record of a step: each star's position sums and the count of non-finite elements.
 __device__ __forceinline__ void add_stats(double (&v)[7], double px, double py, double pz,
@@ -1230,13 +1265,13 @@ __device__ __forceinline__ void add_stats(double (&v)[7], double px, double py, 
 
 // The step that the second kick completes: its number, and its L1 counts cleared for k_advance,
 // whose workgroups add to them. Called by one thread of a system.
-__device__ __forceinline__ void begin_counts(const SysDesc &S)
+__device__ __forceinline__ void begin_counts(SysRef S)
 {
-    DevState *st = S.st;
+    auto *st = glob<DevState>(S.st);
     const int64_t step = st->step + 1;
     st->step = step;
     st->n_past = st->fwd = st->bwd = 0;
-    int32_t *row = S.l1_log + 4 * (size_t)(step % L1_LOG_CAP);
+    auto *row = glob<int32_t>(S.l1_log) + 4 * (size_t)(step % L1_LOG_CAP);
     row[0] = (int32_t)step;
     row[1] = row[2] = row[3] = 0;
 }
@@ -1248,29 +1283,29 @@ __global__ __launch_bounds__(BT) void k_kick_stats(Launch L, int do_kick)
 {
     __shared__ double lds[7][BT / 64];
     for (int u = L.ounit_base + blockIdx.x; u < L.total_ounits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, true)];
+        SysRef S = cst(L.sys)[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
         double v[7] = {0, 0, 0, 0, 0, 0, 0};
         if (i < S.n) {
-            T *vx = static_cast<T *>(S.vx), *vy = static_cast<T *>(S.vy),
-              *vz = static_cast<T *>(S.vz);
+            auto *vx = glob<T>(S.vx), *vy = glob<T>(S.vy),
+              *vz = glob<T>(S.vz);
             T wx = vx[i], wy = vy[i], wz = vz[i];
             if (do_kick) {
-                const T h = h_of<T>(S.st);
-                wx = wx + h * static_cast<const T *>(S.ax)[i];
-                wy = wy + h * static_cast<const T *>(S.ay)[i];
-                wz = wz + h * static_cast<const T *>(S.az)[i];
+                const T h = h_of<T>(glob<const DevState>(S.st));
+                wx = wx + h * glob<const T>(S.ax)[i];
+                wy = wy + h * glob<const T>(S.ay)[i];
+                wz = wz + h * glob<const T>(S.az)[i];
                 vx[i] = wx;
                 vy[i] = wy;
                 vz[i] = wz;
             }
-            add_stats(v, static_cast<const T *>(S.x)[i], static_cast<const T *>(S.y)[i],
-                      static_cast<const T *>(S.z)[i], wx, wy, wz, i >= S.n1);
+            add_stats(v, glob<const T>(S.x)[i], glob<const T>(S.y)[i],
+                      glob<const T>(S.z)[i], wx, wy, wz, i >= S.n1);
         }
         block_sum<7>(v, lds);
         if (threadIdx.x == 0) {
-            double *r = S.rec + (size_t)local * REC_STRIDE;
+            auto *r = glob<double>(S.rec) + (size_t)local * REC_STRIDE;
             for (int k = 0; k < 7; ++k) r[k] = v[k];
             if (do_kick && local == 0) begin_counts(S);
         }
@@ -1298,12 +1333,12 @@ struct OneSidedLaw;
 template <>
 struct OneSidedLaw<float> {
     LawF k;
-    __device__ __forceinline__ void load(const DevState *st, int cls) { k = law_f(st, cls); }
+    __device__ __forceinline__ void load(Const<DevState> *st, int cls) { k = law_f(st, cls); }
 };
 template <>
 struct OneSidedLaw<double> {
     LawD k;
-    __device__ __forceinline__ void load(const DevState *st, int cls) { k = law_d(st, cls); }
+    __device__ __forceinline__ void load(Const<DevState> *st, int cls) { k = law_d(st, cls); }
 };
 
 template <int LAW>
@@ -1373,16 +1408,16 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
     __shared__ T part[BT / 64][IB][3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int u = L.unit_base + blockIdx.x;
-    const SysDesc &S = L.sys[find_sys(L, u, false)];
+    SysRef S = cst(L.sys)[find_sys(L, u, false)];
     const int local = u - S.unit_begin;
     const int n = S.n, n1 = S.n1;
-    const DevState *st = S.st;
-    const T *__restrict__ X = static_cast<const T *>(S.x);
-    const T *__restrict__ Y = static_cast<const T *>(S.y);
-    const T *__restrict__ Z = static_cast<const T *>(S.z);
-    const T *__restrict__ VX = static_cast<const T *>(do_kick ? S.vxs : S.vx);
-    const T *__restrict__ VY = static_cast<const T *>(do_kick ? S.vys : S.vy);
-    const T *__restrict__ VZ = static_cast<const T *>(do_kick ? S.vzs : S.vz);
+    auto *st = cst(S.st);
+    auto *__restrict__ X = glob<const T>(S.x);
+    auto *__restrict__ Y = glob<const T>(S.y);
+    auto *__restrict__ Z = glob<const T>(S.z);
+    auto *__restrict__ VX = glob<const T>(do_kick ? S.vxs : S.vx);
+    auto *__restrict__ VY = glob<const T>(do_kick ? S.vys : S.vy);
+    auto *__restrict__ VZ = glob<const T>(do_kick ? S.vzs : S.vz);
     // star 1's elements take the first ceil(n1 / IB) workgroups
     const int b1 = (n1 + IB - 1) / IB;
     const int istar = local >= b1 ? 1 : 0;
@@ -1472,13 +1507,13 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
         }
         const T gm = gm_of<T>(st);
         const T ax = gm * t[0], ay = gm * t[1], az = gm * t[2];
-        static_cast<T *>(S.ax)[i] = ax;
-        static_cast<T *>(S.ay)[i] = ay;
-        static_cast<T *>(S.az)[i] = az;
+        glob<T>(S.ax)[i] = ax;
+        glob<T>(S.ay)[i] = ay;
+        glob<T>(S.az)[i] = az;
         if (do_kick) {
             const T h = h_of<T>(st);
-            T *vx = static_cast<T *>(S.vx), *vy = static_cast<T *>(S.vy),
-              *vz = static_cast<T *>(S.vz);
+            auto *vx = glob<T>(S.vx), *vy = glob<T>(S.vy),
+              *vz = glob<T>(S.vz);
             const T wx = vx[i] + h * ax, wy = vy[i] + h * ay, wz = vz[i] + h * az;
             vx[i] = wx;
             vy[i] = wy;
@@ -1493,7 +1528,7 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
         for (int w = IB / 2; w >= 1; w /= 2) v[k] += __shfl_xor(v[k], w, 64);
     }
     if (lane == 0) {
-        double *r = S.rec + (size_t)local * REC_STRIDE;
+        auto *r = glob<double>(S.rec) + (size_t)local * REC_STRIDE;
 #pragma unroll
         for (int k = 0; k < 7; ++k) r[k] = v[k];
         if (local == 0) begin_counts(S);
@@ -1509,18 +1544,18 @@ struct Plane {
 };
 
 // The system's records summed by one workgroup, in the same order wherever it is done.
-__device__ __forceinline__ void sum_records(const SysDesc &S, int n_rec, double (&v)[7],
+__device__ __forceinline__ void sum_records(SysRef S, int n_rec, double (&v)[7],
                                             double (*lds)[BT / 64])
 {
     for (int k = 0; k < 7; ++k) v[k] = 0.0;
     for (int u = threadIdx.x; u < n_rec; u += BT) {
-        const double *r = S.rec + (size_t)u * REC_STRIDE;
+        auto *r = glob<const double>(S.rec) + (size_t)u * REC_STRIDE;
         for (int k = 0; k < 7; ++k) v[k] += r[k];
     }
     block_sum<7>(v, lds);
 }
 
-__device__ __forceinline__ void plane_of(const SysDesc &S, const double (&v)[7], Plane &p)
+__device__ __forceinline__ void plane_of(SysRef S, const double (&v)[7], Plane &p)
 {
     const int n1 = S.n1, n2 = S.n - S.n1;
     for (int d = 0; d < 3; ++d) {
@@ -1531,15 +1566,15 @@ __device__ __forceinline__ void plane_of(const SysDesc &S, const double (&v)[7],
     const double dist = sqrt(p.e[0] * p.e[0] + p.e[1] * p.e[1] + p.e[2] * p.e[2]);
     p.ok = (n1 > 0 && n2 > 0 && dist > 0.0) ? 1 : 0;
     for (int d = 0; d < 3; ++d) p.e[d] = p.ok ? p.e[d] / dist : 0.0;
-    p.xi_cut = S.st->xi_l1 * dist;
+    p.xi_cut = glob<DevState>(S.st)->xi_l1 * dist;
 }
 
 // Records the plane and the non-finite count, and (optionally) applies the donor growth update
 // with the derived force constants. Called by one thread of a system.
-__device__ __forceinline__ void finish_step(const SysDesc &S, const Plane &p, double nonfinite,
+__device__ __forceinline__ void finish_step(SysRef S, const Plane &p, double nonfinite,
                                             int do_growth)
 {
-    DevState *st = S.st;
+    auto *st = glob<DevState>(S.st);
     for (int d = 0; d < 3; ++d) {
         st->com1[d] = p.com1[d];
         st->com2[d] = p.com2[d];
@@ -1574,7 +1609,7 @@ __global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int do_growth)
 {
     __shared__ double lds[7][BT / 64];
     for (int s = blockIdx.x; s < L.n_sys; s += gridDim.x) {
-        const SysDesc &S = L.sys[s];
+        SysRef S = cst(L.sys)[s];
         if (S.n_ounits <= COM_FUSE_UNITS) continue;
         double v[7];
         sum_records(S, S.n_ounits, v, lds);
@@ -1602,10 +1637,10 @@ __global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
     __shared__ Plane pl;
     __shared__ int cnt[3][BT / 64];
     for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, true)];
+        SysRef S = cst(L.sys)[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
-        T *x = static_cast<T *>(S.x), *y = static_cast<T *>(S.y), *z = static_cast<T *>(S.z);
+        auto *x = glob<T>(S.x), *y = glob<T>(S.y), *z = glob<T>(S.z);
         T px = 0, py = 0, pz = 0;
         if (i < S.n) {
             px = x[i];
@@ -1613,7 +1648,7 @@ __global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
             pz = z[i];
         }
         if (finish) {
-            DevState *st = S.st;
+            auto *st = glob<DevState>(S.st);
             if (S.n_ounits <= COM_FUSE_UNITS) {
                 double v[7];
                 sum_records(S, finish == ADV_INIT ? S.n_ounits : S.n_rec, v, lds);
@@ -1637,11 +1672,11 @@ __global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
                                   ((double)pz - pl.com1[2]) * pl.e[2];
                 past = pl.ok && xi < pl.xi_cut;
                 if (finish != ADV_INIT) {
-                    const bool prev = S.side[i] != 0;
+                    const bool prev = glob<int8_t>(S.side)[i] != 0;
                     fwd = past && !prev;
                     bwd = !past && prev;
                 }
-                S.side[i] = past ? 1 : 0;
+                glob<int8_t>(S.side)[i] = past ? 1 : 0;
             }
             const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
             const int c0 = __popcll(__ballot(past)), c1 = __popcll(__ballot(fwd)),
@@ -1656,19 +1691,20 @@ __global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
                 const int k = threadIdx.x;
                 const int c = cnt[k][0] + cnt[k][1] + cnt[k][2] + cnt[k][3];
                 if (c != 0) {
-                    atomicAdd(k == 0 ? &st->n_past : (k == 1 ? &st->fwd : &st->bwd), c);
+                    DevState *w = S.st;
+                    atomicAdd(k == 0 ? &w->n_past : (k == 1 ? &w->fwd : &w->bwd), c);
                     if (finish != ADV_INIT)
                         atomicAdd(S.l1_log + 4 * (size_t)(st->step % L1_LOG_CAP) + 1 + k, c);
                 }
             }
         }
         if (kick && i < S.n) {
-            const T h = h_of<T>(S.st), dt = dt_of<T>(S.st);
-            T *vx = static_cast<T *>(S.vx), *vy = static_cast<T *>(S.vy),
-              *vz = static_cast<T *>(S.vz);
-            const T nvx = vx[i] + h * static_cast<const T *>(S.ax)[i];
-            const T nvy = vy[i] + h * static_cast<const T *>(S.ay)[i];
-            const T nvz = vz[i] + h * static_cast<const T *>(S.az)[i];
+            const T h = h_of<T>(glob<const DevState>(S.st)), dt = dt_of<T>(glob<const DevState>(S.st));
+            auto *vx = glob<T>(S.vx), *vy = glob<T>(S.vy),
+              *vz = glob<T>(S.vz);
+            const T nvx = vx[i] + h * glob<const T>(S.ax)[i];
+            const T nvy = vy[i] + h * glob<const T>(S.ay)[i];
+            const T nvz = vz[i] + h * glob<const T>(S.az)[i];
             vx[i] = nvx;
             vy[i] = nvy;
             vz[i] = nvz;
@@ -1678,9 +1714,9 @@ __global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
             if (S.one_sided && S.vxs) {
                 // the one-sided force kernel kicks its own elements while others read the
                 // half-step velocities of eqs. (4)-(6)
-                static_cast<T *>(S.vxs)[i] = nvx;
-                static_cast<T *>(S.vys)[i] = nvy;
-                static_cast<T *>(S.vzs)[i] = nvz;
+                glob<T>(S.vxs)[i] = nvx;
+                glob<T>(S.vys)[i] = nvy;
+                glob<T>(S.vzs)[i] = nvz;
             }
         }
         __syncthreads();  // pl and cnt are rewritten by the next unit
@@ -1699,17 +1735,17 @@ __global__ __launch_bounds__(BT) void k_diag_partials(Launch L)
 {
     __shared__ double lds[10][BT / 64];
     for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, true)];
+        SysRef S = cst(L.sys)[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
         double v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         if (i < S.n) {
-            const double m = S.st->m;
-            const double x = static_cast<const T *>(S.x)[i], y = static_cast<const T *>(S.y)[i],
-                         z = static_cast<const T *>(S.z)[i];
-            const double vx = static_cast<const T *>(S.vx)[i],
-                         vy = static_cast<const T *>(S.vy)[i],
-                         vz = static_cast<const T *>(S.vz)[i];
+            const double m = glob<DevState>(S.st)->m;
+            const double x = glob<const T>(S.x)[i], y = glob<const T>(S.y)[i],
+                         z = glob<const T>(S.z)[i];
+            const double vx = glob<const T>(S.vx)[i],
+                         vy = glob<const T>(S.vy)[i],
+                         vz = glob<const T>(S.vz)[i];
             v[0] = m * x;
             v[1] = m * y;
             v[2] = m * z;
@@ -1723,7 +1759,7 @@ __global__ __launch_bounds__(BT) void k_diag_partials(Launch L)
         }
         block_sum<10>(v, lds);
         if (threadIdx.x == 0) {
-            double *r = S.red + (size_t)local * RED_STRIDE + RED_DIAG;
+            auto *r = glob<double>(S.red) + (size_t)local * RED_STRIDE + RED_DIAG;
             for (int k = 0; k < 10; ++k) r[k] = v[k];
         }
     }
@@ -1763,7 +1799,7 @@ __device__ __forceinline__ double pair_u(double r2, double D, double A, double e
 }
 
 // Real elements of a tile: they come first in it.
-__device__ __forceinline__ int tile_count(const SysDesc &S, int t)
+__device__ __forceinline__ int tile_count(SysRef S, int t)
 {
     const int end = t * TJ >= S.p1 ? S.p1 + (S.n - S.n1) : S.n1;
     return min(TJ, max(0, end - t * TJ));
@@ -1774,14 +1810,14 @@ __global__ __launch_bounds__(BT) void k_pe(Launch L)
 {
     __shared__ double sh[TJ][4];
     __shared__ double lds[1][BT / 64];
-    const SysDesc &S = L.sys[0];
+    SysRef S = cst(L.sys)[0];
     const int I = blockIdx.x % S.ntiles, c = blockIdx.x / S.ntiles;
     const int t0 = I + c * S.pe_ch, t1 = min(S.ntiles, t0 + S.pe_ch);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const DevState *st = S.st;
-    const T *XS = static_cast<const T *>(S.xs), *YS = static_cast<const T *>(S.ys),
-            *ZS = static_cast<const T *>(S.zs);
+    auto *st = cst(S.st);
+    auto *XS = glob<const T>(S.xs), *YS = glob<const T>(S.ys),
+            *ZS = glob<const T>(S.zs);
     const double A = st->G * st->m * st->m, eps = st->leps_d;
     const double go = st->gamma * PI_D / 48.0;
     const int istar = I * TJ >= S.p1 ? 1 : 0, ni = tile_count(S, I);
@@ -1794,7 +1830,7 @@ __global__ __launch_bounds__(BT) void k_pe(Launch L)
         z[k] = ZS[slot];
         acc[k] = 0.0;
     }
-    const float *bi = S.tbox + (size_t)I * 8;
+    auto *bi = cst(S.tbox) + (size_t)I * 8;
     const float lo[3] = {bi[0], bi[1], bi[2]}, hi[3] = {bi[4], bi[5], bi[6]};
     for (int t = t0; t < t1; ++t) {
         sh[tid][0] = XS[t * TJ + tid];
@@ -1805,7 +1841,7 @@ __global__ __launch_bounds__(BT) void k_pe(Launch L)
         const double D = cls == 0 ? st->D1 : (cls == 2 ? st->D2 : 0.5 * (st->D1 + st->D2));
         const int j1 = min(64, tile_count(S, t) - 64 * wave);
         const double(*sj)[4] = sh + 64 * wave;
-        if (far_tile(S.tbox + (size_t)t * 8, lo, hi, st->far2f[cls])) {
+        if (far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi, st->far2f[cls])) {
             for (int j = 0; j < j1; ++j) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -1834,25 +1870,25 @@ __global__ __launch_bounds__(BT) void k_pe(Launch L)
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[0] += 64 * k + lane < ni ? acc[k] : 0.0;
     block_sum<1>(v, lds);
-    if (tid == 0) S.pe_part[blockIdx.x] = LAW == 0 ? -A * v[0] : -v[0];
+    if (tid == 0) glob<double>(S.pe_part)[blockIdx.x] = LAW == 0 ? -A * v[0] : -v[0];
 }
 
 __global__ __launch_bounds__(BT) void k_finalize_diag(Launch L, int with_pe)
 {
     __shared__ double lds[11][BT / 64];
     for (int s = blockIdx.x; s < L.n_sys; s += gridDim.x) {
-        const SysDesc &S = L.sys[s];
+        SysRef S = cst(L.sys)[s];
         double v[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         for (int u = threadIdx.x; u < S.n_ounits; u += BT) {
-            const double *r = S.red + (size_t)u * RED_STRIDE + RED_DIAG;
+            auto *r = glob<const double>(S.red) + (size_t)u * RED_STRIDE + RED_DIAG;
             for (int k = 0; k < 10; ++k) v[k] += r[k];
         }
         if (with_pe) {
-            for (int u = threadIdx.x; u < S.n_peunits; u += BT) v[10] += S.pe_part[u];
+            for (int u = threadIdx.x; u < S.n_peunits; u += BT) v[10] += glob<double>(S.pe_part)[u];
         }
         block_sum<11>(v, lds);
         if (threadIdx.x == 0) {
-            const double M = S.st->m * (double)S.n;
+            const double M = glob<DevState>(S.st)->m * (double)S.n;
             DiagOut *o = S.diag;
             for (int d = 0; d < 3; ++d) o->v[d] = M > 0.0 ? v[d] / M : 0.0;
             for (int k = 3; k < 11; ++k) o->v[k] = v[k];
@@ -1869,18 +1905,18 @@ __global__ __launch_bounds__(BT) void k_ret_vsum(Launch L)
 {
     __shared__ double lds[3][BT / 64];
     for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, true)];
+        SysRef S = cst(L.sys)[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
         double v[3] = {0, 0, 0};
         if (i < S.n1) {
-            v[0] = static_cast<const T *>(S.vx)[i];
-            v[1] = static_cast<const T *>(S.vy)[i];
-            v[2] = static_cast<const T *>(S.vz)[i];
+            v[0] = glob<const T>(S.vx)[i];
+            v[1] = glob<const T>(S.vy)[i];
+            v[2] = glob<const T>(S.vz)[i];
         }
         block_sum<3>(v, lds);
         if (threadIdx.x == 0) {
-            double *r = S.red + (size_t)local * RED_STRIDE + RED_RET;
+            auto *r = glob<double>(S.red) + (size_t)local * RED_STRIDE + RED_RET;
             for (int k = 0; k < 3; ++k) r[k] = v[k];
         }
     }
@@ -1891,15 +1927,15 @@ __global__ __launch_bounds__(BT) void k_ret_mean(Launch L)
 {
     __shared__ double lds[3][BT / 64];
     for (int s = blockIdx.x; s < L.n_sys; s += gridDim.x) {
-        const SysDesc &S = L.sys[s];
+        SysRef S = cst(L.sys)[s];
         double v[3] = {0, 0, 0};
         for (int u = threadIdx.x; u < S.n_ounits; u += BT) {
-            const double *r = S.red + (size_t)u * RED_STRIDE + RED_RET;
+            auto *r = glob<const double>(S.red) + (size_t)u * RED_STRIDE + RED_RET;
             for (int k = 0; k < 3; ++k) v[k] += r[k];
         }
         block_sum<3>(v, lds);
         if (threadIdx.x == 0) {
-            for (int k = 0; k < 3; ++k) S.st->v1[k] = S.n1 > 0 ? v[k] / (double)S.n1 : 0.0;
+            for (int k = 0; k < 3; ++k) glob<DevState>(S.st)->v1[k] = S.n1 > 0 ? v[k] / (double)S.n1 : 0.0;
         }
         __syncthreads();
     }
@@ -1913,20 +1949,20 @@ __global__ __launch_bounds__(BT) void k_ret_count(Launch L)
 {
     __shared__ double lds[2][BT / 64];
     for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
-        const SysDesc &S = L.sys[find_sys(L, u, true)];
+        SysRef S = cst(L.sys)[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
-        const DevState *st = S.st;
+        const auto *st = glob<const DevState>(S.st);
         double v[2] = {0, 0};
         if (i < S.n && i >= S.n1 && S.n1 > 0 && st->plane_ok) {
-            const double rx = (double)static_cast<const T *>(S.x)[i] - st->com1[0];
-            const double ry = (double)static_cast<const T *>(S.y)[i] - st->com1[1];
-            const double rz = (double)static_cast<const T *>(S.z)[i] - st->com1[2];
+            const double rx = (double)glob<const T>(S.x)[i] - st->com1[0];
+            const double ry = (double)glob<const T>(S.y)[i] - st->com1[1];
+            const double rz = (double)glob<const T>(S.z)[i] - st->com1[2];
             if (rx * st->e[0] + ry * st->e[1] + rz * st->e[2] < st->xi_cut) {
                 v[0] = 1.0;
-                const double ux = (double)static_cast<const T *>(S.vx)[i] - st->v1[0];
-                const double uy = (double)static_cast<const T *>(S.vy)[i] - st->v1[1];
-                const double uz = (double)static_cast<const T *>(S.vz)[i] - st->v1[2];
+                const double ux = (double)glob<const T>(S.vx)[i] - st->v1[0];
+                const double uy = (double)glob<const T>(S.vy)[i] - st->v1[1];
+                const double uz = (double)glob<const T>(S.vz)[i] - st->v1[2];
                 const double r = sqrt(rx * rx + ry * ry + rz * rz);
                 const double gm1 = st->G * st->m * (double)S.n1;
                 const double energy = 0.5 * (ux * ux + uy * uy + uz * uz) - gm1 / r;
@@ -1935,7 +1971,7 @@ __global__ __launch_bounds__(BT) void k_ret_count(Launch L)
         }
         block_sum<2>(v, lds);
         if (threadIdx.x == 0) {
-            double *r = S.red + (size_t)local * RED_STRIDE + RED_RET + 3;
+            auto *r = glob<double>(S.red) + (size_t)local * RED_STRIDE + RED_RET + 3;
             r[0] = v[0];
             r[1] = v[1];
         }
@@ -1946,17 +1982,17 @@ __global__ __launch_bounds__(BT) void k_ret_total(Launch L)
 {
     __shared__ double lds[2][BT / 64];
     for (int s = blockIdx.x; s < L.n_sys; s += gridDim.x) {
-        const SysDesc &S = L.sys[s];
+        SysRef S = cst(L.sys)[s];
         double v[2] = {0, 0};
         for (int u = threadIdx.x; u < S.n_ounits; u += BT) {
-            const double *r = S.red + (size_t)u * RED_STRIDE + RED_RET + 3;
+            auto *r = glob<const double>(S.red) + (size_t)u * RED_STRIDE + RED_RET + 3;
             v[0] += r[0];
             v[1] += r[1];
         }
         block_sum<2>(v, lds);
         if (threadIdx.x == 0) {
-            S.st->ret_past = (int32_t)v[0];
-            S.st->ret_bound = (int32_t)v[1];
+            glob<DevState>(S.st)->ret_past = (int32_t)v[0];
+            glob<DevState>(S.st)->ret_bound = (int32_t)v[1];
         }
         __syncthreads();
     }
