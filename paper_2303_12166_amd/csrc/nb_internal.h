@@ -7,13 +7,14 @@
 
 namespace nbk {
 
-// Waves per SIMD asked of the compiler (its vector-register cap) for the force kernels, by kernel
-// and band height (1, 2, 4 tile rows per lane): measured choices.
+// Waves per SIMD asked of the compiler (its vector-register cap) for the force kernels: the most
+// at which the pair loops do not spill (under eqs. (4)-(6) at two rows 16 values spill outside
+// them; three waves without measured 1.5 % slower at 40,009 elements).
 constexpr int PLAIN_WAVES = 8;
-constexpr int SYM_WAVES[3] = {6, 5, 4};
-constexpr int SYM_PAPER_WAVES[3] = {6, 5, 4};  // eqs. (4)-(6): at one row a few per-tile values
-                                               // spill, none inside the pair loop; faster than 5
-                                               // waves without spills
+constexpr int rows_waves(bool fp64, int law, int r)
+{
+    return fp64 ? (law == 0 ? 3 : 2) : (r == 1 && law == 0 ? 5 : 4);
+}
 
 constexpr int BT = 256;          // threads per block, every kernel
 constexpr int TJ = 256;          // j elements staged in LDS per tile (one per thread)

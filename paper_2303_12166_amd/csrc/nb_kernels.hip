@@ -3,13 +3,13 @@
 // The O(N^2) all-pairs force evaluation (Methodology: every element moves only under the sum of
 // all pairwise element-element interactions) is the hot path. It runs on the FP32 vector ALUs:
 // the pair sum is not a dense contraction, so there is no MFMA here. The kernels that evaluate it:
-//   - k_force_sym<KR> / k_force_sym_paper<KR> (FP32, Kahan mode, the default): each unordered
-//     pair once, bands of KR tile rows with one i element of each row per lane in registers and
-//     the j sums rotating across the wave (see the section below), contact law / eqs. (4)-(6);
+//   - k_force_rows<T, LAW, R, BAND> (FP32 Kahan and FP64 modes): each unordered pair once, 4 R i elements
+//     per lane in registers and the j sums rotating across the wave (see below);
+//   - k_force_one_sided<T, LAW> (the same modes, small systems): every ordered pair, in element
+//     order, with the second kick;
 //   - k_force_f32 (FP32, plain mode): one-sided, one i element per lane, the block streams
-//     256-element SoA j tiles through LDS (broadcast ds_read_b128), one FP32 running sum;
-//   - k_force_sym64<LAW> (FP64 reference mode): the symmetric scheme in FP64, both element laws.
-// All of them work on a Morton-sorted, star-by-star padded copy of the positions; the FP32 ones
+//     256-element SoA j tiles through LDS (broadcast ds_read_b128), one FP32 running sum.
+// The first and the last work on a Morton-sorted, star-by-star padded copy of the positions and
 // skip the contact test on tiles whose bounding boxes are at least D apart. Per pair of the
 // contact law:
 //   d = r_j - r_i,  r2 = d.d + eps,  w = rsqrt(r2)  (v_rsq_f32),
@@ -393,38 +393,41 @@ void k_force_f32(Launch L)
     }
 }
 
-// ------------------------------------------------------------------ FP32 symmetric force kernel
+// ------------------------------------------------------------------ symmetric force kernel
 //
 // Newton's third law halves the pair work: the pair (i, j) with i in tile I and j in a later
 // tile J > I is evaluated once. The tile rows are taken in groups ("row bands") of KR consecutive
-// rows (KR = 1, 2 or 4, chosen per system size): a work unit is group g, rows I = KR g .. KR g +
-// KR - 1, against chunk c of its tiles, a run of `ch` tiles starting at KR g + c ch. Each lane of
-// the block's four waves keeps one i element of every row of the band, at the same position in
-// each row. A tile's 256 j elements are taken as four groups of 64. At step s (0..63) lane l
-// meets element (l - s) mod 64 of each group: its position is read from LDS once at that
-// rotating offset and paired with the lane's KR i elements, and the j accumulator travels with
-// it, one lane per step: in short bands by a DPP wave rotation fused into the first row's update
-// a_j <- rotate(a_j) + s (r_j - r_i), in tall ones through the LDS crossbar after the group's
-// last row (see sym_tile); the rows add their terms in row order, and the sums change sign when
-// they are stored (an added term takes the short form of the fused multiply-add). After 64 steps and the last
-// move every lane holds the summed reaction of the wave's 64 KR i elements on its own j. The
-// waves' sums are added in wave order and stored once per (group, tile): a band of KR rows
-// stores 1/KR of the reaction blocks of single rows. Tiles inside the band are split by row:
-// tile KR g + k is one-sided for row k, full for the rows before it and skipped by the rows
-// after it. k_combine_sym adds, per element, its own row's chunk partials and then the reactions
-// of every group with a row before the element's tile, in group order, with Kahan compensation.
-// The order of every sum is fixed by the system's own size, so results do not depend on
-// scheduling or on the other systems of a launch.
+// rows (KR = 1, 2 or 4, chosen per system size; 1 in the FP64 mode): a work unit is group g, rows
+// I = KR g .. KR g + KR - 1, against chunk c of its tiles, a run of `ch` tiles starting at KR g +
+// c ch. The kernel holds R rows at a time (1 or 2; a band of four is taken two rows after the
+// other). The tiles after a unit's rows are full pairs; of the tiles inside the band, tile KR g + k
+// is one-sided for row k, full for the rows before it and skipped by the rows after it.
+//
+// The j are split over the block's four waves: every wave holds all 256 R elements i, 4 R per lane,
+// and wave w takes the 64 j of quarter w of each tile. At step s (0..63) lane l meets element
+// (l - s) mod 64 of them: its position is read from LDS once and paired with the lane's 4 R
+// elements, and the j accumulator travels with it, one lane per step, through the LDS crossbar.
+// After 64 steps lane l holds the whole reaction of the 256 R elements on its own j and stores it
+// (with its sign turned: an added term takes the short form of the fused multiply-add). So a j read
+// and a move of its sums serve 4 R pairs, and the waves share nothing inside the loop: each
+// stages its own 64 j, with no barrier and no sum across waves per tile; their i sums, one FP32
+// partial per tile under Kahan compensation, are added once per unit. A kernel with the i split
+// over the waves instead (one element of each row per lane, KR pairs per read, the reactions of
+// the four waves added through LDS) held four rows at most and needs twice the LDS traffic at
+// the same registers. Measured against it, whole evaluations at the best split of either:
+// contact law 97 -> 77 us at N = 16,384, 241 -> 217 at 32,768, 747 -> 724 at 65,536, 10.69 -> 10.15
+// ms at 262,144; eqs. (4)-(6) 61 -> 50 us at 9,000, 458 -> 412 at 40,009, 13.97 -> 12.90 ms at
+// 262,144; FP64 176 -> 156 us at 16,384, 1082 -> 965 at 50,021, eqs. (4)-(6) 216 -> 197 at 16,384.
+// What bounds it: at 262,144 FP32 issue at the clock that the chip's power leaves (about 2.1 GHz
+// of 2.4); below some 20,000 elements the few, long units.
+//
+// k_combine_sym adds, per element, its own row's chunk partials and then the reactions of every
+// group with a row before the element's tile, in group order, with Kahan compensation. The order
+// of every sum is fixed by the system's own size, so results do not depend on scheduling or on
+// the other systems of a launch.
 
-constexpr int DPP_WAVE_ROR1 = 0x13C;  // lane l receives lane l - 1 (mod 64)
-
-__device__ __forceinline__ float wave_ror1(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), DPP_WAVE_ROR1, 0xf, 0xf, true));
-}
-
-// The same move through the LDS crossbar (ds_bpermute, no LDS storage): addr = 4 ((l - 1) mod 64)
-// in lane l.
+// Lane l receives lane l - 1's value (mod 64) through the LDS crossbar (ds_bpermute, no LDS
+// storage): addr = 4 ((l - 1) mod 64) in lane l.
 __device__ __forceinline__ float xbar_ror1(float v, int addr)
 {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v)));
@@ -505,123 +508,6 @@ __device__ __forceinline__ float pair_s(float r2, float dx, float dy, float dz, 
     }
 }
 
-// The i side of a band: one element of each of KR tile rows per lane.
-template <int KR>
-struct Band {
-    float x[KR], y[KR], z[KR];     // positions
-    float ax[KR], ay[KR], az[KR];  // sums over the current tile
-    float4 v[KR];                  // half-step velocities (eqs. 4-6 only)
-};
-
-// One-sided diagonal tile of one row from an AoS LDS tile (x, y, z, unused). The self pair has
-// d = 0; under eqs. (4)-(6) it is also masked, since its overlap term is of order 1/eps.
-template <int LAW>
-__device__ __forceinline__ void diag_tile(const float4 *__restrict__ sj,
-                                          const float4 *__restrict__ sv, float xi, float yi,
-                                          float zi, const float4 &vi, const LawF &K, float &ax,
-                                          float &ay, float &az)
-{
-    const float eps = 1.0e-24f;
-    const int self = threadIdx.x;
-#pragma unroll 4
-    for (int jj = 0; jj < TJ; ++jj) {
-        const float4 P = sj[jj];
-        const float dx = P.x - xi;
-        const float dy = P.y - yi;
-        const float dz = P.z - zi;
-        const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps)));
-        float s;
-        if constexpr (LAW == 0) {
-            s = pair_s<0, true>(r2, dx, dy, dz, vi, vi, K);
-        } else {
-            s = pair_s<LAW, true>(r2, dx, dy, dz, sv[jj], vi, K);
-            s = jj == self ? 0.0f : s;
-        }
-        ax = fmaf(s, dx, ax);
-        ay = fmaf(s, dy, ay);
-        az = fmaf(s, dz, az);
-    }
-}
-
-// A full tile against the band's rows 0 .. nact - 1 (all KR rows unless MASKED; nact >= 1), with
-// the reactions on the tile's 256 j left in the wave's rw slice.
-template <bool NEAR, int LAW, int KR, bool MASKED>
-__device__ __forceinline__ void sym_tile(const float4 *__restrict__ sj,
-                                         const float4 *__restrict__ sv, Band<KR> &B,
-                                         const LawF (&K)[KR], float *rwx, float *rwy, float *rwz,
-                                         int lane, int nact)
-{
-    // The j sums move one lane per step (lane l takes lane l - 1's sums). With one row per band
-    // the move folds into row 0's update, a_j <- rotate(a_j) + p with p = s d kept as an operand
-    // of its own (a VOP2 addition with a DPP source; a fused multiply-add cannot take one).
-    // The other rows add s d to both sums with fused multiply-adds: two instructions per
-    // component instead of three. In taller bands (four rows under the contact law, two or more
-    // under eqs. (4)-(6)) the sums of each j group move through the LDS crossbar (ds_bpermute)
-    // after the group's last row instead, off the vector ALU, and row 0 takes the FMA form too
-    // (measured 6 % faster at four rows under the contact law, 7.5 % at two under eqs. 4-6).
-    // Under the contact law at two rows the DPP form measured 0.5 % faster (its pair code is
-    // the shorter), and at one row three crossbar moves per pair saturate the LDS (half speed).
-#pragma clang fp contract(off)
-    constexpr bool XBAR = LAW == 0 ? KR >= 4 : KR >= 2;
-    const float eps = 1.0e-24f;
-    float ajx[4] = {0.f, 0.f, 0.f, 0.f}, ajy[4] = {0.f, 0.f, 0.f, 0.f};
-    float ajz[4] = {0.f, 0.f, 0.f, 0.f};
-    const int rot_addr = ((lane + 63) & 63) << 2;  // byte address of lane l - 1 (mod 64)
-    for (int st = 0; st < 64; ++st) {
-        const int e = (lane - st) & 63;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float4 P = sj[g * 64 + e];
-            float4 Vj = make_float4(0.f, 0.f, 0.f, 0.f);
-            if constexpr (LAW != 0 && NEAR) Vj = sv[g * 64 + e];
-#pragma unroll
-            for (int r = 0; r < KR; ++r) {
-                if (MASKED && r >= nact) continue;  // wave-uniform
-                const float dx = P.x - B.x[r];
-                const float dy = P.y - B.y[r];
-                const float dz = P.z - B.z[r];
-                const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps)));
-                const float s = pair_s<LAW, NEAR>(r2, dx, dy, dz, Vj, B.v[r], K[r]);
-                if (!XBAR && r == 0) {
-                    const float px = s * dx, py = s * dy, pz = s * dz;
-                    B.ax[r] += px;
-                    B.ay[r] += py;
-                    B.az[r] += pz;
-                    ajx[g] = wave_ror1(ajx[g]) + px;
-                    ajy[g] = wave_ror1(ajy[g]) + py;
-                    ajz[g] = wave_ror1(ajz[g]) + pz;
-                } else {
-                    B.ax[r] = fmaf(s, dx, B.ax[r]);
-                    B.ay[r] = fmaf(s, dy, B.ay[r]);
-                    B.az[r] = fmaf(s, dz, B.az[r]);
-                    ajx[g] = fmaf(s, dx, ajx[g]);
-                    ajy[g] = fmaf(s, dy, ajy[g]);
-                    ajz[g] = fmaf(s, dz, ajz[g]);
-                }
-                // contact law: keep each pair's instructions together. Left free, the scheduler
-                // gathers the twelve rotated updates of a step at its end, and back-to-back DPP
-                // subtractions issue at about a third of the rate of plain ones (measured 11 %
-                // slower at one row per band; with the crossbar form at four rows 1.5 % slower).
-                // The eqs. (4)-(6) loop measured 3.5 % faster without the barrier.
-                if constexpr (LAW == 0) __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (XBAR) {
-                ajx[g] = xbar_ror1(ajx[g], rot_addr);
-                ajy[g] = xbar_ror1(ajy[g], rot_addr);
-                ajz[g] = xbar_ror1(ajz[g], rot_addr);
-            }
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        // element l's sum back in lane l: one more rotation after the last step (the crossbar
-        // form did it already)
-        rwx[g * 64 + lane] = XBAR ? -ajx[g] : -wave_ror1(ajx[g]);
-        rwy[g * 64 + lane] = XBAR ? -ajy[g] : -wave_ror1(ajy[g]);
-        rwz[g * 64 + lane] = XBAR ? -ajz[g] : -wave_ror1(ajz[g]);
-    }
-}
-
 // Reactions are stored per group g (tile rows KR g .. KR g + KR - 1) for the tiles t after the
 // group's first row, t = KR g + 1 .. T - 1: three components one after the other, each
 // (T - KR g - 1) TJ values. Group g starts after
@@ -642,185 +528,6 @@ __device__ __forceinline__ bool far_tile(Const<float> *bx, const float (&lo)[3],
     const float gz = fmaxf(0.0f, fmaxf(bx[2] - hi[2], lo[2] - bx[6]));
     const float gap2 = gx * gx + gy * gy + gz * gz;
     return __builtin_amdgcn_readfirstlane(gap2 >= far2 ? 1 : 0) != 0;
-}
-
-// One work unit of the symmetric kernel: band `grp` against chunk c of its tiles (see above).
-template <int LAW, int KR>
-__device__ void force_unit_sym(SysRef S, int grp, int c, float4 *sj, float4 *sv,
-                               float (*rw)[3][TJ])
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    auto *__restrict__ XS = glob<const float>(S.xs);
-    auto *__restrict__ YS = glob<const float>(S.ys);
-    auto *__restrict__ ZS = glob<const float>(S.zs);
-    auto *__restrict__ VXS = glob<const float>(S.vxs);
-    auto *__restrict__ VYS = glob<const float>(S.vys);
-    auto *__restrict__ VZS = glob<const float>(S.vzs);
-    auto *st = cst(S.st);
-    const int T = S.ntiles;
-    const int g0 = KR * grp;               // first tile row of the band
-    const int nv = min(KR, T - g0);        // rows of the band inside the system (the last is short)
-    Band<KR> B;
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    LawF Ka[KR], Kb[KR];
-    float far2a = 0.0f, far2b = 0.0f;
-#pragma unroll
-    for (int r = 0; r < KR; ++r) {
-        const int row = r < nv ? g0 + r : g0;  // a missing row mirrors row 0 and stays unused
-        const int slot = row * TJ + tid;
-        B.x[r] = XS[slot];
-        B.y[r] = YS[slot];
-        B.z[r] = ZS[slot];
-        B.ax[r] = B.ay[r] = B.az[r] = 0.0f;
-        B.v[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if constexpr (LAW != 0) B.v[r] = make_float4(VXS[slot], VYS[slot], VZS[slot], 0.0f);
-        if (r < nv && glob<const int32_t>(S.perm)[slot] >= 0) {
-            lo[0] = fminf(lo[0], B.x[r]);
-            lo[1] = fminf(lo[1], B.y[r]);
-            lo[2] = fminf(lo[2], B.z[r]);
-            hi[0] = fmaxf(hi[0], B.x[r]);
-            hi[1] = fmaxf(hi[1], B.y[r]);
-            hi[2] = fmaxf(hi[2], B.z[r]);
-        }
-        const int istar = row * TJ >= S.p1 ? 1 : 0;
-        Ka[r] = law_uniform(law_f(st, istar));
-        Kb[r] = law_uniform(law_f(st, istar + 1));
-        far2a = fmaxf(far2a, st->far2f[istar]);
-        far2b = fmaxf(far2b, st->far2f[istar + 1]);
-    }
-    // the box and the constants are the same in every lane; held in scalar registers they leave
-    // the vector registers to the pair loop
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        lo[d] = wave_uniform(wave_min(lo[d]));
-        hi[d] = wave_uniform(wave_max(hi[d]));
-    }
-    far2a = wave_uniform(far2a);
-    far2b = wave_uniform(far2b);
-
-    float sumx[KR], sumy[KR], sumz[KR], cx[KR], cy[KR], cz[KR];
-#pragma unroll
-    for (int r = 0; r < KR; ++r) sumx[r] = sumy[r] = sumz[r] = cx[r] = cy[r] = cz[r] = 0.0f;
-    const int t0 = g0 + c * S.ch;
-    const int t1 = min(T, t0 + S.ch);
-    auto *R = glob<float>(S.react);
-    const size_t roff = react_group_offset(grp, T, KR);
-    const size_t rlen = (size_t)(T - g0 - 1) * TJ;
-    float px = 0.f, py = 0.f, pz = 0.f, qx = 0.f, qy = 0.f, qz = 0.f;
-    if (t0 < t1) {
-        px = XS[t0 * TJ + tid];
-        py = YS[t0 * TJ + tid];
-        pz = ZS[t0 * TJ + tid];
-        if constexpr (LAW != 0) {
-            qx = VXS[t0 * TJ + tid];
-            qy = VYS[t0 * TJ + tid];
-            qz = VZS[t0 * TJ + tid];
-        }
-    }
-    for (int t = t0; t < t1; ++t) {
-        sj[tid] = make_float4(px, py, pz, 0.0f);
-        if constexpr (LAW != 0) sv[tid] = make_float4(qx, qy, qz, 0.0f);
-        __syncthreads();
-        if (t + 1 < t1) {
-            px = XS[(t + 1) * TJ + tid];
-            py = YS[(t + 1) * TJ + tid];
-            pz = ZS[(t + 1) * TJ + tid];
-            if constexpr (LAW != 0) {
-                qx = VXS[(t + 1) * TJ + tid];
-                qy = VYS[(t + 1) * TJ + tid];
-                qz = VZS[(t + 1) * TJ + tid];
-            }
-        }
-        const bool jstar = t * TJ >= S.p1;
-        LawF K[KR];
-#pragma unroll
-        for (int r = 0; r < KR; ++r) K[r] = jstar ? Kb[r] : Ka[r];
-        const float far2 = jstar ? far2b : far2a;
-        const int k = t - g0;  // tile t is row k of the band when k < KR
-        if (k >= KR) {
-            if (far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi, far2)) {
-                sym_tile<false, LAW, KR, false>(sj, sv, B, K, rw[wave][0], rw[wave][1],
-                                                rw[wave][2], lane, KR);
-            } else {
-                sym_tile<true, LAW, KR, false>(sj, sv, B, K, rw[wave][0], rw[wave][1],
-                                               rw[wave][2], lane, KR);
-            }
-        } else {
-            if (k > 0) {
-                // rows 0 .. k - 1 lie before tile t: full pairs with reactions
-                sym_tile<true, LAW, KR, true>(sj, sv, B, K, rw[wave][0], rw[wave][1], rw[wave][2],
-                                              lane, k);
-            }
-#pragma unroll
-            for (int r = 0; r < KR; ++r) {
-                if (r == k) {
-                    diag_tile<LAW>(sj, sv, B.x[r], B.y[r], B.z[r], B.v[r], K[r], B.ax[r], B.ay[r],
-                                   B.az[r]);
-                }
-            }
-        }
-        if (t > g0) {
-            // tile t lies after the band's first row, so at least one row left reactions
-            __syncthreads();
-            const size_t at = roff + (size_t)(t - g0 - 1) * TJ + tid;
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-                R[at + d * rlen] = ((rw[0][d][tid] + rw[1][d][tid]) + rw[2][d][tid]) + rw[3][d][tid];
-        }
-#pragma unroll
-        for (int r = 0; r < KR; ++r) {
-            kahan_add(sumx[r], cx[r], B.ax[r]);
-            kahan_add(sumy[r], cy[r], B.ay[r]);
-            kahan_add(sumz[r], cz[r], B.az[r]);
-            B.ax[r] = B.ay[r] = B.az[r] = 0.0f;
-        }
-        __syncthreads();  // sj, sv and rw are rewritten by the next tile
-    }
-    auto *P = glob<float>(S.part);
-    const size_t na = S.nalloc;
-#pragma unroll
-    for (int r = 0; r < KR; ++r) {
-        if (r >= nv) continue;
-        const int slot = (g0 + r) * TJ + tid;
-        if (glob<const int32_t>(S.perm)[slot] < 0) continue;
-        const size_t b = (size_t)c * 3 * na + slot;
-        P[b] = sumx[r] - cx[r];
-        P[b + na] = sumy[r] - cy[r];
-        P[b + 2 * na] = sumz[r] - cz[r];
-    }
-}
-
-template <int LAW, int KR>
-__device__ __forceinline__ void force_sym_units(const Launch &L, float4 *sj, float4 *sv,
-                                                float (*rw)[3][TJ])
-{
-    for (int u = L.unit_base + blockIdx.x; u < L.total_units; u += gridDim.x) {
-        SysRef S = cst(L.sys)[find_sys(L, u, false)];
-        const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
-        force_unit_sym<LAW, KR>(S, gc[0], gc[1], sj, sv, rw);
-    }
-}
-
-// Contact law; the launch covers the units [unit_base, total_units) of systems with KR rows per
-// band (the runtime orders a segment table by band height, so each height is one range).
-template <int KR>
-__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(SYM_WAVES[KR / 2])))
-void k_force_sym(Launch L)
-{
-    __shared__ float4 sj[TJ];
-    __shared__ __attribute__((aligned(16))) float rw[4][3][TJ];
-    force_sym_units<0, KR>(L, sj, nullptr, rw);
-}
-
-// The same under eqs. (4)-(6): each tile also stages the sorted half-step velocities.
-template <int KR>
-__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(SYM_PAPER_WAVES[KR / 2])))
-void k_force_sym_paper(Launch L)
-{
-    __shared__ float4 sj[TJ];
-    __shared__ float4 sv[TJ];
-    __shared__ __attribute__((aligned(16))) float rw[4][3][TJ];
-    force_sym_units<1, KR>(L, sj, sv, rw);
 }
 
 // a = G m (sum of the element's own chunk partials, then the reactions of every band with a
@@ -979,18 +686,18 @@ __device__ __forceinline__ LawD law_d(St st, int cls)
 // itself). Coincident elements (d = 0, r^2 = 1e-200 after the floor added in pair_s64_at) get a
 // large but finite s under both laws (w = 1e100, s at most about 1e300 with eps = 0), so their
 // term s d is exactly 0, the oracle's r = 0 rule.
-template <int LAW>
+template <int LAW, bool NEAR = true>
 __device__ __forceinline__ double pair_s64(double r2, double w, double dx, double dy, double dz,
                                            double dvx, double dvy, double dvz, const LawD &K)
 {
     if constexpr (LAW == 0) {
         const double w3 = w * w * w;
-        return fmin(w3, K.c1 - K.c2 * w);
+        return NEAR ? fmin(w3, K.c1 - K.c2 * w) : w3;
     } else {
         const double r = r2 * w;
         const double t = r + K.eps;
         double s = w * rcp_f64(t * t);
-        if (r < K.D) {
+        if (NEAR && r < K.D) {
             const double dot = dvx * dx + dvy * dy + dvz * dz;
             const double g = dot < 0.0 ? K.gc : K.gcb;
             const double u = K.D - r;
@@ -1000,149 +707,7 @@ __device__ __forceinline__ double pair_s64(double r2, double w, double dx, doubl
     }
 }
 
-// ------------------------------------------------------------------ FP64 symmetric force kernel
-//
-// The FP64 reference mode with the work split of k_force_sym (one tile row per block): each
-// unordered pair once, i in registers, the j sums rotating across the wave (a double moves as its
-// two 32-bit halves, one DPP move each), the diagonal tile one-sided, reactions stored per (tile
-// row, later tile) and added by k_combine_sym64 after the element's own chunk partials, rows in
-// order. Every sum is plain FP64 in a fixed order. There is no far-tile path: the tile boxes are
-// FP32, and every pair takes the full law.
-
-__device__ __forceinline__ double wave_ror1_d(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), DPP_WAVE_ROR1, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), DPP_WAVE_ROR1, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
-struct I64 {
-    double x, y, z, vx, vy, vz;
-};
-
-template <int LAW>
-__device__ __forceinline__ double pair_s64_at(const double (*sj)[TJ], const double (*sv)[TJ], int j,
-                                              const I64 &I, const LawD &K, double &dx, double &dy,
-                                              double &dz)
-{
-    dx = sj[0][j] - I.x;
-    dy = sj[1][j] - I.y;
-    dz = sj[2][j] - I.z;
-    // the 1e-200 floor changes no r^2 above about 1e-184 and keeps the pair code free of a
-    // branch for d = 0 (measured 4 % faster for the contact law, 7 % under eqs. 4-6)
-    const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, 1.0e-200)));
-    const double w = rsqrt_f64(r2);
-    if constexpr (LAW == 0) {
-        return pair_s64<0>(r2, w, dx, dy, dz, 0.0, 0.0, 0.0, K);
-    } else {
-        return pair_s64<LAW>(r2, w, dx, dy, dz, sv[0][j] - I.vx, sv[1][j] - I.vy, sv[2][j] - I.vz,
-                             K);
-    }
-}
-
-template <int LAW>
-__device__ void force_unit_sym64(SysRef S, int I, int c, double (*sj)[TJ],
-                                 double (*sv)[TJ], double (*rw)[3][TJ])
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    auto *__restrict__ XS = glob<const double>(S.xs);
-    auto *__restrict__ YS = glob<const double>(S.ys);
-    auto *__restrict__ ZS = glob<const double>(S.zs);
-    auto *__restrict__ VXS = glob<const double>(S.vxs);
-    auto *__restrict__ VYS = glob<const double>(S.vys);
-    auto *__restrict__ VZS = glob<const double>(S.vzs);
-    auto *st = cst(S.st);
-    const int T = S.ntiles;
-    const int slot = I * TJ + tid;
-    I64 Ist{XS[slot], YS[slot], ZS[slot], 0.0, 0.0, 0.0};
-    if constexpr (LAW != 0) {
-        Ist.vx = VXS[slot];
-        Ist.vy = VYS[slot];
-        Ist.vz = VZS[slot];
-    }
-    const int istar = I * TJ >= S.p1 ? 1 : 0;
-    double ax = 0.0, ay = 0.0, az = 0.0;
-    const int t0 = I + c * S.ch;
-    const int t1 = min(T, t0 + S.ch);
-    auto *R = glob<double>(S.react);
-    const size_t roff = react_group_offset(I, T, 1);
-    const size_t rlen = (size_t)(T - I - 1) * TJ;
-    for (int t = t0; t < t1; ++t) {
-        sj[0][tid] = XS[t * TJ + tid];
-        sj[1][tid] = YS[t * TJ + tid];
-        sj[2][tid] = ZS[t * TJ + tid];
-        if constexpr (LAW != 0) {
-            sv[0][tid] = VXS[t * TJ + tid];
-            sv[1][tid] = VYS[t * TJ + tid];
-            sv[2][tid] = VZS[t * TJ + tid];
-        }
-        __syncthreads();
-        const int cls = pair_class(istar, t * TJ >= S.p1 ? 1 : 0);
-        const LawD K = law_d(st, cls);
-        if (t == I) {
-            // the self pair (d = 0) adds s d = 0 under both laws
-            for (int jj = 0; jj < TJ; ++jj) {
-                double dx, dy, dz;
-                const double s = pair_s64_at<LAW>(sj, sv, jj, Ist, K, dx, dy, dz);
-                ax = fma(s, dx, ax);
-                ay = fma(s, dy, ay);
-                az = fma(s, dz, az);
-            }
-        } else {
-            double ajx[4] = {0.0, 0.0, 0.0, 0.0}, ajy[4] = {0.0, 0.0, 0.0, 0.0};
-            double ajz[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int step = 0; step < 64; ++step) {
-                const int e = (lane - step) & 63;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    double dx, dy, dz;
-                    const double s = pair_s64_at<LAW>(sj, sv, g * 64 + e, Ist, K, dx, dy, dz);
-                    const double px = s * dx, py = s * dy, pz = s * dz;
-                    ax += px;
-                    ay += py;
-                    az += pz;
-                    ajx[g] = wave_ror1_d(ajx[g]) - px;
-                    ajy[g] = wave_ror1_d(ajy[g]) - py;
-                    ajz[g] = wave_ror1_d(ajz[g]) - pz;
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                // one more rotation brings element l's sum back to lane l
-                rw[wave][0][g * 64 + lane] = wave_ror1_d(ajx[g]);
-                rw[wave][1][g * 64 + lane] = wave_ror1_d(ajy[g]);
-                rw[wave][2][g * 64 + lane] = wave_ror1_d(ajz[g]);
-            }
-            __syncthreads();
-            const size_t at = roff + (size_t)(t - I - 1) * TJ + tid;
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-                R[at + d * rlen] = ((rw[0][d][tid] + rw[1][d][tid]) + rw[2][d][tid]) + rw[3][d][tid];
-        }
-        __syncthreads();  // sj, sv and rw are rewritten by the next tile
-    }
-    if (glob<const int32_t>(S.perm)[slot] >= 0) {
-        auto *P = glob<double>(S.part);
-        const size_t na = S.nalloc;
-        const size_t b = (size_t)c * 3 * na + slot;
-        P[b] = ax;
-        P[b + na] = ay;
-        P[b + 2 * na] = az;
-    }
-}
-
-template <int LAW>
-__global__ __launch_bounds__(BT) void k_force_sym64(Launch L)
-{
-    __shared__ double sj[3][TJ];
-    __shared__ double sv[LAW == 0 ? 1 : 3][TJ];
-    __shared__ double rw[4][3][TJ];
-    for (int u = L.unit_base + blockIdx.x; u < L.total_units; u += gridDim.x) {
-        SysRef S = cst(L.sys)[find_sys(L, u, false)];
-        const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
-        force_unit_sym64<LAW>(S, gc[0], gc[1], sj, sv, rw);
-    }
-}
+// ------------------------------------------------------------------ FP64 combine
 
 // a = G m (sum of the element's own chunk partials, then the reactions of every earlier tile row
 // in row order), plain FP64, scattered to the element's own index.
@@ -1532,6 +1097,334 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
 #pragma unroll
         for (int k = 0; k < 7; ++k) r[k] = v[k];
         if (local == 0) begin_counts(S);
+    }
+}
+
+// ------------------------------------------------------------------ symmetric force kernel: code
+
+template <typename T>
+struct RowsMem;  // one wave's staged j, each stored twice so that a rotating read never wraps
+template <>
+struct RowsMem<float> {
+    float4 p[128];
+    __device__ __forceinline__ void put(int lane, float x, float y, float z)
+    {
+        p[lane] = p[lane + 64] = make_float4(x, y, z, 0.0f);
+    }
+    __device__ __forceinline__ float4 get(int k) const { return p[k]; }
+};
+template <>
+struct RowsMem<double> {
+    double2 p[128];
+    double q[128];
+    __device__ __forceinline__ void put(int lane, double x, double y, double z)
+    {
+        p[lane] = p[lane + 64] = make_double2(x, y);
+        q[lane] = q[lane + 64] = z;
+    }
+    __device__ __forceinline__ double4 get(int k) const
+    {
+        const double2 a = p[k];
+        return make_double4(a.x, a.y, q[k], 0.0);
+    }
+};
+
+__device__ __forceinline__ double xbar_ror1(double v, int addr)
+{
+    const int lo = __builtin_amdgcn_ds_bpermute(addr, __double2loint(v));
+    const int hi = __builtin_amdgcn_ds_bpermute(addr, __double2hiint(v));
+    return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ LawF law_of(Const<DevState> *st, int cls, float)
+{
+    return law_uniform(law_f(st, cls));
+}
+__device__ __forceinline__ LawD law_of(Const<DevState> *st, int cls, double)
+{
+    return law_d(st, cls);
+}
+
+template <int LAW, bool NEAR>
+__device__ __forceinline__ float pair_at(float dx, float dy, float dz, const float4 &vj,
+                                         const float4 &vi, const LawF &K)
+{
+    const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, 1.0e-24f)));
+    return pair_s<LAW, NEAR>(r2, dx, dy, dz, vj, vi, K);
+}
+template <int LAW, bool NEAR>
+__device__ __forceinline__ double pair_at(double dx, double dy, double dz, const double4 &vj,
+                                          const double4 &vi, const LawD &K)
+{
+    const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, 1.0e-200)));
+    return pair_s64<LAW, NEAR>(r2, rsqrt_f64(r2), dx, dy, dz, vj.x - vi.x, vj.y - vi.y,
+                               vj.z - vi.z, K);
+}
+
+// The band's elements of one lane.
+template <typename T, int NI>
+struct Rows {
+    T x[NI], y[NI], z[NI], a[NI][3];
+};
+
+// The wave's 64 j against the elements [K0, K0 + NK) of every lane, with (REACT) their reaction added
+// to aj, or one-sided (a row's own tile, where the self pair is at step 0 of element K0 + wave).
+// vi: the elements' half-step velocities (eqs. 4-6, near form only).
+template <typename T, int LAW, int NI, int K0, int NK, bool NEAR, bool REACT, typename Law, typename V4>
+__device__ __forceinline__ void rows_tile(const RowsMem<T> &P, const RowsMem<T> &V, Rows<T, NI> &B,
+                                          const Law *K, const V4 *vi, int lane, int wave,
+                                          T (&aj)[3])
+{
+    constexpr int U = sizeof(T) == 4 ? 4 : 2;
+    const int rot_addr = ((lane + 63) & 63) << 2;  // byte address of lane l - 1 (mod 64)
+    V4 p = P.get(lane + 64);
+#pragma unroll 1
+    for (int s0 = 0; s0 < 64; s0 += U) {
+        const int at = lane + 64 - s0 - U;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const V4 pn = P.get(at + U - u - 1);
+            V4 vj{};
+            if constexpr (LAW != 0 && NEAR) vj = V.get(at + U - u);
+#pragma unroll
+            for (int k = K0; k < K0 + NK; ++k) {
+                const T dx = p.x - B.x[k], dy = p.y - B.y[k], dz = p.z - B.z[k];
+                V4 v{};
+                if constexpr (LAW != 0 && NEAR) v = vi[k - K0];
+                T s = pair_at<LAW, NEAR>(dx, dy, dz, vj, v, K[k / 4]);
+                if constexpr (LAW != 0 && !REACT) s = u == 0 && s0 == 0 && k - K0 == wave ? (T)0 : s;
+                B.a[k][0] = fma_t(s, dx, B.a[k][0]);
+                B.a[k][1] = fma_t(s, dy, B.a[k][1]);
+                B.a[k][2] = fma_t(s, dz, B.a[k][2]);
+                if constexpr (REACT) {
+                    aj[0] = fma_t(s, dx, aj[0]);
+                    aj[1] = fma_t(s, dy, aj[1]);
+                    aj[2] = fma_t(s, dz, aj[2]);
+                }
+                if constexpr (LAW == 0 && sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (sizeof(T) == 4) asm volatile("" ::"v"(p.w));
+            if constexpr (REACT) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) aj[d] = xbar_ror1(aj[d], rot_addr);
+            }
+            p = pn;
+        }
+    }
+}
+
+// The near form of the band's rows r0, r0 + 1, .. against tile k of the band's tiles (k >= R: a tile
+// after the band): the rows before tile k with reactions, row k one-sided.
+template <typename T, int LAW, int R, int r0, typename Law>
+__device__ __forceinline__ void near_rows(SysRef S, const RowsMem<T> &P,
+                                          const RowsMem<T> &V, Rows<T, 4 * R> &B, const Law *K,
+                                          int I0, int k, int lane, int wave, T (&aj)[3])
+{
+    using V4 = typename Vec4<T>::type;
+    if (r0 <= k) {
+        V4 vi[4];
+        if constexpr (LAW != 0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int slot = (I0 + r0) * TJ + 64 * q + lane;
+                vi[q].x = glob<const T>(S.vxs)[slot];
+                vi[q].y = glob<const T>(S.vys)[slot];
+                vi[q].z = glob<const T>(S.vzs)[slot];
+                vi[q].w = 0;
+            }
+        }
+        if (r0 == k) {
+            T none[3] = {0, 0, 0};
+            rows_tile<T, LAW, 4 * R, 4 * r0, 4, true, false, Law, V4>(P, V, B, K, vi, lane, wave,
+                                                                      none);
+        } else {
+            rows_tile<T, LAW, 4 * R, 4 * r0, 4, true, true, Law, V4>(P, V, B, K, vi, lane, wave, aj);
+        }
+    }
+    if constexpr (r0 + 1 < R) near_rows<T, LAW, R, r0 + 1>(S, P, V, B, K, I0, k, lane, wave, aj);
+}
+
+// R rows of a unit: rows I0 .. I0 + R - 1 of band grp (BAND rows high) against chunk c of the band's
+// tiles. Where the band's rows before I0 have left reactions, these rows' are added to them.
+template <typename T, int LAW, int R, int BAND>
+__device__ __forceinline__ void rows_unit(SysRef S, int grp, int I0, int c, RowsMem<T> *mem,
+                                          T (*red)[3][TJ])
+{
+    constexpr int NI = 4 * R;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto *st = cst(S.st);
+    auto *XS = glob<const T>(S.xs), *YS = glob<const T>(S.ys), *ZS = glob<const T>(S.zs);
+    auto *VXS = glob<const T>(S.vxs), *VYS = glob<const T>(S.vys), *VZS = glob<const T>(S.vzs);
+    const int ntiles = S.ntiles;
+    const int G0 = BAND * grp;           // the band's first row
+    const int nv = min(R, ntiles - I0);  // rows inside the system (the last band may be short)
+    using V4 = typename Vec4<T>::type;
+    Rows<T, NI> B;
+    using Law = decltype(law_of(st, 0, (T)0));
+    Law Ka[R], Kb[R];
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    float far2a = 0.0f, far2b = 0.0f;
+    T sum[NI][3], comp[sizeof(T) == 4 ? NI : 1][3];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int row = r < nv ? I0 + r : I0;  // a missing row mirrors row 0 and stays unused
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 4 * r + q, slot = row * TJ + 64 * q + lane;
+            B.x[k] = XS[slot];
+            B.y[k] = YS[slot];
+            B.z[k] = ZS[slot];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                B.a[k][d] = sum[k][d] = 0;
+                if constexpr (sizeof(T) == 4) comp[k][d] = 0;
+            }
+        }
+        auto *bx = cst(S.tbox) + (size_t)row * 8;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = fminf(lo[d], bx[d]);
+            hi[d] = fmaxf(hi[d], bx[4 + d]);
+        }
+        const int istar = row * TJ >= S.p1 ? 1 : 0;
+        Ka[r] = law_of(st, istar, (T)0);
+        Kb[r] = law_of(st, istar + 1, (T)0);
+        far2a = fmaxf(far2a, st->far2f[istar]);
+        far2b = fmaxf(far2b, st->far2f[istar + 1]);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        lo[d] = wave_uniform(lo[d]);
+        hi[d] = wave_uniform(hi[d]);
+    }
+    far2a = wave_uniform(far2a);
+    far2b = wave_uniform(far2b);
+    RowsMem<T> &P = mem[wave], &V = mem[LAW != 0 ? 4 + wave : wave];
+    auto *RE = glob<T>(S.react);
+    const size_t roff = react_group_offset(grp, ntiles, BAND);
+    const size_t rlen = (size_t)(ntiles - G0 - 1) * TJ;
+    const int t1 = min(ntiles, G0 + (c + 1) * S.ch);
+    const int t0 = max(I0, G0 + c * S.ch);  // the rows' own pairs begin at their own tile
+    T px = 0, py = 0, pz = 0, qx = 0, qy = 0, qz = 0;
+    auto fetch = [&](int t) {
+        const int slot = t * TJ + 64 * wave + lane;
+        px = XS[slot];
+        py = YS[slot];
+        pz = ZS[slot];
+        if constexpr (LAW != 0) {
+            qx = VXS[slot];
+            qy = VYS[slot];
+            qz = VZS[slot];
+        }
+    };
+    if (t0 < t1) fetch(t0);
+#pragma unroll 1
+    for (int t = t0; t < t1; ++t) {
+        P.put(lane, px, py, pz);
+        if constexpr (LAW != 0) V.put(lane, qx, qy, qz);
+        // one wave writes and reads its own part of LDS, in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (t + 1 < t1) fetch(t + 1);
+        const bool jstar = t * TJ >= S.p1;
+        Law K[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) K[r] = jstar ? Kb[r] : Ka[r];
+        const int k = t - I0;  // tile t is one of these rows when k < R
+        const size_t at = roff + (size_t)(t - G0 - 1) * TJ + 64 * wave + lane;
+        T aj[3] = {0, 0, 0}, old[3] = {0, 0, 0};
+        if (BAND > R && k > 0 && I0 > G0) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) old[d] = RE[at + d * rlen];
+        }
+        if (k >= R && far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi,
+                               jstar ? far2b : far2a)) {
+            rows_tile<T, LAW, NI, 0, NI, false, true, Law, V4>(P, V, B, K, nullptr, lane, wave, aj);
+        } else if (LAW == 0 && k >= R) {
+            rows_tile<T, LAW, NI, 0, NI, true, true, Law, V4>(P, V, B, K, nullptr, lane, wave, aj);
+        } else {
+            // one row at a time, so that only a row's velocities are held
+            near_rows<T, LAW, R, 0>(S, P, V, B, K, I0, k, lane, wave, aj);
+        }
+        if (k > 0) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) RE[at + d * rlen] = old[d] - aj[d];
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                if constexpr (sizeof(T) == 4) {
+                    kahan_add(sum[i][d], comp[i][d], B.a[i][d]);
+                } else {
+                    sum[i][d] += B.a[i][d];
+                }
+                B.a[i][d] = 0;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    // the waves' sums of each element, in wave order
+    auto *PA = glob<T>(S.part);
+    const size_t na = S.nalloc;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        __syncthreads();  // red is the staging memory of the loop
+        if (r < nv) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    T v = sum[4 * r + q][d];
+                    if constexpr (sizeof(T) == 4) v -= comp[4 * r + q][d];
+                    red[wave][d][64 * q + lane] = v;
+                }
+            }
+        }
+        __syncthreads();
+        const int slot = (I0 + r) * TJ + tid;
+        if (r < nv && glob<const int32_t>(S.perm)[slot] >= 0) {
+            const size_t b = (size_t)c * 3 * na + slot;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                T v = red[0][d][tid];
+                if constexpr (sizeof(T) == 4) {
+                    T e = 0;
+#pragma unroll
+                    for (int w = 1; w < 4; ++w) kahan_add(v, e, red[w][d][tid]);
+                    v -= e;
+                } else {
+                    v = ((v + red[1][d][tid]) + red[2][d][tid]) + red[3][d][tid];
+                }
+                PA[b + d * na] = v;
+            }
+        }
+    }
+    __syncthreads();  // the next unit's staging
+}
+
+template <typename T, int LAW, int R, int BAND = R>
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(rows_waves(sizeof(T) == 8, LAW, R))))
+void k_force_rows(Launch L)
+{
+    union Shared {
+        RowsMem<T> mem[LAW == 0 ? 4 : 8];
+        T red[4][3][TJ];
+    };
+    __shared__ __attribute__((aligned(16))) char raw[sizeof(Shared)];
+    Shared &sh = *reinterpret_cast<Shared *>(raw);
+    for (int u = L.unit_base + blockIdx.x; u < L.total_units; u += gridDim.x) {
+        SysRef S = cst(L.sys)[find_sys(L, u, false)];
+        const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
+        const int grp = gc[0], c = gc[1];
+        if constexpr (BAND == R) {
+            rows_unit<T, LAW, R, BAND>(S, grp, R * grp, c, sh.mem, sh.red);
+        } else {
+#pragma unroll 1
+            for (int I0 = BAND * grp; I0 < min(S.ntiles, BAND * (grp + 1)); I0 += R)
+                rows_unit<T, LAW, R, BAND>(S, grp, I0, c, sh.mem, sh.red);
+        }
     }
 }
 
@@ -2100,19 +1993,19 @@ hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks,
         } else if (mode == 2) {
             if (b != 1) return hipErrorInvalidValue;
             if (L.law == 0) {
-                hipLaunchKernelGGL(k_force_sym64<0>, g, blk, 0, s, R);
+                hipLaunchKernelGGL((k_force_rows<double, 0, 1>), g, blk, 0, s, R);
             } else {
-                hipLaunchKernelGGL(k_force_sym64<1>, g, blk, 0, s, R);
+                hipLaunchKernelGGL((k_force_rows<double, 1, 1>), g, blk, 0, s, R);
             }
         } else {
             // FP32 Kahan: one launch per band height present in the table
             switch (b * 2 + L.law) {
-            case 2: hipLaunchKernelGGL(k_force_sym<1>, g, blk, 0, s, R); break;
-            case 3: hipLaunchKernelGGL(k_force_sym_paper<1>, g, blk, 0, s, R); break;
-            case 4: hipLaunchKernelGGL(k_force_sym<2>, g, blk, 0, s, R); break;
-            case 5: hipLaunchKernelGGL(k_force_sym_paper<2>, g, blk, 0, s, R); break;
-            case 6: hipLaunchKernelGGL(k_force_sym<4>, g, blk, 0, s, R); break;
-            default: hipLaunchKernelGGL(k_force_sym_paper<4>, g, blk, 0, s, R); break;
+            case 2: hipLaunchKernelGGL((k_force_rows<float, 0, 1>), g, blk, 0, s, R); break;
+            case 3: hipLaunchKernelGGL((k_force_rows<float, 1, 1>), g, blk, 0, s, R); break;
+            case 4: hipLaunchKernelGGL((k_force_rows<float, 0, 2>), g, blk, 0, s, R); break;
+            case 5: hipLaunchKernelGGL((k_force_rows<float, 1, 2>), g, blk, 0, s, R); break;
+            case 6: hipLaunchKernelGGL((k_force_rows<float, 0, 2, 4>), g, blk, 0, s, R); break;
+            default: hipLaunchKernelGGL((k_force_rows<float, 1, 2, 4>), g, blk, 0, s, R); break;
             }
         }
         const hipError_t e = hipGetLastError();

@@ -183,3 +183,27 @@ def test_split_coarsened_by_the_workspace_budget(mode, tol):
     p64, _ = ic.f32_as_f64()
     ref = oracle.accel(p64, ic.n1, ic.G, ic.m, ic.D1, ic.D2)
     assert force_error(a, ref) <= tol
+
+
+@pytest.mark.parametrize("mode,law,tol", [("kahan", "contact", 1e-5), ("kahan", "paper", 1e-5),
+                                          ("fp64", "contact", 1e-12), ("fp64", "paper", 1e-11)])
+@pytest.mark.parametrize("n,q,ch", [(1500, 0.5, 2), (2900, 0.03, 3), (5000, 0.9, 5), (6400, 1.0, 7)])
+def test_chunks_that_cut_a_band(n, q, ch, mode, law, tol):
+    """Chunks whose first tile lies inside a band (fewer tiles than rows, or not a multiple), short
+    last bands and a star of a few elements, for every band height: a band of four is taken two
+    rows after the other, the second pair of rows beginning at its own tile."""
+    nb = require_gpu()
+    M, W = nb.MODES[mode], nb.LAWS[law]
+    ic, kw = _law(synth.make_binary(n, q, seed=n), law)
+    tiles = -(-ic.n1 // 256) - (-(n - ic.n1) // 256)
+    ref = _oracle_forces(ic, kw)
+    for rows in (1, 2, 4) if mode == "kahan" else (1,):
+        print_case("chunks that cut a band", n, q, ch, mode, law, rows)
+        nb.nb_tile_override(n, n, M, -(-tiles // ch), rows, law=W)
+        try:
+            s = nb.System.from_ic(ic, mode=mode, **kw)
+            a = s.accelerations()
+            s.close()
+        finally:
+            nb.nb_tile_override(n, n, M, 0, 1, law=W)
+        assert force_error(a, ref) <= tol
