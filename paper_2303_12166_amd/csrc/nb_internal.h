@@ -8,12 +8,13 @@
 namespace nbk {
 
 // Waves per SIMD asked of the compiler (its vector-register cap) for the force kernels: the most
-// at which the pair loops do not spill (under eqs. (4)-(6) at two rows 16 values spill outside
-// them; three waves without measured 1.5 % slower at 40,009 elements).
+// at which the pair loops do not spill (eqs. (4)-(6) at two rows and four waves: 13.9 ms at
+// 262,144 elements against 12.8 at three; the contact law at two rows 10.1-10.2 ms at four waves,
+// 10.25-10.34 at three).
 constexpr int PLAIN_WAVES = 8;
 constexpr int rows_waves(bool fp64, int law, int r)
 {
-    return fp64 ? (law == 0 ? 3 : 2) : (r == 1 && law == 0 ? 5 : 4);
+    return fp64 ? (law == 0 ? 3 : 2) : (law == 0 ? (r == 1 ? 5 : 4) : (r == 1 ? 4 : 3));
 }
 
 constexpr int BT = 256;          // threads per block, every kernel

@@ -479,7 +479,11 @@ __device__ __forceinline__ LawF law_f(St st, int cls)
 //                 pair has r >= D. (pi / 12) (D - r)^2 (r + 2D) is the overlap volume of eq. (5)
 //                 in factored form, so it has no cancellation near D. The square root form takes
 //                 one multiply fewer per far pair than r = r2 rsqrt(r2) (measured 2.5 % faster).
-//                 A padding slot (r near 1.7e18) gives t^2 r = inf, s = 0 and w = 0.
+//                 A padding slot (r near 1.7e18) gives t^2 r = inf, s = 0 and w = 0. The near form
+//                 works the overlap out only where a lane of the wave is in contact: it is half
+//                 of the instructions, and in most steps of a near tile no pair touches (measured
+//                 at 9,000 elements 53 -> 45 us, 16,384 111 -> 94, 262,144 12.99 -> 12.76 ms, and
+//                 one-sided at 7,001 49 -> 36).
 // On a far tile the near form gives the same bits (the contact law's minimum picks w^3 by a margin
 // far above rounding once r^2 >= (1 + FAR_MARGIN) D^2; the overlap term is exactly 0 for r >= D),
 // so the near/far choice changes speed only.
@@ -498,11 +502,13 @@ __device__ __forceinline__ float pair_s(float r2, float dx, float dy, float dz, 
         const float t2 = t * t;
         float s = rcp_p(t2 * r);
         if constexpr (NEAR) {
-            const float w = t2 * s;
-            const float dot = fmaf(vj.x - vi.x, dx, fmaf(vj.y - vi.y, dy, (vj.z - vi.z) * dz));
-            const float g = dot < 0.0f ? K.gc : K.gcb;
-            const float u = fmaxf(K.D - r, 0.0f);
-            s = s - ((g * u) * u) * fmaf(K.twoD, w, 1.0f);
+            if (__any(r < K.D)) {
+                const float w = t2 * s;
+                const float dot = fmaf(vj.x - vi.x, dx, fmaf(vj.y - vi.y, dy, (vj.z - vi.z) * dz));
+                const float g = dot < 0.0f ? K.gc : K.gcb;
+                const float u = fmaxf(K.D - r, 0.0f);
+                s = s - ((g * u) * u) * fmaf(K.twoD, w, 1.0f);
+            }
         }
         return s;
     }
@@ -1175,7 +1181,8 @@ __device__ __forceinline__ void rows_tile(const RowsMem<T> &P, const RowsMem<T> 
                                           const Law *K, const V4 *vi, int lane, int wave,
                                           T (&aj)[3])
 {
-    constexpr int U = sizeof(T) == 4 ? 4 : 2;
+    // (unrolled, the near form of eqs. (4)-(6) with its branches spills inside the loop)
+    constexpr int U = LAW != 0 && NEAR ? 1 : (sizeof(T) == 4 ? 4 : 2);
     const int rot_addr = ((lane + 63) & 63) << 2;  // byte address of lane l - 1 (mod 64)
     V4 p = P.get(lane + 64);
 #pragma unroll 1
