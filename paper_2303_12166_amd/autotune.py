@@ -120,6 +120,15 @@ def _workspace(ic, mode: str, law_kw: dict) -> int:
     return nb_scratch_bytes(p)
 
 
+def _finest(n: int, n1: int, mode: int, law: int, nsplit: int) -> bool:
+    """Whether this request gives chunks of one tile at one row per band."""
+    nb_tile_override(n, n, mode, nsplit, 1, law=law)
+    try:
+        return nb_tile_config(n, n1, mode, law)["jchunk"] == 256
+    finally:
+        nb_tile_override(n, n, mode, 0, 1, law=law)
+
+
 def tune_key(key: str, q: float = 0.5, repeats: int = 4, max_n: int = 262144,
              budget: int = 0, log=print) -> dict:
     import synth
@@ -174,6 +183,13 @@ def tune_key(key: str, q: float = 0.5, repeats: int = 4, max_n: int = 262144,
             best = close[0]
         rows, ns = (int(v) for v in best.split(":"))
         ms = refined.get(best, timings[best])
+        # one tile per chunk, the finest split (one-sided in small systems): keep it so at the
+        # bucket's larger sizes, whose finest splits have more chunks
+        tiles = hi // 256 + 2
+        if rows == 1 and _finest(n, ic.n1, M, W, ns) and ns < tiles <= CHUNKS[-1]:
+            ns = next(c for c in CHUNKS if c >= tiles)
+            best = "%d:%d" % (rows, ns)
+            timings.setdefault(best, ms)
         log("%s bucket [%d, %d] tuned at n=%d: rows %d nsplit %d (%.3f ms); %s%s" % (
             key, lo, hi, n, rows, ns, ms,
             " ".join("%s=%.3f" % (k, v) for k, v in sorted(timings.items())),

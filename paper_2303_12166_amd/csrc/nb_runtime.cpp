@@ -70,10 +70,10 @@ Layout layout_for(int mode, int law, const TileCfg &c);
 size_t layout_total(int mode, int law, const TileCfg &c);
 
 // Largest systems of the one-sided force kernel, by FP64 mode and element law: where a step of it
-// and of the symmetric kernel at its finest split cost the same (FP32 contact law 44.2 and 44.4 us
+// and of the symmetric kernel at its finest split cost about the same (FP32 contact law 44.2 and 44.4 us
 // at 9,000 elements, 56.9 and 51.5 at 11,000; eqs. (4)-(6) 43.1 and 49.5 at 7,000, 62.7 and 52.5 at
 // 9,000; FP64 59 and 71 at 7,000, 86.5 and 81 at 9,000, eqs. (4)-(6) 81 and 89, 121 and 110).
-constexpr int64_t ONE_SIDED_MAX[2][2] = {{8960, 7680}, {8192, 7680}};
+constexpr int64_t ONE_SIDED_MAX[2][2] = {{8960, 8192}, {8192, 8192}};
 
 // The work split fields of c for ns requested chunks and bands of `rows` tile rows.
 void finish_split(TileCfg &c, int64_t n, int64_t n1, int mode, int law, int ns, int rows)
