@@ -11,12 +11,13 @@ namespace nbk {
 // at which the pair loops do not spill (eqs. (4)-(6) at two rows and four waves: 13.9 ms at
 // 262,144 elements against 12.8 at three; the contact law at two rows 10.1-10.2 ms at four waves,
 // 10.25-10.34 at three).
-constexpr int PLAIN_WAVES = 8;
+constexpr int PLAIN_WAVES = 4;
 constexpr int rows_waves(bool fp64, int law, int r)
 {
     return fp64 ? (law == 0 ? 3 : 2) : (law == 0 ? (r == 1 ? 5 : 4) : (r == 1 ? 4 : 3));
 }
 
+constexpr int CU_COUNT = 256;    // compute units of the card
 constexpr int BT = 256;          // threads per block, every kernel
 constexpr int TJ = 256;          // j elements staged in LDS per tile (one per thread)
 constexpr int MAX_BAND = 4;      // tallest band of the FP32 symmetric kernel (tile rows per lane)

@@ -124,7 +124,7 @@ constexpr double PI_D = 3.14159265358979323846;
 // and 83 without; 99 is what the parts allow: 14 at 115 and one at 32). The chip answers with a
 // lower clock (2.09 against 2.22 GHz in k_force_sym<4>), so at N = 262,144 the evaluation gains 3.6 %
 // (10.95 -> 10.55 ms; eqs. (4)-(6) 14.67 -> 14.34), at 40,009 under eqs. (4)-(6) 5 %, and
-// k_force_f32 at N = 131,072, at two waves per SIMD, 13 % (8.12 -> 7.07 ms). s_setprio after the
+// k_force_f32 at N = 131,072, at two waves per SIMD, 13 % (8.12 -> 7.07 ms before its staging). s_setprio after the
 // transcendental is also the wait state that its first use needs.
 __device__ __forceinline__ float rsq_p(float x)
 {
@@ -262,40 +262,103 @@ __global__ __launch_bounds__(BT) void k_gather(Launch L)
     }
 }
 
-// ------------------------------------------------------------------ FP32 one-sided force kernel
-
-// Near tiles: the contact law s = min(w^3, c1 - c2 w) for every pair; far tiles (every pair at
-// r >= D, proven from bounding boxes): s = w^3, the value the contact law's minimum selects there.
-template <bool FAR>
-__device__ __forceinline__ void interact4_f32(const float4 &X, const float4 &Y, const float4 &Z,
-                                              float xi, float yi, float zi, float &ax, float &ay,
-                                              float &az, float c1, float nc2)
+// A value that is the same in every lane, moved to a scalar register.
+__device__ __forceinline__ float wave_uniform(float v)
 {
-    const float eps = 1.0e-24f;
-    const float xs[4] = {X.x, X.y, X.z, X.w};
-    const float ys[4] = {Y.x, Y.y, Y.z, Y.w};
-    const float zs[4] = {Z.x, Z.y, Z.z, Z.w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const float dx = xs[q] - xi;
-        const float dy = ys[q] - yi;
-        const float dz = zs[q] - zi;
-        const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps)));
-        const float w = rsq_p(r2);
-        const float w3 = (w * w) * w;
-        const float s = FAR ? w3 : fminf(w3, fmaf(nc2, w, c1));
-        ax = fmaf(s, dx, ax);
-        ay = fmaf(s, dy, ay);
-        az = fmaf(s, dz, az);
-    }
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
+
+// Whether a tile lies at least D from every i of the wave (its bounding box against the wave's),
+// for the larger of the band's thresholds.
+__device__ __forceinline__ bool far_tile(Const<float> *bx, const float (&lo)[3],
+                                         const float (&hi)[3], float far2)
+{
+    const float gx = fmaxf(0.0f, fmaxf(bx[0] - hi[0], lo[0] - bx[4]));
+    const float gy = fmaxf(0.0f, fmaxf(bx[1] - hi[1], lo[1] - bx[5]));
+    const float gz = fmaxf(0.0f, fmaxf(bx[2] - hi[2], lo[2] - bx[6]));
+    const float gap2 = gx * gx + gy * gy + gz * gz;
+    return __builtin_amdgcn_readfirstlane(gap2 >= far2 ? 1 : 0) != 0;
+}
+
+// ------------------------------------------------------------------ FP32 one-sided force kernel
 
 __device__ __forceinline__ float4 lds4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
-// One force unit of the plain mode: i-block `ib` (256 sorted slots, one per lane) against j
-// chunk `c` (a run of whole tiles), one running FP32 sum per element in tile order.
-__device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c,
-                                               float (*sh)[3][TJ])
+// One tile's 256 j, eight at a time, each stage of the pair code for all eight before the next: one
+// running sum per element leaves n / 64 waves, two per SIMD at 131,072 elements, and a wave on its
+// own issues a dependent chain at half the rate of independent instructions (pair after pair
+// 7.06 ms an evaluation at 131,072, staged 5.12; with at most one wave per SIMD the raised priority
+// of the reciprocal square roots only costs issue slots: 2.25 -> 2.04 ms at 65,536 without it, 5.50
+// with two waves without it). Near tiles: the contact law s = min(w^3, c1 - c2 w) for every
+// pair; far tiles (every pair at r >= D, proven from bounding boxes): s = w^3, the value the contact
+// law's minimum selects there.
+template <bool FAR, bool PRIO>
+__device__ __forceinline__ void plain_tile(const float *sx, const float *sy, const float *sz,
+                                           float xi, float yi, float zi, float c1, float nc2,
+                                           float eps, float &ax, float &ay, float &az)
+{
+    constexpr int G = 8;
+    float4 X[2], Y[2], Z[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        X[h] = lds4(sx + 4 * h);
+        Y[h] = lds4(sy + 4 * h);
+        Z[h] = lds4(sz + 4 * h);
+    }
+#pragma unroll 1
+    for (int jj = 0; jj < TJ; jj += G) {
+        float dx[G], dy[G], dz[G], s[G];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float x[4] = {X[h].x, X[h].y, X[h].z, X[h].w};
+            const float y[4] = {Y[h].x, Y[h].y, Y[h].z, Y[h].w};
+            const float z[4] = {Z[h].x, Z[h].y, Z[h].z, Z[h].w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                dx[4 * h + q] = x[q] - xi;
+                dy[4 * h + q] = y[q] - yi;
+                dz[4 * h + q] = z[q] - zi;
+            }
+        }
+        const int nx = (jj + G) & (TJ - 1);  // the next eight (after the last the first: not used)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            X[h] = lds4(sx + nx + 4 * h);
+            Y[h] = lds4(sy + nx + 4 * h);
+            Z[h] = lds4(sz + nx + 4 * h);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < G; ++q) s[q] = fmaf(dz[q], dz[q], eps);
+#pragma unroll
+        for (int q = 0; q < G; ++q) s[q] = fmaf(dy[q], dy[q], s[q]);
+#pragma unroll
+        for (int q = 0; q < G; ++q) s[q] = fmaf(dx[q], dx[q], s[q]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < G; ++q) s[q] = PRIO ? rsq_p(s[q]) : __builtin_amdgcn_rsqf(s[q]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const float w = s[q];
+            const float w3 = (w * w) * w;
+            s[q] = FAR ? w3 : fminf(w3, fmaf(nc2, w, c1));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            ax = fmaf(s[q], dx[q], ax);
+            ay = fmaf(s[q], dy[q], ay);
+            az = fmaf(s[q], dz[q], az);
+        }
+    }
+}
+
+// One force unit of the plain mode: the 256 elements from ib 256 in sorted order without padding, one
+// per lane, against j chunk `c` (a run of whole tiles), one running FP32 sum per element in tile
+// order.
+template <bool PRIO>
+__device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c, float (*sh)[3][TJ])
 {
     const int tid = threadIdx.x;
     auto *__restrict__ XS = glob<const float>(S.xs);
@@ -303,21 +366,27 @@ __device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c,
     auto *__restrict__ ZS = glob<const float>(S.zs);
     auto *st = cst(S.st);
 
-    const int slot = ib * BT + tid;
+    const int g = ib * BT + tid;  // among the real elements: star 1's n1 slots, then from slot p1
+    const bool real = g < S.n;
+    const int gc = real ? g : S.n - 1;
+    const int istar = gc >= S.n1 ? 1 : 0;
+    const int slot = istar ? S.p1 + (gc - S.n1) : gc;
     const float xi = XS[slot], yi = YS[slot], zi = ZS[slot];
     float ax = 0.0f, ay = 0.0f, az = 0.0f;
-    const bool real = glob<const int32_t>(S.perm)[slot] >= 0;
-    float lo[3], hi[3];
-    lo[0] = wave_min(real ? xi : INFINITY);
-    lo[1] = wave_min(real ? yi : INFINITY);
-    lo[2] = wave_min(real ? zi : INFINITY);
-    hi[0] = wave_max(real ? xi : -INFINITY);
-    hi[1] = wave_max(real ? yi : -INFINITY);
-    hi[2] = wave_max(real ? zi : -INFINITY);
-    // the block's slots lie in one star (p1 is a multiple of TJ)
-    const int istar = ib * BT >= S.p1 ? 1 : 0;
-    const float c1a = st->c1f[istar], nc2a = -st->c2f[istar], far2a = st->far2f[istar];
-    const float c1b = st->c1f[istar + 1], nc2b = -st->c2f[istar + 1], far2b = st->far2f[istar + 1];
+    float lo[3] = {wave_min(xi), wave_min(yi), wave_min(zi)};
+    float hi[3] = {wave_max(xi), wave_max(yi), wave_max(zi)};
+    const float c1a = st->c1f[istar], nc2a = -st->c2f[istar];
+    const float c1b = st->c1f[istar + 1], nc2b = -st->c2f[istar + 1];
+    // the wave's (a wave may hold the end of one star and the start of the other)
+    const float far2a = wave_uniform(wave_max(st->far2f[istar]));
+    const float far2b = wave_uniform(wave_max(st->far2f[istar + 1]));
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        lo[d] = wave_uniform(lo[d]);
+        hi[d] = wave_uniform(hi[d]);
+    }
+    float eps;  // in a vector register: a literal halves the issue rate
+    asm("v_mov_b32 %0, 0x179abe15" : "=v"(eps));  // 1e-24
 
     // chunk c covers tiles [c ntiles / nsplit, (c + 1) ntiles / nsplit): sizes differ by <= 1
     const int t0 = (int)(((int64_t)c * S.ntiles) / S.nsplit);
@@ -340,31 +409,19 @@ __device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c,
             pz = ZS[(t + 1) * TJ + tid];
         }
         const bool jstar = t * TJ >= S.p1;
-        auto *bx = cst(S.tbox) + (size_t)t * 8;
-        const float gx = fmaxf(0.0f, fmaxf(bx[0] - hi[0], lo[0] - bx[4]));
-        const float gy = fmaxf(0.0f, fmaxf(bx[1] - hi[1], lo[1] - bx[5]));
-        const float gz = fmaxf(0.0f, fmaxf(bx[2] - hi[2], lo[2] - bx[6]));
-        const float gap2 = gx * gx + gy * gy + gz * gz;
-        const int far = __builtin_amdgcn_readfirstlane(gap2 >= (jstar ? far2b : far2a) ? 1 : 0);
         const float *sx = sh[buf][0], *sy = sh[buf][1], *sz = sh[buf][2];
-        if (far) {
-#pragma unroll 2
-            for (int jj = 0; jj < TJ; jj += 4)
-                interact4_f32<true>(lds4(sx + jj), lds4(sy + jj), lds4(sz + jj), xi, yi, zi, ax,
-                                    ay, az, 0.f, 0.f);
+        if (far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi, jstar ? far2b : far2a)) {
+            plain_tile<true, PRIO>(sx, sy, sz, xi, yi, zi, 0.f, 0.f, eps, ax, ay, az);
         } else {
-            const float c1 = jstar ? c1b : c1a, nc2 = jstar ? nc2b : nc2a;
-#pragma unroll 2
-            for (int jj = 0; jj < TJ; jj += 4)
-                interact4_f32<false>(lds4(sx + jj), lds4(sy + jj), lds4(sz + jj), xi, yi, zi, ax,
-                                     ay, az, c1, nc2);
+            plain_tile<false, PRIO>(sx, sy, sz, xi, yi, zi, jstar ? c1b : c1a, jstar ? nc2b : nc2a, eps,
+                              ax, ay, az);
         }
     }
     __syncthreads();  // the next unit of this block reuses both LDS buffers
 
-    const int idx = glob<const int32_t>(S.perm)[slot];
-    if (idx < 0) return;
+    if (!real) return;
     if (S.nsplit == 1) {
+        const int idx = glob<const int32_t>(S.perm)[slot];
         const float gm = st->gm_f;
         glob<float>(S.ax)[idx] = gm * ax;
         glob<float>(S.ay)[idx] = gm * ay;
@@ -379,6 +436,7 @@ __device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c,
     }
 }
 
+template <bool PRIO>
 __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(PLAIN_WAVES)))
 void k_force_f32(Launch L)
 {
@@ -389,7 +447,7 @@ void k_force_f32(Launch L)
         const int local = u - S.unit_begin;
         const int ib = local / S.nsplit;
         const int c = local - ib * S.nsplit;
-        force_unit_f32(S, ib, c, sh);
+        force_unit_f32<PRIO>(S, ib, c, sh);
     }
 }
 
@@ -431,12 +489,6 @@ void k_force_f32(Launch L)
 __device__ __forceinline__ float xbar_ror1(float v, int addr)
 {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v)));
-}
-
-// A value that is the same in every lane, moved to a scalar register.
-__device__ __forceinline__ float wave_uniform(float v)
-{
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 // Constants of one pair class for the FP32 kernels.
@@ -522,18 +574,6 @@ __device__ __forceinline__ size_t react_group_offset(int g, int ntiles, int kr)
 {
     return (size_t)3 * TJ *
            ((size_t)g * (ntiles - 1) - (size_t)kr * (size_t)g * (size_t)(g - 1) / 2);
-}
-
-// Whether a tile lies at least D from every i of the wave (its bounding box against the wave's),
-// for the larger of the band's thresholds.
-__device__ __forceinline__ bool far_tile(Const<float> *bx, const float (&lo)[3],
-                                         const float (&hi)[3], float far2)
-{
-    const float gx = fmaxf(0.0f, fmaxf(bx[0] - hi[0], lo[0] - bx[4]));
-    const float gy = fmaxf(0.0f, fmaxf(bx[1] - hi[1], lo[1] - bx[5]));
-    const float gz = fmaxf(0.0f, fmaxf(bx[2] - hi[2], lo[2] - bx[6]));
-    const float gap2 = gx * gx + gy * gy + gz * gz;
-    return __builtin_amdgcn_readfirstlane(gap2 >= far2 ? 1 : 0) != 0;
 }
 
 // a = G m (sum of the element's own chunk partials, then the reactions of every band with a
@@ -1996,7 +2036,12 @@ hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks,
             }
         } else if (mode == 0) {
             if (L.law != 0 || b != 1) return hipErrorInvalidValue;  // no eqs. (4)-(6), no bands
-            hipLaunchKernelGGL(k_force_f32, g, blk, 0, s, R);
+            if (end - begin > CU_COUNT) {
+                hipLaunchKernelGGL(k_force_f32<true>, g, blk, 0, s, R);
+            } else {
+                // at most one wave per SIMD
+                hipLaunchKernelGGL(k_force_f32<false>, g, blk, 0, s, R);
+            }
         } else if (mode == 2) {
             if (b != 1) return hipErrorInvalidValue;
             if (L.law == 0) {

@@ -117,6 +117,7 @@ void finish_split(TileCfg &c, int64_t n, int64_t n1, int mode, int law, int ns, 
     // chunk c covers tiles [c ntiles / nsplit, (c + 1) ntiles / nsplit)
     c.nsplit = c.ntiles > 0 ? std::max(1, std::min(ns, c.ntiles)) : 1;
     c.jchunk = c.ntiles > 0 ? (c.ntiles + c.nsplit - 1) / c.nsplit * TJ : TJ;
+    c.n_iblocks = (int)((n + BT - 1) / BT);  // the real elements, not the padded slots
     const int64_t units = (int64_t)c.n_iblocks * c.nsplit;
     c.n_units = units > INT32_MAX ? -1 : (int)units;
 }
