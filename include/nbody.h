@@ -218,9 +218,8 @@ int nb_retention(nb_system *s, int32_t *n_past, int32_t *n_bound, void *stream);
  * the contact test, and the force evaluation slows. The new order changes the order of the pair
  * sums, so results agree with an unsorted run to rounding, not bitwise; a system re-sorted by a
  * rule that depends only on its own state (for example every K of its own steps) gets the same
- * bits alone and in any batch. Synchronises `stream` (the positions are read back and sorted on
- * the host); work on the system must be ordered before the call. NB_E_INVAL for a null or
- * foreign system. */
+ * bits alone and in any batch. Synchronises `stream`; work on the system must be ordered before
+ * the call. NB_E_INVAL for a null or foreign system. */
 int nb_resort(nb_system *s, void *stream);
 
 /* The sorted order the force kernels work in (a diagnostic of the layout, no part of the model):

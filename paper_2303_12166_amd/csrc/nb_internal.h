@@ -31,6 +31,13 @@ constexpr int KERNEL_CLASSES = 4;    // force kernels of a launch: one-sided, ba
 constexpr int ADV_INIT = 2;      // k_advance: record the sides at creation
 constexpr int RED_DIAG = 16;     // record slots [16, 32): diagnostics sums
 constexpr int RED_RET = 26;      // record slots [26, 31): retention sums (after the diagnostics)
+constexpr int SORT_TILE = 2048;  // elements per workgroup of a pass of the order's sort
+constexpr int SORT_BOUNDS = 64;  // most workgroups that find the stars' bounding boxes
+constexpr size_t sort_work_bytes(int64_t n)
+{
+    return 12 * SORT_BOUNDS * sizeof(double) +
+           256 * sizeof(uint32_t) * (1 + (size_t)((n + SORT_TILE - 1) / SORT_TILE));
+}
 constexpr int L1_LOG_CAP = 4096; // rows of the per-step L1 log
 // Position of padding slots in the sorted layout. A padding element at 1e18 (FP32) or 1e150
 // (FP64) gives w^3 below the type's smallest subnormal, so its contribution is exactly 0.
@@ -139,8 +146,9 @@ struct TableChunk {
 
 // Host-side launchers (nb_kernels.hip). All return the HIP status of the launch.
 hipError_t launch_init_state(DevState *st, const DevState &init, hipStream_t s);
-hipError_t launch_fill_sorted(void *xs, void *ys, void *zs, int nalloc, int mode, bool sentinel,
-                              hipStream_t s);
+hipError_t launch_reset_sorted(const SysDesc &d, int mode, hipStream_t s);
+hipError_t launch_zero_velocities(const SysDesc &d, int mode, hipStream_t s);
+hipError_t launch_sort(const SysDesc &d, int mode, void *work, hipStream_t s);
 hipError_t launch_gather(const Launch &L, int mode, hipStream_t s);
 hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks, hipStream_t s);
 hipError_t launch_combine(const Launch &L, int mode, hipStream_t s);

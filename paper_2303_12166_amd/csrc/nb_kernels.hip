@@ -177,14 +177,231 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// Sentinel positions in every slot of the sorted copy and -1 in the padding slots of the order.
 template <typename T>
-__global__ __launch_bounds__(BT) void k_fill_sorted(T *xs, T *ys, T *zs, int nalloc, T value)
+__global__ __launch_bounds__(BT) void k_reset_sorted(T *xs, T *ys, T *zs, int32_t *perm, int n, int n1,
+                                                     int p1, int nalloc, T value)
 {
     const int k = blockIdx.x * BT + threadIdx.x;
-    if (k < nalloc) {
-        xs[k] = value;
-        ys[k] = value;
-        zs[k] = value;
+    if (k >= nalloc) return;
+    xs[k] = value;
+    ys[k] = value;
+    zs[k] = value;
+    if ((k >= n1 && k < p1) || k >= p1 + (n - n1)) perm[k] = -1;
+}
+
+template <typename T>
+__global__ __launch_bounds__(BT) void k_zero_sorted(T *xs, T *ys, T *zs, int nalloc)
+{
+    const int k = blockIdx.x * BT + threadIdx.x;
+    if (k < nalloc) xs[k] = ys[k] = zs[k] = 0;
+}
+
+// ------------------------------------------------------------------ sorted order
+//
+// The order of a system's slots: star by star, by the Morton code of the position (10 bits per axis
+// inside the star's bounding box), ties by index. A least-digit radix sort of (star, code) from
+// index order, four stable passes of eight bits over tiles of SORT_TILE elements: a histogram per
+// tile, its prefix sums per digit, and the scatter. The arrays it works in are those of the sorted
+// copy, which is rebuilt before anything reads it. Launches bound it (fifteen, a few microseconds
+// each) up to some 100,000 elements; a read-back and a comparison sort on the host took 1.37 ms at
+// 32,768 elements and 13.2 ms at 262,144 (nb_resort), this 0.08 and 0.09.
+
+// Per workgroup: each star's smallest and largest finite coordinates.
+template <typename T>
+__global__ __launch_bounds__(BT) void k_sort_bounds(const T *x, const T *y, const T *z, int n, int n1,
+                                                    double *out)
+{
+    __shared__ double lds[12][BT / 64];
+    double v[12];  // per star: min x, y, z, then -max x, y, z
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = 1e300;
+    for (int i = blockIdx.x * BT + threadIdx.x; i < n; i += gridDim.x * BT) {
+        const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if (!isfinite(p[d])) continue;
+#pragma unroll
+            for (int star = 0; star < 2; ++star) {
+                if ((i >= n1) != (star == 1)) continue;
+                v[6 * star + d] = fmin(v[6 * star + d], p[d]);
+                v[6 * star + 3 + d] = fmin(v[6 * star + 3 + d], -p[d]);
+            }
+        }
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) v[k] = fmin(v[k], __shfl_xor(v[k], off, 64));
+        if (lane == 0) lds[k][wave] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 12) {
+        const int k = threadIdx.x;
+        out[12 * blockIdx.x + k] = fmin(fmin(lds[k][0], lds[k][1]), fmin(lds[k][2], lds[k][3]));
+    }
+}
+
+__device__ __forceinline__ uint32_t spread10(uint32_t v)
+{
+    v &= 0x3ffu;
+    v = (v | (v << 16)) & 0x030000ffu;
+    v = (v | (v << 8)) & 0x0300f00fu;
+    v = (v | (v << 4)) & 0x030c30c3u;
+    v = (v | (v << 2)) & 0x09249249u;
+    return v;
+}
+
+template <typename T>
+__global__ __launch_bounds__(BT) void k_sort_keys(const T *x, const T *y, const T *z, int n, int n1,
+                                                  const double *bounds, int n_bounds, uint32_t *keys)
+{
+    __shared__ double box[12];
+    if (threadIdx.x < 64) {
+        // one wave: lane 5 k .. 5 k + 4 take value k of every fifth workgroup's bounds
+        const int k = threadIdx.x / 5, part = threadIdx.x % 5;
+        double v = 1e300;
+        if (k < 12) {
+#pragma unroll 4
+            for (int b = part; b < n_bounds; b += 5) v = fmin(v, bounds[12 * b + k]);
+        }
+        double m = v;
+#pragma unroll
+        for (int q = 1; q < 5; ++q) m = fmin(m, __shfl(v, min(63, 5 * k + (part + q) % 5), 64));
+        if (k < 12 && part == 0) box[k] = m;
+    }
+    __syncthreads();
+    const int i = blockIdx.x * BT + threadIdx.x;
+    if (i >= n) return;
+    const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
+    const int star = i >= n1 ? 1 : 0;
+    uint32_t key = (uint32_t)star << 30;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double lo = box[6 * star + d], hi = -box[6 * star + 3 + d];
+        const double span = hi > lo ? hi - lo : 1.0;
+        double f = isfinite(p[d]) ? (p[d] - lo) / span : 0.0;
+        f = f < 0.0 ? 0.0 : f;
+        f = 1.0 < f ? 1.0 : f;
+        f = f * 1024.0;
+        key |= spread10((uint32_t)(f < 1023.0 ? f : 1023.0)) << d;
+    }
+    keys[i] = key;
+}
+
+// Digit counts of one tile, stored digit by digit (entry digit n_tiles + tile).
+__global__ __launch_bounds__(BT) void k_sort_hist(const uint32_t *keys, int n, int shift, int n_tiles,
+                                                  uint32_t *hist)
+{
+    __shared__ uint32_t cnt[256];
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int base = blockIdx.x * SORT_TILE;
+#pragma unroll
+    for (int r = 0; r < SORT_TILE / BT; ++r) {
+        const int i = base + r * BT + threadIdx.x;
+        if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & 255u], 1u);
+    }
+    __syncthreads();
+    hist[(size_t)threadIdx.x * n_tiles + blockIdx.x] = cnt[threadIdx.x];
+}
+
+// Exclusive prefix sum of 256 values, one per thread; the last thread also returns the total.
+__device__ __forceinline__ uint32_t scan256(uint32_t v, uint32_t *wsum, uint32_t &total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t x = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
+    }
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int w = 0; w < wave; ++w) before += wsum[w];
+    total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    __syncthreads();
+    return before + x - v;
+}
+
+// One digit per workgroup: its tiles' counts become the elements before each tile, and its total.
+__global__ __launch_bounds__(BT) void k_sort_scan(uint32_t *hist, int n_tiles, uint32_t *totals)
+{
+    __shared__ uint32_t wsum[BT / 64];
+    uint32_t *h = hist + (size_t)blockIdx.x * n_tiles;
+    uint32_t carry = 0;
+    for (int t0 = 0; t0 < n_tiles; t0 += BT) {
+        const int t = t0 + threadIdx.x;
+        const uint32_t v = t < n_tiles ? h[t] : 0u;
+        uint32_t total;
+        const uint32_t before = scan256(v, wsum, total);
+        if (t < n_tiles) h[t] = carry + before;
+        carry += total;
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// Moves one tile's elements to their places, in order within a digit: every wave takes a run of the
+// tile, 64 elements at a time, an element's place among equal digits of the 64 being the number
+// of lanes before it that hold the same one. vals_in null: the index itself (first pass). keys_out
+// null: the last pass, where the values become the order of the slots.
+__global__ __launch_bounds__(BT) void k_sort_scatter(const uint32_t *keys_in, const int32_t *vals_in,
+                                                     uint32_t *keys_out, int32_t *vals_out, int n,
+                                                     int shift, int n_tiles, const uint32_t *hist,
+                                                     const uint32_t *totals, int n1, int p1)
+{
+    __shared__ uint32_t wsum[BT / 64];
+    __shared__ volatile uint32_t at[BT / 64][256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int ROWS = SORT_TILE / BT;
+    const int base = blockIdx.x * SORT_TILE + wave * (SORT_TILE / 4);
+    uint32_t key[ROWS];
+#pragma unroll
+    for (int w = 0; w < BT / 64; ++w) at[w][tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int i = base + 64 * r + lane;
+        key[r] = i < n ? keys_in[i] : 0u;
+        if (i < n) atomicAdd(const_cast<uint32_t *>(&at[wave][(key[r] >> shift) & 255u]), 1u);
+    }
+    uint32_t total;
+    uint32_t place = scan256(totals[tid], wsum, total) + hist[(size_t)tid * n_tiles + blockIdx.x];
+#pragma unroll
+    for (int w = 0; w < BT / 64; ++w) {
+        const uint32_t c = at[w][tid];
+        at[w][tid] = place;
+        place += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int i = base + 64 * r + lane;
+        const bool valid = i < n;
+        const uint32_t digit = (key[r] >> shift) & 255u;
+        unsigned long long same = __ballot(valid);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const unsigned long long one = __ballot((digit >> b) & 1u);
+            same &= (digit >> b) & 1u ? one : ~one;
+        }
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
+        uint32_t pos = 0;
+        if (valid) pos = at[wave][digit] + rank;
+        __builtin_amdgcn_wave_barrier();
+        if (valid && rank == 0) at[wave][digit] = pos + __popcll(same);
+        __builtin_amdgcn_wave_barrier();
+        if (valid) {
+            const int32_t val = vals_in ? vals_in[i] : i;
+            if (keys_out) {
+                keys_out[pos] = key[r];
+                vals_out[pos] = val;
+            } else {
+                vals_out[(int)pos < n1 ? pos : p1 + (pos - n1)] = val;
+            }
+        }
     }
 }
 
@@ -1979,22 +2196,72 @@ hipError_t launch_init_state(DevState *st, const DevState &init, hipStream_t s)
     return hipGetLastError();
 }
 
-// sentinel: fill with the padding position; otherwise with zeros (sorted velocities)
-hipError_t launch_fill_sorted(void *xs, void *ys, void *zs, int nalloc, int mode, bool sentinel,
-                              hipStream_t s)
+hipError_t launch_reset_sorted(const SysDesc &d, int mode, hipStream_t s)
 {
-    if (nalloc <= 0) return hipSuccess;
-    const dim3 g((nalloc + BT - 1) / BT), b(BT);
+    const dim3 g((d.nalloc + BT - 1) / BT), b(BT);
     if (mode == 2) {
-        hipLaunchKernelGGL(k_fill_sorted<double>, g, b, 0, s, static_cast<double *>(xs),
-                           static_cast<double *>(ys), static_cast<double *>(zs), nalloc,
-                           sentinel ? SENTINEL_F64 : 0.0);
+        hipLaunchKernelGGL(k_reset_sorted<double>, g, b, 0, s, static_cast<double *>(d.xs),
+                           static_cast<double *>(d.ys), static_cast<double *>(d.zs), d.perm, d.n,
+                           d.n1, d.p1, d.nalloc, SENTINEL_F64);
     } else {
-        hipLaunchKernelGGL(k_fill_sorted<float>, g, b, 0, s, static_cast<float *>(xs),
-                           static_cast<float *>(ys), static_cast<float *>(zs), nalloc,
-                           sentinel ? SENTINEL_F32 : 0.0f);
+        hipLaunchKernelGGL(k_reset_sorted<float>, g, b, 0, s, static_cast<float *>(d.xs),
+                           static_cast<float *>(d.ys), static_cast<float *>(d.zs), d.perm, d.n,
+                           d.n1, d.p1, d.nalloc, SENTINEL_F32);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_zero_velocities(const SysDesc &d, int mode, hipStream_t s)
+{
+    const dim3 g((d.nalloc + BT - 1) / BT), b(BT);
+    if (mode == 2) {
+        hipLaunchKernelGGL(k_zero_sorted<double>, g, b, 0, s, static_cast<double *>(d.vxs),
+                           static_cast<double *>(d.vys), static_cast<double *>(d.vzs), d.nalloc);
+    } else {
+        hipLaunchKernelGGL(k_zero_sorted<float>, g, b, 0, s, static_cast<float *>(d.vxs),
+                           static_cast<float *>(d.vys), static_cast<float *>(d.vzs), d.nalloc);
+    }
+    return hipGetLastError();
+}
+
+template <typename T>
+static void sort_keys(const SysDesc &d, double *bounds, uint32_t *keys, hipStream_t s)
+{
+    const T *x = static_cast<const T *>(d.x), *y = static_cast<const T *>(d.y),
+            *z = static_cast<const T *>(d.z);
+    const int blocks = (d.n + BT - 1) / BT, nb = std::min(blocks, SORT_BOUNDS);
+    hipLaunchKernelGGL(k_sort_bounds<T>, dim3(nb), dim3(BT), 0, s, x, y, z, d.n, d.n1, bounds);
+    hipLaunchKernelGGL(k_sort_keys<T>, dim3(blocks), dim3(BT), 0, s, x, y, z, d.n, d.n1, bounds, nb,
+                       keys);
+}
+
+hipError_t launch_sort(const SysDesc &d, int mode, void *work, hipStream_t s)
+{
+    if (d.n > 0) {
+        double *bounds = static_cast<double *>(work);
+        uint32_t *totals = reinterpret_cast<uint32_t *>(bounds + 12 * SORT_BOUNDS);
+        uint32_t *hist = totals + 256;
+        const int n_tiles = (d.n + SORT_TILE - 1) / SORT_TILE;
+        uint32_t *keys[2] = {static_cast<uint32_t *>(d.xs), static_cast<uint32_t *>(d.ys)};
+        int32_t *vals[2] = {d.perm, static_cast<int32_t *>(d.zs)};
+        if (mode == 2) {
+            sort_keys<double>(d, bounds, keys[0], s);
+        } else {
+            sort_keys<float>(d, bounds, keys[0], s);
+        }
+        for (int pass = 0; pass < 4; ++pass) {
+            const int in = pass & 1, out = in ^ 1;
+            hipLaunchKernelGGL(k_sort_hist, dim3(n_tiles), dim3(BT), 0, s, keys[in], d.n, 8 * pass,
+                               n_tiles, hist);
+            hipLaunchKernelGGL(k_sort_scan, dim3(256), dim3(BT), 0, s, hist, n_tiles, totals);
+            hipLaunchKernelGGL(k_sort_scatter, dim3(n_tiles), dim3(BT), 0, s, keys[in],
+                               pass == 0 ? nullptr : vals[in], pass == 3 ? nullptr : keys[out],
+                               vals[out], d.n, 8 * pass, n_tiles, hist, totals, d.n1, d.p1);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return launch_reset_sorted(d, mode, s);
 }
 
 hipError_t launch_gather(const Launch &L, int mode, hipStream_t s)

@@ -49,6 +49,7 @@ struct TileCfg {
     int npad, p1, nalloc, ntiles;
     int sym, ch;            // symmetric kernel (Kahan and FP64 modes) and its tiles per chunk
     int rows;               // tile rows per band of the symmetric kernel (1, 2 or 4)
+    int64_t n_sort;         // elements the order's sort works on
     int one_sided, n_rec;   // one-sided force kernel; records of a step
     int pe_ch, n_peunits;   // potential energy: tiles per chunk, (tile row, chunk) units
     size_t react_floats;    // reaction partials of the symmetric kernel (elements of the mode's type)
@@ -137,6 +138,7 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
 {
     TileCfg c{};
     c.ki = 1;
+    c.n_sort = n;
     c.iblock = BT;
     c.p1 = (int)round_up(n1, TJ);
     c.npad = c.p1 + (int)round_up(n - n1, TJ);
@@ -181,7 +183,7 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
 }
 
 struct Layout {
-    size_t state, desc, diag, red, rec, pe, log, xs, ys, zs, vxs, vys, vzs, perm, tbox, units, react,
+    size_t state, desc, diag, red, rec, sort, pe, log, xs, ys, zs, vxs, vys, vzs, perm, tbox, units, react,
         part, total;
 };
 
@@ -203,6 +205,7 @@ Layout layout_for(int mode, int law, const TileCfg &c)
     L.diag = take(sizeof(DiagOut));
     L.red = take((size_t)std::max(c.n_ounits, 1) * RED_STRIDE * sizeof(double));
     L.rec = take((size_t)std::max(std::max(c.n_ounits, c.n_rec), 1) * REC_STRIDE * sizeof(double));
+    L.sort = take(sort_work_bytes((int64_t)c.n_sort));
     L.pe = take((size_t)c.n_peunits * sizeof(double));
     L.log = take((size_t)L1_LOG_CAP * 4 * sizeof(int32_t));
     L.xs = take((size_t)c.nalloc * elem);
@@ -223,89 +226,6 @@ Layout layout_for(int mode, int law, const TileCfg &c)
 }
 
 size_t layout_total(int mode, int law, const TileCfg &c) { return layout_for(mode, law, c).total; }
-
-// Morton order of each star's initial positions (10 bits per axis inside the star's bounding
-// box, ties by index): consecutive sorted slots are close in space, so tiles have small boxes.
-uint32_t spread10(uint32_t v)
-{
-    v &= 0x3ffu;
-    v = (v | (v << 16)) & 0x030000ffu;
-    v = (v | (v << 8)) & 0x0300f00fu;
-    v = (v | (v << 4)) & 0x030c30c3u;
-    v = (v | (v << 2)) & 0x09249249u;
-    return v;
-}
-
-template <typename T>
-void morton_order(const T *x, const T *y, const T *z, int64_t b, int64_t e,
-                  std::vector<int32_t> &out)
-{
-    out.clear();
-    if (e <= b) return;
-    double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-    for (int64_t i = b; i < e; ++i) {
-        const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
-        for (int d = 0; d < 3; ++d) {
-            if (std::isfinite(p[d])) {
-                lo[d] = std::min(lo[d], p[d]);
-                hi[d] = std::max(hi[d], p[d]);
-            }
-        }
-    }
-    std::vector<std::pair<uint32_t, int32_t>> keys((size_t)(e - b));
-    for (int64_t i = b; i < e; ++i) {
-        const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
-        uint32_t q[3];
-        for (int d = 0; d < 3; ++d) {
-            const double span = hi[d] > lo[d] ? hi[d] - lo[d] : 1.0;
-            double f = std::isfinite(p[d]) ? (p[d] - lo[d]) / span : 0.0;
-            f = std::min(std::max(f, 0.0), 1.0);
-            q[d] = (uint32_t)std::min(1023.0, f * 1024.0);
-        }
-        keys[(size_t)(i - b)] = {spread10(q[0]) | (spread10(q[1]) << 1) | (spread10(q[2]) << 2),
-                                 (int32_t)i};
-    }
-    std::sort(keys.begin(), keys.end());
-    out.resize(keys.size());
-    for (size_t k = 0; k < keys.size(); ++k) out[k] = keys[k].second;
-}
-
-// The sorted order of the current positions (each star in Morton order, star 2 from slot p1,
-// padding -1) into `perm`, uploaded to dperm on `st`. Synchronises `st` (the positions are read
-// back first); `perm` must stay alive until the upload has completed.
-int upload_sorted_order(const nb_params *p, const nb_buffers *b, const TileCfg &cfg,
-                        int32_t *dperm, hipStream_t st, std::vector<int32_t> &perm)
-{
-    perm.assign((size_t)cfg.nalloc, -1);
-    if (p->n > 0) {
-        const size_t elem = p->mode == NB_FP64 ? sizeof(double) : sizeof(float);
-        const size_t bytes = (size_t)p->n * elem;
-        std::vector<char> hx(bytes), hy(bytes), hz(bytes);
-        if (hipMemcpyAsync(hx.data(), b->x, bytes, hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipMemcpyAsync(hy.data(), b->y, bytes, hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipMemcpyAsync(hz.data(), b->z, bytes, hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return NB_E_HIP;
-        std::vector<int32_t> o1, o2;
-        if (p->mode == NB_FP64) {
-            const double *X = (const double *)hx.data(), *Y = (const double *)hy.data(),
-                         *Z = (const double *)hz.data();
-            morton_order(X, Y, Z, 0, p->n1, o1);
-            morton_order(X, Y, Z, p->n1, p->n, o2);
-        } else {
-            const float *X = (const float *)hx.data(), *Y = (const float *)hy.data(),
-                        *Z = (const float *)hz.data();
-            morton_order(X, Y, Z, 0, p->n1, o1);
-            morton_order(X, Y, Z, p->n1, p->n, o2);
-        }
-        std::copy(o1.begin(), o1.end(), perm.begin());
-        std::copy(o2.begin(), o2.end(), perm.begin() + cfg.p1);
-    }
-    if (hipMemcpyAsync(dperm, perm.data(), perm.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                       st) != hipSuccess)
-        return NB_E_HIP;
-    return NB_OK;
-}
 
 bool params_ok(const nb_params *p)
 {
@@ -808,42 +728,34 @@ int nb_create(const nb_params *p, const nb_buffers *b, void *stream, nb_system *
     hipStream_t st = static_cast<hipStream_t>(stream);
     int rc = NB_OK;
     do {
-        // sorted layout: permutation from the initial positions (host-side Morton sort)
-        std::vector<int32_t> perm;
-        rc = upload_sorted_order(p, b, cfg, d.perm, st, perm);
-        if (rc != NB_OK) break;
+        // sorted layout: order from the initial positions
+        if (launch_sort(d, p->mode, base + lay.sort, st) != hipSuccess) { rc = NB_E_HIP; break; }
         std::vector<int32_t> units;
         if (cfg.sym) {
-            // (band, chunk) pairs, full-length chunks first (each band's last chunk may be short)
-            std::vector<std::pair<int, std::pair<int, int>>> order;
+            // (band, chunk) pairs: the full chunks in band order, then the bands' last, short ones
+            // by length
+            std::vector<std::pair<int, std::pair<int, int>>> last;
+            units.reserve((size_t)cfg.n_units * 2);
             for (int g = 0; g * cfg.rows < cfg.ntiles; ++g) {
                 const int span = cfg.ntiles - g * cfg.rows;
-                const int chunks = (span + cfg.ch - 1) / cfg.ch;
-                for (int c = 0; c < chunks; ++c) {
-                    const int len = std::min(cfg.ch, span - c * cfg.ch);
-                    order.push_back({-len, {g, c}});
+                const int full = span / cfg.ch, rest = span - full * cfg.ch;
+                for (int c = 0; c < full; ++c) {
+                    units.push_back(g);
+                    units.push_back(c);
                 }
+                if (rest > 0) last.push_back({-rest, {g, full}});
             }
-            std::stable_sort(order.begin(), order.end(),
+            std::stable_sort(last.begin(), last.end(),
                              [](const auto &a, const auto &b) { return a.first < b.first; });
-            units.reserve(order.size() * 2);
-            for (const auto &o : order) {
+            for (const auto &o : last) {
                 units.push_back(o.second.first);
                 units.push_back(o.second.second);
             }
-            if ((int)order.size() != cfg.n_units) { rc = NB_E_INVAL; break; }
+            if (units.size() != (size_t)cfg.n_units * 2) { rc = NB_E_INVAL; break; }
             if (hipMemcpyAsync(d.units, units.data(), units.size() * sizeof(int32_t),
                                hipMemcpyHostToDevice, st) != hipSuccess) { rc = NB_E_HIP; break; }
         }
-        if (launch_fill_sorted(d.xs, d.ys, d.zs, cfg.nalloc, p->mode, true, st) != hipSuccess) {
-            rc = NB_E_HIP;
-            break;
-        }
-        if (paper && launch_fill_sorted(d.vxs, d.vys, d.vzs, cfg.nalloc, p->mode, false, st) !=
-                         hipSuccess) {
-            rc = NB_E_HIP;
-            break;
-        }
+        if (paper && launch_zero_velocities(d, p->mode, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (launch_init_state(s->d_state, init, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (hipMemcpyAsync(s->d_desc, &s->desc, sizeof(SysDesc), hipMemcpyHostToDevice, st) !=
             hipSuccess) { rc = NB_E_HIP; break; }
@@ -1133,10 +1045,9 @@ int nb_resort(nb_system *s, void *stream)
 {
     if (!s || !on_own_device(s)) return NB_E_INVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    std::vector<int32_t> perm;
-    const int rc = upload_sorted_order(&s->p, &s->b, s->cfg, s->desc.perm, st, perm);
-    if (rc != NB_OK) return rc;
-    NB_TRY(hipStreamSynchronize(st));  // perm is read by the upload until it completes
+    NB_TRY(launch_sort(s->desc, s->p.mode,
+                       static_cast<char *>(s->b.scratch) + s->lay.sort, st));
+    NB_TRY(hipStreamSynchronize(st));
     return NB_OK;
 }
 
