@@ -53,15 +53,18 @@ class System:
         k = dict(dtype=dtype, device=self.device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
 
-        def col(a, c):
-            return torch.from_numpy(np.ascontiguousarray(a[:, c])).to(**k) if n else \
-                torch.zeros(1, **k)
+        def cols(a):
+            # one upload of the rows, turned into three contiguous columns on the device
+            if not n:
+                return [torch.zeros(1, **k) for _ in range(3)]
+            rows = torch.from_numpy(np.ascontiguousarray(a[:, :3])).to(self.device)
+            return list(rows.t().to(dtype).contiguous())
 
         # every upload and allocation is ordered on the system's stream
         with torch.cuda.stream(self.stream):
-            self.x, self.y, self.z = col(pos, 0), col(pos, 1), col(pos, 2)
-            self.vx, self.vy, self.vz = col(vel, 0), col(vel, 1), col(vel, 2)
-            self.ax, self.ay, self.az = (torch.zeros(max(n, 1), **k) for _ in range(3))
+            self.x, self.y, self.z = cols(pos)
+            self.vx, self.vy, self.vz = cols(vel)
+            self.ax, self.ay, self.az = torch.zeros(3, max(n, 1), **k)
             self.side = torch.zeros(max(n, 1), dtype=torch.int8, device=self.device)
             # 256-byte alignment: over-allocate and offset
             self._scratch = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
