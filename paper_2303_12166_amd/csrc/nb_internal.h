@@ -47,28 +47,36 @@ constexpr float FAR_MARGIN = 2.0e-5f;  // relative margin on D^2 for the far-til
 
 // Pair classes: 0 = star 1 with star 1, 1 = across the stars, 2 = star 2 with star 2.
 
+// What the donor growth changes: the donor's element diameter and the force constants that follow.
+struct LawState {
+    double D2;               // FP64 master
+    double c1d[3], c2d[3];   // 11 / D^3 and 10 / D^2 per pair class
+    float c1f[3], c2f[3];    // FP32 copies used by the FP32 kernels
+    float far2f[3];          // (1 + FAR_MARGIN) D^2 per pair class
+    float lD_f[3];           // D per pair class
+    int32_t growth_stopped, pad;
+};
+
 // Per-system state that lives in device memory (first bytes of the system's workspace).
 struct alignas(16) DevState {
     // FP64 masters
-    double D1, D2, D2_0, R2_0, rL_a, growth_rate;
+    double D1, D2_0, R2_0, rL_a, growth_rate;
     double G, m, dt, xi_l1;
-    double c1d[3], c2d[3];   // 11 / D^3 and 10 / D^2 per pair class
     double gm_d, h_d;        // G m and dt / 2
     // L1 plane of the current step
     double com1[3], com2[3], e[3], xi_cut;
-    // FP32 copies used by the FP32 kernels
-    float c1f[3], c2f[3];
-    float far2f[3];          // (1 + FAR_MARGIN) D^2 per pair class
     float gm_f, h_f, dt_f, pad_f;
+    LawState cur;            // after the last completed call
+    LawState slot[2];        // within a call, one-sided systems: before odd and before even steps
     int64_t step;
-    int32_t growth_on, growth_stopped;
-    int32_t n_past, fwd, bwd, nonfinite;
-    int32_t plane_ok, law;
+    int64_t step_done;       // within a call, one-sided systems: `step` after the step in progress
+    int32_t growth_on, nonfinite;
+    int32_t n_past, fwd, bwd;
+    int32_t plane_ok, law, pad_s;
     // element law of eqs. (4)-(6), with the overlap volume written as (pi / 12) (D - r)^2
     // (r + 2D), D = 2R the pair's element diameter: gc = gamma pi / (12 G m^2) and
     // gcb = beta gc scale it for converging and separating pairs; eps softens the attraction
     double gamma, beta, leps_d, lgc_d, lgcb_d;
-    float lD_f[3];           // D per pair class (follows the donor growth)
     float leps_f, lgc_f, lgcb_f, pad_l;
     // accretor-side retention (nb_retention): star 1's mean velocity and the two counts
     double v1[3];
@@ -95,7 +103,10 @@ struct SysDesc {
     float *tbox;          // ntiles * 8: min xyz, pad, max xyz, pad of each j tile
     void *part;         // j-split partial sums, nsplit * 3 * nalloc values (nsplit > 1 only)
     double *red;        // n_ounits * RED_STRIDE doubles
-    double *rec;        // records of a step, n_rec (at creation n_ounits) * REC_STRIDE doubles
+    double *rec;        // records of a step, rec_len * REC_STRIDE doubles (one-sided: twice, the
+                        // second for odd steps of a call)
+    void *alt;          // one-sided systems: positions and half-step velocities of three steps of a
+                        // call, 3 * 6 * nalloc values
     double *pe_part;    // potential-energy partials, n_peunits doubles
     int32_t *l1_log;    // L1_LOG_CAP * 4 int32
     DiagOut *diag;
@@ -105,6 +116,7 @@ struct SysDesc {
     int32_t n_units, n_ounits;  // force units (n_iblocks * nsplit) and O(N) units (ceil(n / BT))
     int32_t n_rec, one_sided;   // records of a step; 1 for the one-sided force kernel, whose units
                                 // are its workgroups
+    int32_t rec_len, pad3;      // at least n_rec and n_ounits (at creation there are n_ounits records)
     int32_t unit_begin, ounit_begin;  // prefix offsets in the launch's segment table
     int32_t n_peunits, pe_ch;         // potential energy: units (tile row, chunk), tiles per chunk
     int32_t npad, p1, nalloc, ntiles;  // sorted layout (see above)
@@ -150,11 +162,13 @@ hipError_t launch_reset_sorted(const SysDesc &d, int mode, hipStream_t s);
 hipError_t launch_zero_velocities(const SysDesc &d, int mode, hipStream_t s);
 hipError_t launch_sort(const SysDesc &d, int mode, void *work, hipStream_t s);
 hipError_t launch_gather(const Launch &L, int mode, hipStream_t s);
-hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks, hipStream_t s);
+hipError_t launch_forces(const Launch &L, int mode, int step, int last, int max_blocks,
+                         hipStream_t s);
 hipError_t launch_combine(const Launch &L, int mode, hipStream_t s);
 hipError_t launch_kick_stats(const Launch &L, int mode, int do_kick, hipStream_t s);
 hipError_t launch_finalize_step(const Launch &L, int do_growth, hipStream_t s);
-hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, hipStream_t s);
+hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, int n_steps,
+                          hipStream_t s);
 hipError_t launch_diag(const Launch &L, int mode, int with_pe, int n_peunits, hipStream_t s);
 hipError_t launch_retention(const Launch &L, int mode, hipStream_t s);
 hipError_t launch_valu_probe(int op, float *sink, int blocks, int iters, hipStream_t s);

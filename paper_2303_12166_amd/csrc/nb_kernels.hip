@@ -592,11 +592,11 @@ __device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c, float (*
     float ax = 0.0f, ay = 0.0f, az = 0.0f;
     float lo[3] = {wave_min(xi), wave_min(yi), wave_min(zi)};
     float hi[3] = {wave_max(xi), wave_max(yi), wave_max(zi)};
-    const float c1a = st->c1f[istar], nc2a = -st->c2f[istar];
-    const float c1b = st->c1f[istar + 1], nc2b = -st->c2f[istar + 1];
+    const float c1a = st->cur.c1f[istar], nc2a = -st->cur.c2f[istar];
+    const float c1b = st->cur.c1f[istar + 1], nc2b = -st->cur.c2f[istar + 1];
     // the wave's (a wave may hold the end of one star and the start of the other)
-    const float far2a = wave_uniform(wave_max(st->far2f[istar]));
-    const float far2b = wave_uniform(wave_max(st->far2f[istar + 1]));
+    const float far2a = wave_uniform(wave_max(st->cur.far2f[istar]));
+    const float far2b = wave_uniform(wave_max(st->cur.far2f[istar + 1]));
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         lo[d] = wave_uniform(lo[d]);
@@ -726,14 +726,13 @@ __device__ __forceinline__ LawF law_uniform(LawF K)
     return K;
 }
 
-template <typename St>
-__device__ __forceinline__ LawF law_f(St st, int cls)
+__device__ __forceinline__ LawF law_f(Const<DevState> *st, Const<LawState> *ls, int cls)
 {
     LawF K;
-    K.c1 = st->c1f[cls];
-    K.nc2 = -st->c2f[cls];
-    K.D = st->lD_f[cls];
-    K.twoD = 2.0f * st->lD_f[cls];
+    K.c1 = ls->c1f[cls];
+    K.nc2 = -ls->c2f[cls];
+    K.D = ls->lD_f[cls];
+    K.twoD = 2.0f * ls->lD_f[cls];
     K.eps = st->leps_f;
     K.gc = st->lgc_f;
     K.gcb = st->lgcb_f;
@@ -930,13 +929,12 @@ struct LawD {
     double D, c1, c2, eps, gc, gcb;
 };
 
-template <typename St>
-__device__ __forceinline__ LawD law_d(St st, int cls)
+__device__ __forceinline__ LawD law_d(Const<DevState> *st, Const<LawState> *ls, int cls)
 {
     LawD K;
-    K.D = cls == 0 ? st->D1 : (cls == 2 ? st->D2 : 0.5 * (st->D1 + st->D2));
-    K.c1 = st->c1d[cls];
-    K.c2 = st->c2d[cls];
+    K.D = cls == 0 ? st->D1 : (cls == 2 ? ls->D2 : 0.5 * (st->D1 + ls->D2));
+    K.c1 = ls->c1d[cls];
+    K.c2 = ls->c2d[cls];
     K.eps = st->leps_d;
     K.gc = st->lgc_d;
     K.gcb = st->lgcb_d;
@@ -1091,15 +1089,18 @@ __device__ __forceinline__ void add_stats(double (&v)[7], double px, double py, 
     v[6] = fin ? 0.0 : 1.0;
 }
 
-// The step that the second kick completes: its number, and its L1 counts cleared for k_advance,
-// whose workgroups add to them. Called by one thread of a system.
-__device__ __forceinline__ void begin_counts(SysRef S)
+// Row of the L1 log of a step: its number, then the counts.
+__device__ __forceinline__ int32_t *log_row(SysRef S, int64_t step)
 {
-    auto *st = glob<DevState>(S.st);
-    const int64_t step = st->step + 1;
-    st->step = step;
+    return S.l1_log + 4 * (size_t)(step % L1_LOG_CAP);
+}
+
+// The counts of step number `step` start from nothing.
+__device__ __forceinline__ void clear_counts(SysRef S, int64_t step)
+{
+    DevState *st = S.st;
     st->n_past = st->fwd = st->bwd = 0;
-    auto *row = glob<int32_t>(S.l1_log) + 4 * (size_t)(step % L1_LOG_CAP);
+    int32_t *row = log_row(S, step);
     row[0] = (int32_t)step;
     row[1] = row[2] = row[3] = 0;
 }
@@ -1135,7 +1136,132 @@ __global__ __launch_bounds__(BT) void k_kick_stats(Launch L, int do_kick)
         if (threadIdx.x == 0) {
             auto *r = glob<double>(S.rec) + (size_t)local * REC_STRIDE;
             for (int k = 0; k < 7; ++k) r[k] = v[k];
-            if (do_kick && local == 0) begin_counts(S);
+            if (do_kick && local == 0) {
+                // the step that this kick completes
+                const int64_t step = S.st->step + 1;
+                S.st->step = step;
+                clear_counts(S, step);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ end of a step
+
+// Star centres and L1 plane.
+struct Plane {
+    double com1[3], com2[3], e[3], xi_cut;
+    int ok;
+};
+
+// The system's records summed by one workgroup, in the same order wherever it is done.
+__device__ __forceinline__ void sum_records(SysRef S, int first, int n_rec, double (&v)[7],
+                                            double (*lds)[BT / 64])
+{
+    for (int k = 0; k < 7; ++k) v[k] = 0.0;
+    for (int u = threadIdx.x; u < n_rec; u += BT) {
+        auto *r = glob<const double>(S.rec) + (size_t)(first + u) * REC_STRIDE;
+        for (int k = 0; k < 7; ++k) v[k] += r[k];
+    }
+    block_sum<7>(v, lds);
+}
+
+__device__ __forceinline__ void plane_of(SysRef S, const double (&v)[7], Plane &p)
+{
+    const int n1 = S.n1, n2 = S.n - S.n1;
+    for (int d = 0; d < 3; ++d) {
+        p.com1[d] = n1 > 0 ? v[d] / (double)n1 : 0.0;
+        p.com2[d] = n2 > 0 ? v[3 + d] / (double)n2 : 0.0;
+        p.e[d] = p.com2[d] - p.com1[d];
+    }
+    const double dist = sqrt(p.e[0] * p.e[0] + p.e[1] * p.e[1] + p.e[2] * p.e[2]);
+    p.ok = (n1 > 0 && n2 > 0 && dist > 0.0) ? 1 : 0;
+    for (int d = 0; d < 3; ++d) p.e[d] = p.ok ? p.e[d] / dist : 0.0;
+    p.xi_cut = glob<DevState>(S.st)->xi_l1 * dist;
+}
+
+// The donor growth update with the derived force constants: `to` is `from` after one more step.
+__device__ __forceinline__ void grow(const DevState *st, const LawState *from, LawState *to)
+{
+    LawState w = *from;
+    if (st->growth_on && !w.growth_stopped) {
+        const double R2 = st->R2_0 * w.D2 / st->D2_0;
+        if (R2 <= st->rL_a) {
+            w.D2 = w.D2 * (1.0 + st->growth_rate);
+            const double Ds[3] = {st->D1, 0.5 * (st->D1 + w.D2), w.D2};
+            for (int k = 0; k < 3; ++k) {
+                const double D = Ds[k];
+                w.c1d[k] = 11.0 / (D * D * D);
+                w.c2d[k] = 10.0 / (D * D);
+                w.c1f[k] = (float)w.c1d[k];
+                w.c2f[k] = (float)w.c2d[k];
+                w.far2f[k] = (float)(D * D * (1.0 + (double)FAR_MARGIN));
+                w.lD_f[k] = (float)D;
+            }
+        } else {
+            w.growth_stopped = 1;
+        }
+    }
+    *to = w;
+}
+
+// Records the plane and the non-finite count, and (optionally) grows the donor. Called by one thread
+// of a system.
+__device__ __forceinline__ void finish_step(SysRef S, const Plane &p, double nonfinite,
+                                            int do_growth)
+{
+    DevState *st = S.st;
+    for (int d = 0; d < 3; ++d) {
+        st->com1[d] = p.com1[d];
+        st->com2[d] = p.com2[d];
+        st->e[d] = p.e[d];
+    }
+    st->xi_cut = p.xi_cut;
+    st->plane_ok = p.ok;
+    st->nonfinite = (int32_t)nonfinite;
+    if (do_growth) grow(st, &st->cur, &st->cur);
+}
+
+struct FinishMem {
+    double lds[7][BT / 64];
+    Plane pl;
+    int cnt[3][BT / 64];
+};
+
+// Donor elements' side of the plane and the crossings since the last step, for the element i of this
+// lane at (px, py, pz); the plane is in m.pl. The counts are whole numbers, added atomically to
+// `total` (null: not kept) and `row` (null: not kept), so their order does not matter.
+template <typename T>
+__device__ __forceinline__ void classify(SysRef S, int i, T px, T py, T pz, FinishMem &m, bool init,
+                                         int32_t *total, int32_t *row)
+{
+    bool past = false, fwd = false, bwd = false;
+    if (i < S.n && i >= S.n1) {
+        const double xi = ((double)px - m.pl.com1[0]) * m.pl.e[0] +
+                          ((double)py - m.pl.com1[1]) * m.pl.e[1] +
+                          ((double)pz - m.pl.com1[2]) * m.pl.e[2];
+        past = m.pl.ok && xi < m.pl.xi_cut;
+        if (!init) {
+            const bool prev = glob<int8_t>(S.side)[i] != 0;
+            fwd = past && !prev;
+            bwd = !past && prev;
+        }
+        glob<int8_t>(S.side)[i] = past ? 1 : 0;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c0 = __popcll(__ballot(past)), c1 = __popcll(__ballot(fwd)), c2 = __popcll(__ballot(bwd));
+    if (lane == 0) {
+        m.cnt[0][wave] = c0;
+        m.cnt[1][wave] = c1;
+        m.cnt[2][wave] = c2;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        const int k = threadIdx.x;
+        const int c = m.cnt[k][0] + m.cnt[k][1] + m.cnt[k][2] + m.cnt[k][3];
+        if (c != 0) {
+            if (total) atomicAdd(total + k, c);
+            if (row) atomicAdd(row + k, c);
         }
     }
 }
@@ -1147,13 +1273,17 @@ __global__ __launch_bounds__(BT) void k_kick_stats(Launch L, int do_kick)
 // takes os_ib elements i of one star, all of them in every lane's registers, and its 256 lanes
 // share out the j: lane t takes j = t, t + 256, ..., so a j is read once per workgroup, straight
 // from memory, for os_ib pairs. Each lane's sums (at most n / 256 terms per element) are added
-// across the wave by a halving exchange and across the waves in order; the elements then take
-// their second kick and the workgroup stores its record of the step. The symmetric kernels need
+// across the wave by a halving exchange and across the waves in order. In a step the elements
+// then take their second kick and, at once, the next step's kick and drift into a set of their own
+// (others still read this step's), the workgroup stores its record of the step, and further
+// workgroups end the step before (its plane and counts). So a step is one launch: ten steps of
+// 2,048 elements take 76 us; with the drift and the counts as a kernel of their own between the
+// evaluations they took 132, and with every workgroup drifting all j itself, from three times the
+// loads, 90 (but 326 against 312 at 7,001, where this one takes 244). The symmetric kernels need
 // half the pairs, but also a sorted copy, reactions, a combine and the kick as kernels of their
 // own, and one 256 x 256 tile pair takes a wave about 5000 instructions one after the other:
-// 2,048 elements are 45 such units on 256 CUs. Ten steps of 2,048 elements: 539 us with the
-// symmetric kernel and its passes, 139 us with this one and k_advance; 7,001: 610 and 315; FP64,
-// 4,096: 602 and 293.
+// 2,048 elements are 45 such units on 256 CUs. With them ten steps of 2,048 took 539 us, of 7,001
+// 610, and in FP64 of 4,096 602 (now 231).
 // The law is taken in its near form for every pair (the far form gives the same bits).
 
 template <typename T>
@@ -1161,12 +1291,18 @@ struct OneSidedLaw;
 template <>
 struct OneSidedLaw<float> {
     LawF k;
-    __device__ __forceinline__ void load(Const<DevState> *st, int cls) { k = law_f(st, cls); }
+    __device__ __forceinline__ void load(Const<DevState> *st, Const<LawState> *ls, int cls)
+    {
+        k = law_f(st, ls, cls);
+    }
 };
 template <>
 struct OneSidedLaw<double> {
     LawD k;
-    __device__ __forceinline__ void load(Const<DevState> *st, int cls) { k = law_d(st, cls); }
+    __device__ __forceinline__ void load(Const<DevState> *st, Const<LawState> *ls, int cls)
+    {
+        k = law_d(st, ls, cls);
+    }
 };
 
 template <int LAW>
@@ -1228,44 +1364,94 @@ __device__ __forceinline__ void wave_reduce(T (&a)[IB][3], T (&out)[3], int lane
     }
 }
 
-template <typename T, int LAW>
-__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
+// A step's beginning for one element: v' = v + a dt/2, x' = x + v' dt. The same operations wherever
+// an element is worked out, so that every workgroup has the same x' of it.
+template <typename T>
+__device__ __forceinline__ void kick_drift(T h, T dt, T &x, T &v, T a)
+{
+    v = fma_t(h, a, v);
+    x = fma_t(dt, v, x);
+}
+
+// One of the three sets (x, y, z, half-step vx, vy, vz) that hold the elements as step k's force sees
+// them. Step k's workgroups read set k, leave set k + 1 and look back at set k - 1.
+template <typename T>
+__device__ __forceinline__ Glob<T> *step_set(SysRef S, int k)
+{
+    return glob<T>(S.alt) + (size_t)(k % 3) * 6 * S.nalloc;
+}
+
+// step 0: the forces at the current positions (nb_forces). step k >= 1: the k-th step of a call, from
+// the drift to the next step's; the `last` one leaves the state in the caller's arrays.
+template <typename T, int LAW, bool STEP>
+__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int last)
 {
     constexpr int IB = os_ib(sizeof(T) == 8);
     using V4 = typename Vec4<T>::type;
-    __shared__ T part[BT / 64][IB][3];
+    __shared__ union {
+        T part[BT / 64][IB][3];
+        FinishMem fin;
+    } sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int u = L.unit_base + blockIdx.x;
+    const bool odd = (step & 1) != 0;
+    if (STEP && (int)blockIdx.x >= L.total_units) {
+        // the end of the step before: 256 elements' side of the L1 plane
+        SysRef S = cst(L.sys)[find_sys(L, (int)blockIdx.x - L.total_units, true)];
+        const int local = (int)blockIdx.x - L.total_units - S.ounit_begin;
+        double v[7];
+        sum_records(S, odd ? 0 : S.rec_len, S.n_rec, v, sh.fin.lds);
+        if (tid == 0) plane_of(S, v, sh.fin.pl);
+        __syncthreads();
+        const int i = min(local * BT + tid, S.n - 1);
+        const size_t na = S.nalloc;
+        auto *A = step_set<const T>(S, step - 1);
+        classify(S, local * BT + tid, (T)A[i], (T)A[na + i], (T)A[2 * na + i], sh.fin, false, nullptr,
+                 log_row(S, cst(S.st)->step + step - 1) + 1);
+        return;
+    }
+    const int u = blockIdx.x;
     SysRef S = cst(L.sys)[find_sys(L, u, false)];
     const int local = u - S.unit_begin;
     const int n = S.n, n1 = S.n1;
     auto *st = cst(S.st);
-    auto *__restrict__ X = glob<const T>(S.x);
-    auto *__restrict__ Y = glob<const T>(S.y);
-    auto *__restrict__ Z = glob<const T>(S.z);
-    auto *__restrict__ VX = glob<const T>(do_kick ? S.vxs : S.vx);
-    auto *__restrict__ VY = glob<const T>(do_kick ? S.vys : S.vy);
-    auto *__restrict__ VZ = glob<const T>(do_kick ? S.vzs : S.vz);
+    const size_t na = S.nalloc;
+    auto *A = step_set<const T>(S, step);
+    auto *X = STEP ? A : glob<const T>(S.x), *Y = STEP ? A + na : glob<const T>(S.y),
+         *Z = STEP ? A + 2 * na : glob<const T>(S.z);
+    auto *VX = STEP ? A + 3 * na : glob<const T>(S.vx), *VY = STEP ? A + 4 * na : glob<const T>(S.vy),
+         *VZ = STEP ? A + 5 * na : glob<const T>(S.vz);
     // star 1's elements take the first ceil(n1 / IB) workgroups
     const int b1 = (n1 + IB - 1) / IB;
     const int istar = local >= b1 ? 1 : 0;
     const int i0 = istar ? n1 + (local - b1) * IB : local * IB;
     const int iend = istar ? n : n1;
     T xi[IB], yi[IB], zi[IB], acc[IB][3];
-    V4 vi[IB];
+    V4 vi[LAW != 0 ? IB : 1];
 #pragma unroll
     for (int k = 0; k < IB; ++k) {
         const int i = min(i0 + k, iend - 1);
         xi[k] = X[i];
         yi[k] = Y[i];
         zi[k] = Z[i];
-        vi[k] = V4{};
         if constexpr (LAW != 0) vi[k] = V4{VX[i], VY[i], VZ[i], 0};
         acc[k][0] = acc[k][1] = acc[k][2] = 0;
     }
+    // wave 0's lane k < IB finishes element i0 + k
+    const int i = i0 + lane;
+    const bool mine = wave == 0 && lane < IB && i < iend;
+    T ox = 0, oy = 0, oz = 0, ovx = 0, ovy = 0, ovz = 0;
+    if (STEP && mine) {
+        ox = X[i];
+        oy = Y[i];
+        oz = Z[i];
+        ovx = VX[i];
+        ovy = VY[i];
+        ovz = VZ[i];
+    }
+    auto *ls = !STEP || step == 1 ? &st->cur : &st->slot[odd ? 0 : 1];
     OneSidedLaw<T> Ka, Kb;
-    Ka.load(st, istar);
-    Kb.load(st, istar + 1);
+    Ka.load(st, ls, istar);
+    Kb.load(st, ls, istar + 1);
     // UN j of the lane are fetched while the previous ones are worked on
     constexpr int UN = sizeof(T) == 4 ? 4 : 2;
     T px[UN], py[UN], pz[UN];
@@ -1302,7 +1488,7 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
 #pragma unroll
             for (int k = 0; k < IB; ++k) {
                 const T dx = xj[q] - xi[k], dy = yj[q] - yi[k], dz = zj[q] - zi[k];
-                T s = one_sided_s<LAW>(dx, dy, dz, vj[q], vi[k], K);
+                T s = one_sided_s<LAW>(dx, dy, dz, vj[q], vi[LAW != 0 ? k : 0], K);
                 // the self pair: d = 0 makes its term 0 under the contact law; the overlap term
                 // of eqs. (4)-(6) is of order 1 / eps there
                 if constexpr (LAW != 0) s = j - i0 == k ? (T)0 : s;
@@ -1317,49 +1503,70 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int do_kick)
     constexpr int LPE = 64 / IB;  // lanes that hold one element's sums
     if (lane % LPE == 0) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) part[wave][lane / LPE][d] = sum[d];
+        for (int d = 0; d < 3; ++d) sh.part[wave][lane / LPE][d] = sum[d];
     }
     __syncthreads();
     if (wave != 0) return;
-    // lane k < IB finishes element i0 + k
-    const int i = i0 + lane;
-    const bool mine = lane < IB && i < iend;
     double v[7] = {0, 0, 0, 0, 0, 0, 0};
     if (mine) {
-        T t[3];
+        T a[3];
+        const T gm = gm_of<T>(st);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            t[d] = part[0][lane][d];
+            T t = sh.part[0][lane][d];
 #pragma unroll
-            for (int w = 1; w < BT / 64; ++w) t[d] += part[w][lane][d];
+            for (int w = 1; w < BT / 64; ++w) t += sh.part[w][lane][d];
+            a[d] = gm * t;
         }
-        const T gm = gm_of<T>(st);
-        const T ax = gm * t[0], ay = gm * t[1], az = gm * t[2];
-        glob<T>(S.ax)[i] = ax;
-        glob<T>(S.ay)[i] = ay;
-        glob<T>(S.az)[i] = az;
-        if (do_kick) {
-            const T h = h_of<T>(st);
-            auto *vx = glob<T>(S.vx), *vy = glob<T>(S.vy),
-              *vz = glob<T>(S.vz);
-            const T wx = vx[i] + h * ax, wy = vy[i] + h * ay, wz = vz[i] + h * az;
-            vx[i] = wx;
-            vy[i] = wy;
-            vz[i] = wz;
-            add_stats(v, X[i], Y[i], Z[i], wx, wy, wz, istar != 0);
+        if (!STEP || last) {
+            glob<T>(S.ax)[i] = a[0];
+            glob<T>(S.ay)[i] = a[1];
+            glob<T>(S.az)[i] = a[2];
+        }
+        if constexpr (STEP) {
+            const T h = h_of<T>(st), dt = dt_of<T>(st);
+            ovx = fma_t(h, a[0], ovx);
+            ovy = fma_t(h, a[1], ovy);
+            ovz = fma_t(h, a[2], ovz);
+            add_stats(v, ox, oy, oz, ovx, ovy, ovz, istar != 0);
+            if (last) {
+                glob<T>(S.x)[i] = ox;
+                glob<T>(S.y)[i] = oy;
+                glob<T>(S.z)[i] = oz;
+                glob<T>(S.vx)[i] = ovx;
+                glob<T>(S.vy)[i] = ovy;
+                glob<T>(S.vz)[i] = ovz;
+            } else {
+                kick_drift(h, dt, ox, ovx, a[0]);
+                kick_drift(h, dt, oy, ovy, a[1]);
+                kick_drift(h, dt, oz, ovz, a[2]);
+                auto *N = step_set<T>(S, step + 1) + i;
+                N[0] = ox;
+                N[na] = oy;
+                N[2 * na] = oz;
+                N[3 * na] = ovx;
+                N[4 * na] = ovy;
+                N[5 * na] = ovz;
+            }
         }
     }
-    if (!do_kick) return;
+    if constexpr (!STEP) return;
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
 #pragma unroll
         for (int w = IB / 2; w >= 1; w /= 2) v[k] += __shfl_xor(v[k], w, 64);
     }
     if (lane == 0) {
-        auto *r = glob<double>(S.rec) + (size_t)local * REC_STRIDE;
+        auto *r = glob<double>(S.rec) + (size_t)((odd ? S.rec_len : 0) + local) * REC_STRIDE;
 #pragma unroll
         for (int k = 0; k < 7; ++k) r[k] = v[k];
-        if (local == 0) begin_counts(S);
+        if (local == 0) {
+            DevState *w = S.st;
+            const int64_t done = w->step + step;
+            w->step_done = done;
+            clear_counts(S, done);
+            grow(w, step == 1 ? &w->cur : &w->slot[odd ? 0 : 1], &w->slot[odd ? 1 : 0]);
+        }
     }
 }
 
@@ -1401,11 +1608,11 @@ __device__ __forceinline__ double xbar_ror1(double v, int addr)
 
 __device__ __forceinline__ LawF law_of(Const<DevState> *st, int cls, float)
 {
-    return law_uniform(law_f(st, cls));
+    return law_uniform(law_f(st, &st->cur, cls));
 }
 __device__ __forceinline__ LawD law_of(Const<DevState> *st, int cls, double)
 {
-    return law_d(st, cls);
+    return law_d(st, &st->cur, cls);
 }
 
 template <int LAW, bool NEAR>
@@ -1554,8 +1761,8 @@ __device__ __forceinline__ void rows_unit(SysRef S, int grp, int I0, int c, Rows
         const int istar = row * TJ >= S.p1 ? 1 : 0;
         Ka[r] = law_of(st, istar, (T)0);
         Kb[r] = law_of(st, istar + 1, (T)0);
-        far2a = fmaxf(far2a, st->far2f[istar]);
-        far2b = fmaxf(far2b, st->far2f[istar + 1]);
+        far2a = fmaxf(far2a, st->cur.far2f[istar]);
+        far2b = fmaxf(far2b, st->cur.far2f[istar + 1]);
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -1694,72 +1901,6 @@ void k_force_rows(Launch L)
 
 // ------------------------------------------------------------------ between two evaluations
 
-// Star centres and L1 plane.
-struct Plane {
-    double com1[3], com2[3], e[3], xi_cut;
-    int ok;
-};
-
-// The system's records summed by one workgroup, in the same order wherever it is done.
-__device__ __forceinline__ void sum_records(SysRef S, int n_rec, double (&v)[7],
-                                            double (*lds)[BT / 64])
-{
-    for (int k = 0; k < 7; ++k) v[k] = 0.0;
-    for (int u = threadIdx.x; u < n_rec; u += BT) {
-        auto *r = glob<const double>(S.rec) + (size_t)u * REC_STRIDE;
-        for (int k = 0; k < 7; ++k) v[k] += r[k];
-    }
-    block_sum<7>(v, lds);
-}
-
-__device__ __forceinline__ void plane_of(SysRef S, const double (&v)[7], Plane &p)
-{
-    const int n1 = S.n1, n2 = S.n - S.n1;
-    for (int d = 0; d < 3; ++d) {
-        p.com1[d] = n1 > 0 ? v[d] / (double)n1 : 0.0;
-        p.com2[d] = n2 > 0 ? v[3 + d] / (double)n2 : 0.0;
-        p.e[d] = p.com2[d] - p.com1[d];
-    }
-    const double dist = sqrt(p.e[0] * p.e[0] + p.e[1] * p.e[1] + p.e[2] * p.e[2]);
-    p.ok = (n1 > 0 && n2 > 0 && dist > 0.0) ? 1 : 0;
-    for (int d = 0; d < 3; ++d) p.e[d] = p.ok ? p.e[d] / dist : 0.0;
-    p.xi_cut = glob<DevState>(S.st)->xi_l1 * dist;
-}
-
-// Records the plane and the non-finite count, and (optionally) applies the donor growth update
-// with the derived force constants. Called by one thread of a system.
-__device__ __forceinline__ void finish_step(SysRef S, const Plane &p, double nonfinite,
-                                            int do_growth)
-{
-    auto *st = glob<DevState>(S.st);
-    for (int d = 0; d < 3; ++d) {
-        st->com1[d] = p.com1[d];
-        st->com2[d] = p.com2[d];
-        st->e[d] = p.e[d];
-    }
-    st->xi_cut = p.xi_cut;
-    st->plane_ok = p.ok;
-    st->nonfinite = (int32_t)nonfinite;
-    if (do_growth && st->growth_on && !st->growth_stopped) {
-        const double R2 = st->R2_0 * st->D2 / st->D2_0;
-        if (R2 <= st->rL_a) {
-            st->D2 = st->D2 * (1.0 + st->growth_rate);
-            const double Ds[3] = {st->D1, 0.5 * (st->D1 + st->D2), st->D2};
-            for (int k = 0; k < 3; ++k) {
-                const double D = Ds[k];
-                st->c1d[k] = 11.0 / (D * D * D);
-                st->c2d[k] = 10.0 / (D * D);
-                st->c1f[k] = (float)st->c1d[k];
-                st->c2f[k] = (float)st->c2d[k];
-                st->far2f[k] = (float)(D * D * (1.0 + (double)FAR_MARGIN));
-                st->lD_f[k] = (float)D;
-            }
-        } else {
-            st->growth_stopped = 1;
-        }
-    }
-}
-
 // Systems above COM_FUSE_UNITS units: one workgroup each sums the records and finishes the step
 // (every workgroup of k_advance doing so would read n / 256 records n / 256 times).
 __global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int do_growth)
@@ -1769,7 +1910,7 @@ __global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int do_growth)
         SysRef S = cst(L.sys)[s];
         if (S.n_ounits <= COM_FUSE_UNITS) continue;
         double v[7];
-        sum_records(S, S.n_ounits, v, lds);
+        sum_records(S, 0, S.n_ounits, v, lds);
         if (threadIdx.x == 0) {
             Plane p;
             plane_of(S, v, p);
@@ -1783,21 +1924,21 @@ __global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int do_growth)
 // kick wrote the records (ADV_INIT: only records the sides at creation) -- star centres, L1
 // plane, growth, and the donor elements' side of the plane with the crossings since the last
 // step. `kick`: begins the next step, v += a dt/2, x += v dt. One kernel of a step in place of
-// four: each had a few microseconds of launch and drain, most of a small system's step
-// (65,536 elements: 784 -> 762 us a step). Up to COM_FUSE_UNITS units every workgroup sums the system's
-// records itself, in one order, and its first one records the result; the counts are whole
-// numbers added atomically to what begin_counts cleared, so their order does not matter.
+// four: each had a few microseconds of launch and drain (65,536 elements: 784 -> 762 us a step).
+// Up to COM_FUSE_UNITS units every workgroup sums the system's records itself, in one order, and
+// its first one records the result. One-sided systems come here at the beginning of a call (their
+// kick and drift go to the first step's set) and at its end, after n_steps.
 template <typename T>
-__global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
+__global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick, int n_steps)
 {
-    __shared__ double lds[7][BT / 64];
-    __shared__ Plane pl;
-    __shared__ int cnt[3][BT / 64];
-    for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
+    __shared__ FinishMem m;
+    for (int u = L.ounit_base + blockIdx.x; u < L.total_ounits; u += gridDim.x) {
         SysRef S = cst(L.sys)[find_sys(L, u, true)];
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
         auto *x = glob<T>(S.x), *y = glob<T>(S.y), *z = glob<T>(S.z);
+        const bool call_end = S.one_sided && finish != ADV_INIT;
+        const bool odd = call_end && (n_steps & 1) != 0;
         T px = 0, py = 0, pz = 0;
         if (i < S.n) {
             px = x[i];
@@ -1805,78 +1946,51 @@ __global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick)
             pz = z[i];
         }
         if (finish) {
-            auto *st = glob<DevState>(S.st);
+            DevState *st = S.st;
             if (S.n_ounits <= COM_FUSE_UNITS) {
                 double v[7];
-                sum_records(S, finish == ADV_INIT ? S.n_ounits : S.n_rec, v, lds);
+                sum_records(S, odd ? S.rec_len : 0, finish == ADV_INIT ? S.n_ounits : S.n_rec, v,
+                            m.lds);
                 if (threadIdx.x == 0) {
-                    plane_of(S, v, pl);
-                    if (local == 0) finish_step(S, pl, v[6], finish != ADV_INIT);
+                    plane_of(S, v, m.pl);
+                    if (local == 0) {
+                        finish_step(S, m.pl, v[6], finish != ADV_INIT && !call_end);
+                        if (call_end) {
+                            st->cur = st->slot[odd ? 1 : 0];
+                            st->step = st->step_done;
+                        }
+                    }
                 }
             } else if (threadIdx.x == 0) {
                 for (int d = 0; d < 3; ++d) {
-                    pl.com1[d] = st->com1[d];
-                    pl.e[d] = st->e[d];
+                    m.pl.com1[d] = st->com1[d];
+                    m.pl.e[d] = st->e[d];
                 }
-                pl.xi_cut = st->xi_cut;
-                pl.ok = st->plane_ok;
+                m.pl.xi_cut = st->xi_cut;
+                m.pl.ok = st->plane_ok;
             }
             __syncthreads();
-            bool past = false, fwd = false, bwd = false;
-            if (i < S.n && i >= S.n1) {
-                const double xi = ((double)px - pl.com1[0]) * pl.e[0] +
-                                  ((double)py - pl.com1[1]) * pl.e[1] +
-                                  ((double)pz - pl.com1[2]) * pl.e[2];
-                past = pl.ok && xi < pl.xi_cut;
-                if (finish != ADV_INIT) {
-                    const bool prev = glob<int8_t>(S.side)[i] != 0;
-                    fwd = past && !prev;
-                    bwd = !past && prev;
-                }
-                glob<int8_t>(S.side)[i] = past ? 1 : 0;
-            }
-            const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-            const int c0 = __popcll(__ballot(past)), c1 = __popcll(__ballot(fwd)),
-                      c2 = __popcll(__ballot(bwd));
-            if (lane == 0) {
-                cnt[0][wave] = c0;
-                cnt[1][wave] = c1;
-                cnt[2][wave] = c2;
-            }
-            __syncthreads();
-            if (threadIdx.x < 3) {
-                const int k = threadIdx.x;
-                const int c = cnt[k][0] + cnt[k][1] + cnt[k][2] + cnt[k][3];
-                if (c != 0) {
-                    DevState *w = S.st;
-                    atomicAdd(k == 0 ? &w->n_past : (k == 1 ? &w->fwd : &w->bwd), c);
-                    if (finish != ADV_INIT)
-                        atomicAdd(S.l1_log + 4 * (size_t)(st->step % L1_LOG_CAP) + 1 + k, c);
-                }
-            }
+            classify(S, i, px, py, pz, m, finish == ADV_INIT, &st->n_past,
+                     finish == ADV_INIT ? nullptr
+                                        : log_row(S, call_end ? st->step_done : st->step) + 1);
         }
         if (kick && i < S.n) {
-            const T h = h_of<T>(glob<const DevState>(S.st)), dt = dt_of<T>(glob<const DevState>(S.st));
-            auto *vx = glob<T>(S.vx), *vy = glob<T>(S.vy),
-              *vz = glob<T>(S.vz);
-            const T nvx = vx[i] + h * glob<const T>(S.ax)[i];
-            const T nvy = vy[i] + h * glob<const T>(S.ay)[i];
-            const T nvz = vz[i] + h * glob<const T>(S.az)[i];
-            vx[i] = nvx;
-            vy[i] = nvy;
-            vz[i] = nvz;
-            x[i] = px + dt * nvx;
-            y[i] = py + dt * nvy;
-            z[i] = pz + dt * nvz;
-            if (S.one_sided && S.vxs) {
-                // the one-sided force kernel kicks its own elements while others read the
-                // half-step velocities of eqs. (4)-(6)
-                glob<T>(S.vxs)[i] = nvx;
-                glob<T>(S.vys)[i] = nvy;
-                glob<T>(S.vzs)[i] = nvz;
-            }
+            auto *st = glob<const DevState>(S.st);
+            const T h = h_of<T>(st), dt = dt_of<T>(st);
+            T vx = glob<T>(S.vx)[i], vy = glob<T>(S.vy)[i], vz = glob<T>(S.vz)[i];
+            kick_drift(h, dt, px, vx, (T)glob<const T>(S.ax)[i]);
+            kick_drift(h, dt, py, vy, (T)glob<const T>(S.ay)[i]);
+            kick_drift(h, dt, pz, vz, (T)glob<const T>(S.az)[i]);
+            const size_t na = S.nalloc;
+            auto *A = step_set<T>(S, 1);
+            (S.one_sided ? A : x)[i] = px;
+            (S.one_sided ? A + na : y)[i] = py;
+            (S.one_sided ? A + 2 * na : z)[i] = pz;
+            (S.one_sided ? A + 3 * na : glob<T>(S.vx))[i] = vx;
+            (S.one_sided ? A + 4 * na : glob<T>(S.vy))[i] = vy;
+            (S.one_sided ? A + 5 * na : glob<T>(S.vz))[i] = vz;
         }
-        __syncthreads();  // pl and cnt are rewritten by the next unit
+        __syncthreads();  // m is rewritten by the next unit
     }
 }
 
@@ -1995,10 +2109,11 @@ __global__ __launch_bounds__(BT) void k_pe(Launch L)
         sh[tid][2] = ZS[t * TJ + tid];
         __syncthreads();
         const int cls = pair_class(istar, t * TJ >= S.p1 ? 1 : 0);
-        const double D = cls == 0 ? st->D1 : (cls == 2 ? st->D2 : 0.5 * (st->D1 + st->D2));
+        const double D =
+            cls == 0 ? st->D1 : (cls == 2 ? st->cur.D2 : 0.5 * (st->D1 + st->cur.D2));
         const int j1 = min(64, tile_count(S, t) - 64 * wave);
         const double(*sj)[4] = sh + 64 * wave;
-        if (far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi, st->far2f[cls])) {
+        if (far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi, st->cur.far2f[cls])) {
             for (int j = 0; j < j1; ++j) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -2276,7 +2391,8 @@ hipError_t launch_gather(const Launch &L, int mode, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks, hipStream_t s)
+hipError_t launch_forces(const Launch &L, int mode, int step, int last, int max_blocks,
+                         hipStream_t s)
 {
     if (L.total_units == 0) return hipSuccess;
     if (L.law != 0 && L.law != 1) return hipErrorInvalidValue;
@@ -2291,15 +2407,21 @@ hipError_t launch_forces(const Launch &L, int mode, int do_kick, int max_blocks,
         if (end <= begin) continue;
         R.unit_base = begin;
         R.total_units = end;
-        const dim3 g = b == 0 ? dim3(end - begin) : grid(end - begin), blk(BT);
+        const dim3 g = grid(end - begin), blk(BT);
         if (b == 0) {
-            // one-sided: one workgroup per unit whatever the launch shape
+            // one workgroup per unit whatever the launch shape, and from a call's second step on
+            // one per 256 elements for the end of the step before
             if (mode == 0) return hipErrorInvalidValue;
-            switch ((mode == 2 ? 2 : 0) + L.law) {
-            case 0: hipLaunchKernelGGL((k_force_one_sided<float, 0>), g, blk, 0, s, R, do_kick); break;
-            case 1: hipLaunchKernelGGL((k_force_one_sided<float, 1>), g, blk, 0, s, R, do_kick); break;
-            case 2: hipLaunchKernelGGL((k_force_one_sided<double, 0>), g, blk, 0, s, R, do_kick); break;
-            default: hipLaunchKernelGGL((k_force_one_sided<double, 1>), g, blk, 0, s, R, do_kick); break;
+            const dim3 gs(end + (step > 1 ? L.ounit_base : 0));
+            switch ((mode == 2 ? 4 : 0) + L.law * 2 + (step > 0 ? 1 : 0)) {
+            case 0: hipLaunchKernelGGL((k_force_one_sided<float, 0, false>), gs, blk, 0, s, R, 0, 0); break;
+            case 1: hipLaunchKernelGGL((k_force_one_sided<float, 0, true>), gs, blk, 0, s, R, step, last); break;
+            case 2: hipLaunchKernelGGL((k_force_one_sided<float, 1, false>), gs, blk, 0, s, R, 0, 0); break;
+            case 3: hipLaunchKernelGGL((k_force_one_sided<float, 1, true>), gs, blk, 0, s, R, step, last); break;
+            case 4: hipLaunchKernelGGL((k_force_one_sided<double, 0, false>), gs, blk, 0, s, R, 0, 0); break;
+            case 5: hipLaunchKernelGGL((k_force_one_sided<double, 0, true>), gs, blk, 0, s, R, step, last); break;
+            case 6: hipLaunchKernelGGL((k_force_one_sided<double, 1, false>), gs, blk, 0, s, R, 0, 0); break;
+            default: hipLaunchKernelGGL((k_force_one_sided<double, 1, true>), gs, blk, 0, s, R, step, last); break;
             }
         } else if (mode == 0) {
             if (L.law != 0 || b != 1) return hipErrorInvalidValue;  // no eqs. (4)-(6), no bands
@@ -2370,14 +2492,17 @@ hipError_t launch_finalize_step(const Launch &L, int do_growth, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, hipStream_t s)
+hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, int n_steps, hipStream_t s)
 {
-    if (L.total_ounits == 0) return hipSuccess;
-    const dim3 g(grid_for(L.total_ounits)), b(BT);
+    // between two steps of a call only the systems outside the one-sided kernel pass here
+    Launch R = L;
+    if (!(finish && kick)) R.ounit_base = 0;
+    if (R.total_ounits <= R.ounit_base) return hipSuccess;
+    const dim3 g(grid_for(R.total_ounits - R.ounit_base)), b(BT);
     if (mode == 2) {
-        hipLaunchKernelGGL(k_advance<double>, g, b, 0, s, L, finish, kick);
+        hipLaunchKernelGGL(k_advance<double>, g, b, 0, s, R, finish, kick, n_steps);
     } else {
-        hipLaunchKernelGGL(k_advance<float>, g, b, 0, s, L, finish, kick);
+        hipLaunchKernelGGL(k_advance<float>, g, b, 0, s, R, finish, kick, n_steps);
     }
     return hipGetLastError();
 }

@@ -183,9 +183,11 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
 }
 
 struct Layout {
-    size_t state, desc, diag, red, rec, sort, pe, log, xs, ys, zs, vxs, vys, vzs, perm, tbox, units, react,
+    size_t state, desc, diag, red, rec, alt, sort, pe, log, xs, ys, zs, vxs, vys, vzs, perm, tbox, units, react,
         part, total;
 };
+
+int rec_len(const TileCfg &c) { return std::max(std::max(c.n_ounits, c.n_rec), 1); }
 
 // Whether the force kernel leaves partial sums for a combine.
 bool needs_partials(const TileCfg &c) { return !c.one_sided && (c.nsplit > 1 || c.sym); }
@@ -204,7 +206,8 @@ Layout layout_for(int mode, int law, const TileCfg &c)
     L.desc = take(sizeof(SysDesc));
     L.diag = take(sizeof(DiagOut));
     L.red = take((size_t)std::max(c.n_ounits, 1) * RED_STRIDE * sizeof(double));
-    L.rec = take((size_t)std::max(std::max(c.n_ounits, c.n_rec), 1) * REC_STRIDE * sizeof(double));
+    L.rec = take((size_t)rec_len(c) * (c.one_sided ? 2 : 1) * REC_STRIDE * sizeof(double));
+    L.alt = take(c.one_sided ? (size_t)18 * (size_t)c.nalloc * elem : 0);
     L.sort = take(sort_work_bytes((int64_t)c.n_sort));
     L.pe = take((size_t)c.n_peunits * sizeof(double));
     L.log = take((size_t)L1_LOG_CAP * 4 * sizeof(int32_t));
@@ -340,7 +343,7 @@ int hip_status(hipError_t e) { return e == hipSuccess ? NB_OK : NB_E_HIP; }
         if (e_ != hipSuccess) return NB_E_HIP; \
     } while (0)
 
-int launch_force_timed(const Launch &L, int mode, int do_kick, hipStream_t st, bool need_combine,
+int launch_force_timed(const Launch &L, int mode, int step, int last, hipStream_t st, bool need_combine,
                        bool allow_timing = true)
 {
     NB_TRY(launch_gather(L, mode, st));
@@ -359,7 +362,7 @@ int launch_force_timed(const Launch &L, int mode, int do_kick, hipStream_t st, b
             return NB_E_HIP;
         }
     }
-    const hipError_t e = launch_forces(L, mode, do_kick, g_force_grid.load(), st);
+    const hipError_t e = launch_forces(L, mode, step, last, g_force_grid.load(), st);
     if (timed) {
         if (e != hipSuccess || hipEventRecord(b, st) != hipSuccess) {
             (void)hipEventDestroy(a);
@@ -374,18 +377,20 @@ int launch_force_timed(const Launch &L, int mode, int do_kick, hipStream_t st, b
     return NB_OK;
 }
 
-// k_advance ends one step and begins the next, so a call of n_steps runs it n_steps + 1 times.
+// k_advance ends one step and begins the next, so a call of n_steps runs it n_steps + 1 times; for
+// one-sided systems the force kernel does both between the steps, and only the call's beginning and
+// end are left to it.
 int run_steps(const Launch &L, int mode, int n_steps, bool need_combine, hipStream_t st,
               bool allow_timing = true)
 {
-    for (int k = 0; k < n_steps; ++k) {
-        NB_TRY(launch_advance(L, mode, k > 0 ? 1 : 0, 1, st));
-        int rc = launch_force_timed(L, mode, 1, st, need_combine, allow_timing);
+    for (int k = 1; k <= n_steps; ++k) {
+        NB_TRY(launch_advance(L, mode, k > 1 ? 1 : 0, 1, 0, st));
+        int rc = launch_force_timed(L, mode, k, k == n_steps ? 1 : 0, st, need_combine, allow_timing);
         if (rc != NB_OK) return rc;
         NB_TRY(launch_kick_stats(L, mode, 1, st));
         NB_TRY(launch_finalize_step(L, 1, st));
     }
-    if (n_steps > 0) NB_TRY(launch_advance(L, mode, 1, 0, st));
+    if (n_steps > 0) NB_TRY(launch_advance(L, mode, 1, 0, n_steps, st));
     return NB_OK;
 }
 
@@ -541,6 +546,8 @@ void fill_desc(SysDesc &d, const nb_params *p, const nb_buffers *b, const TileCf
     d.red = reinterpret_cast<double *>(base + lay.red);
     d.rec = reinterpret_cast<double *>(base + lay.rec);
     d.n_rec = cfg.n_rec;
+    d.rec_len = rec_len(cfg);
+    d.alt = cfg.one_sided ? base + lay.alt : nullptr;
     d.one_sided = cfg.one_sided;
     d.pe_part = reinterpret_cast<double *>(base + lay.pe);
     d.l1_log = reinterpret_cast<int32_t *>(base + lay.log);
@@ -563,7 +570,7 @@ void fill_state(DevState &init, const nb_params *p)
 {
     std::memset(&init, 0, sizeof init);
     init.D1 = p->D1;
-    init.D2 = p->D2;
+    init.cur.D2 = p->D2;
     init.D2_0 = p->D2;
     init.R2_0 = p->R2_0;
     init.rL_a = roche_lobe_ratio(p->q) * p->a;
@@ -574,11 +581,11 @@ void fill_state(DevState &init, const nb_params *p)
     init.xi_l1 = l1_from_accretor(p->q);
     const double Ds[3] = {p->D1, 0.5 * (p->D1 + p->D2), p->D2};
     for (int k = 0; k < 3; ++k) {
-        init.c1d[k] = 11.0 / (Ds[k] * Ds[k] * Ds[k]);
-        init.c2d[k] = 10.0 / (Ds[k] * Ds[k]);
-        init.c1f[k] = (float)init.c1d[k];
-        init.c2f[k] = (float)init.c2d[k];
-        init.far2f[k] = (float)(Ds[k] * Ds[k] * (1.0 + (double)FAR_MARGIN));
+        init.cur.c1d[k] = 11.0 / (Ds[k] * Ds[k] * Ds[k]);
+        init.cur.c2d[k] = 10.0 / (Ds[k] * Ds[k]);
+        init.cur.c1f[k] = (float)init.cur.c1d[k];
+        init.cur.c2f[k] = (float)init.cur.c2d[k];
+        init.cur.far2f[k] = (float)(Ds[k] * Ds[k] * (1.0 + (double)FAR_MARGIN));
     }
     init.gm_d = p->G * p->m;
     init.h_d = 0.5 * p->dt;
@@ -594,7 +601,7 @@ void fill_state(DevState &init, const nb_params *p)
         init.lgc_d = p->gamma * PI / (12.0 * p->G * p->m * p->m);
         init.lgcb_d = p->beta * init.lgc_d;
     }
-    for (int k = 0; k < 3; ++k) init.lD_f[k] = (float)Ds[k];
+    for (int k = 0; k < 3; ++k) init.cur.lD_f[k] = (float)Ds[k];
     init.leps_f = (float)p->eps;
     init.lgc_f = (float)init.lgc_d;
     init.lgcb_f = (float)init.lgcb_d;
@@ -762,9 +769,9 @@ int nb_create(const nb_params *p, const nb_buffers *b, void *stream, nb_system *
         Launch L = single_launch(s);
         if (launch_kick_stats(L, p->mode, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (launch_finalize_step(L, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
-        if (launch_advance(L, p->mode, ADV_INIT, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
+        if (launch_advance(L, p->mode, ADV_INIT, 0, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (launch_gather(L, p->mode, st) != hipSuccess) { rc = NB_E_HIP; break; }
-        if (launch_forces(L, p->mode, 0, g_force_grid.load(), st) != hipSuccess) { rc = NB_E_HIP; break; }
+        if (launch_forces(L, p->mode, 0, 0, g_force_grid.load(), st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (needs_partials(cfg) && launch_combine(L, p->mode, st) != hipSuccess) {
             rc = NB_E_HIP;
             break;
@@ -782,7 +789,7 @@ int nb_create(const nb_params *p, const nb_buffers *b, void *stream, nb_system *
 int nb_forces(nb_system *s, void *stream)
 {
     if (!s || !on_own_device(s)) return NB_E_INVAL;
-    return launch_force_timed(single_launch(s), s->p.mode, 0, static_cast<hipStream_t>(stream),
+    return launch_force_timed(single_launch(s), s->p.mode, 0, 0, static_cast<hipStream_t>(stream),
                               needs_partials(s->cfg));
 }
 
@@ -978,13 +985,13 @@ int nb_diagnostics(nb_system *s, int32_t with_pe, nb_diag *out, void *stream)
     out->KE = d.v[9];
     out->PE = with_pe ? d.v[10] : 0.0;
     out->E = out->KE + out->PE;
-    out->D2 = ds.D2;
-    out->R2 = ds.R2_0 * ds.D2 / ds.D2_0;
+    out->D2 = ds.cur.D2;
+    out->R2 = ds.R2_0 * ds.cur.D2 / ds.D2_0;
     out->step = ds.step;
     out->n_past_L1 = ds.n_past;
     out->cross_fwd = ds.fwd;
     out->cross_bwd = ds.bwd;
-    out->growth_stopped = ds.growth_stopped;
+    out->growth_stopped = ds.cur.growth_stopped;
     out->nonfinite = ds.nonfinite;
     return ds.nonfinite ? NB_E_NONFINITE : NB_OK;
 }
