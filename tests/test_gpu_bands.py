@@ -207,3 +207,25 @@ def test_chunks_that_cut_a_band(n, q, ch, mode, law, tol):
         finally:
             nb.nb_tile_override(n, n, M, 0, 1, law=W)
         assert force_error(a, ref) <= tol
+
+
+@pytest.mark.parametrize("n,q,ch", [(300, 0.5, 2), (520, 0.9, 3), (9011, 0.4, 1), (9011, 1.0, 36),
+                                    (17003, 0.1, 1)])
+def test_fp64_combine_runs(n, q, ch):
+    """Runs of the FP64 combine: fewer terms than runs, runs that end among the chunk partials, and
+    runs of more than eight reactions with a remainder."""
+    nb = require_gpu()
+    ic = synth.make_binary(n, q, seed=n)
+    tiles = -(-ic.n1 // 256) - (-(n - ic.n1) // 256)
+    rows = sample_rows(n, ic.n1, 64)
+    print_case("FP64 combine runs", n, q, ch)
+    nb.nb_tile_override(n, n, nb.MODES["fp64"], -(-tiles // ch), 1)
+    try:
+        s = nb.System.from_ic(ic, mode="fp64")
+        a = s.accelerations()
+        s.close()
+    finally:
+        nb.nb_tile_override(n, n, nb.MODES["fp64"], 0, 1)
+    p, _ = ic.f32_as_f64()
+    ref = oracle.accel(p, ic.n1, ic.G, ic.m, ic.D1, ic.D2, rows=rows)
+    assert force_error(a[rows], ref) <= 1e-12
