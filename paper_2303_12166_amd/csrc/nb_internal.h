@@ -25,8 +25,9 @@ constexpr int RED_STRIDE = 32;   // doubles per O(N)-unit partial record of the 
 constexpr int REC_STRIDE = 8;    // doubles per record of a step (position sums, non-finite count)
 constexpr int COM_FUSE_UNITS = 256;  // largest system (in units of 256 elements) whose records
                                      // every workgroup of k_advance sums for itself
-// i elements per workgroup of the one-sided force kernel
-constexpr int os_ib(bool fp64) { return fp64 ? 4 : 8; }
+// Most i elements per workgroup of the one-sided force kernel. Under eqs. (4)-(6) eight would need 144
+// registers (velocities are held too): three workgroups on a CU instead of four.
+constexpr int os_ib(bool fp64, int law) { return fp64 ? 4 : (law == 0 ? 8 : 7); }
 constexpr int KERNEL_CLASSES = 4;    // force kernels of a launch: one-sided, bands of 1, 2, 4 rows
 constexpr int ADV_INIT = 2;      // k_advance: record the sides at creation
 constexpr int RED_DIAG = 16;     // record slots [16, 32): diagnostics sums
@@ -116,7 +117,7 @@ struct SysDesc {
     int32_t n_units, n_ounits;  // force units (n_iblocks * nsplit) and O(N) units (ceil(n / BT))
     int32_t n_rec, one_sided;   // records of a step; 1 for the one-sided force kernel, whose units
                                 // are its workgroups
-    int32_t rec_len, pad3;      // at least n_rec and n_ounits (at creation there are n_ounits records)
+    int32_t rec_len, ib;        // at least n_rec and n_ounits (at creation there are n_ounits records)
     int32_t unit_begin, ounit_begin;  // prefix offsets in the launch's segment table
     int32_t n_peunits, pe_ch;         // potential energy: units (tile row, chunk), tiles per chunk
     int32_t npad, p1, nalloc, ntiles;  // sorted layout (see above)

@@ -1299,20 +1299,22 @@ __device__ __forceinline__ void classify(SysRef S, int i, T px, T py, T pz, Fini
 //
 // Small systems (FP32 Kahan and FP64 modes; see the runtime's one_sided rule): every ordered pair, in
 // element order, with nothing between the drift and the second kick but this kernel. A workgroup
-// takes os_ib elements i of one star, all of them in every lane's registers, and its 256 lanes
-// share out the j: lane t takes j = t, t + 256, ..., so a j is read once per workgroup, straight
-// from memory, for os_ib pairs. Each lane's sums (at most n / 256 terms per element) are added
-// across the wave by a halving exchange and across the waves in order. In a step the elements
-// then take their second kick and, at once, the next step's kick and drift into a set of their own
-// (others still read this step's), the workgroup stores its record of the step, and further
-// workgroups end the step before (its plane and counts). So a step is one launch: ten steps of
-// 2,048 elements take 76 us; with the drift and the counts as a kernel of their own between the
-// evaluations they took 132, and with every workgroup drifting all j itself, from three times the
-// loads, 90 (but 326 against 312 at 7,001, where this one takes 244). The symmetric kernels need
-// half the pairs, but also a sorted copy, reactions, a combine and the kick as kernels of their
-// own, and one 256 x 256 tile pair takes a wave about 5000 instructions one after the other:
-// 2,048 elements are 45 such units on 256 CUs. With them ten steps of 2,048 took 539 us, of 7,001
-// 610, and in FP64 of 4,096 602 (now 231).
+// takes the system's ib elements i of one star (the runtime's one_sided_ib rule), all of them in
+// every lane's registers, and its 256 lanes share out the j: lane t takes j = t, t + 256, ..., so a j
+// is read once per workgroup, straight from memory, for ib pairs. Each lane's sums (at most n / 256
+// terms per element) are added across the wave by a halving exchange and across the waves in
+// order: the same order for every ib. In a step the elements then take their second kick and, at
+// once, the next step's kick and drift into a set of their own (others still read this step's), the
+// workgroup stores its record of the step, and further workgroups end the step before (its plane
+// and counts). So a step is one launch: ten steps of 2,048 elements take 70 us; with the drift and
+// the counts as a kernel of their own between the evaluations they took 132, and with every
+// workgroup drifting all j itself, from three times the loads, 90 (but 326 against 312 at 7,001,
+// where this one takes 221). The symmetric kernels need half the pairs, but also a sorted copy,
+// reactions, a combine and the kick as kernels of their own, and one 256 x 256 tile pair takes a
+// wave about 5000 instructions one after the other: 2,048 elements are 45 such units on 256 CUs.
+// What bounds it: at 2,048 elements a launch and one workgroup's chain of loads, pairs and sums
+// (7 us a step); at 7,001 FP32 issue, at 2,980 pairs a nanosecond. Taking all ib pairs through each
+// operation together instead of one after the other changed nothing, eqs. (4)-(6) 5 to 25 % slower.
 // The law is taken in its near form for every pair (the far form gives the same bits).
 
 template <typename T>
@@ -1323,6 +1325,8 @@ struct OneSidedLaw<float> {
     __device__ __forceinline__ void load(Const<DevState> *st, Const<LawState> *ls, int cls)
     {
         k = law_f(st, ls, cls);
+        // in vector registers: a choice between two of them takes one instruction
+        asm("" : "+v"(k.c1), "+v"(k.nc2));
     }
 };
 template <>
@@ -1338,7 +1342,9 @@ template <int LAW>
 __device__ __forceinline__ float one_sided_s(float dx, float dy, float dz, const float4 &vj,
                                              const float4 &vi, const LawF &K)
 {
-    const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, 1.0e-24f)));
+    float eps;  // in a vector register: a literal halves the issue rate
+    asm("v_mov_b32 %0, 0x179abe15" : "=v"(eps));  // 1e-24
+    const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps)));
     return pair_s<LAW, true>(r2, dx, dy, dz, vj, vi, K);
 }
 
@@ -1364,15 +1370,30 @@ struct Vec4<double> {
     using type = double4;
 };
 
-// Sums NV values per lane over the wave, NV a power of two times 3 with the element index first:
-// halves the elements a lane holds at each of the first steps. On return lane l holds element
-// l / (64 / IB)'s three sums, summed over all lanes.
+template <int V>
+struct Int {
+    static constexpr int value = V;
+};
+
+// The power of two that holds IB.
+constexpr int pow2_of(int ib) { return ib <= 1 ? 1 : (ib <= 2 ? 2 : (ib <= 4 ? 4 : 8)); }
+
+// Sums IB elements' three values per lane over the wave: halves the elements that a lane holds at
+// each of the first steps (elements beyond IB are zeros). With P = pow2_of(IB), on return lane l holds
+// element l / (64 / P)'s three sums, summed over all lanes, in the same order for every IB.
 template <typename T, int IB>
-__device__ __forceinline__ void wave_reduce(T (&a)[IB][3], T (&out)[3], int lane)
+__device__ __forceinline__ void wave_reduce(const T (&in)[IB][3], T (&out)[3], int lane)
 {
+    constexpr int P = pow2_of(IB);
+    T a[P][3];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) a[k][d] = k < IB ? in[k < IB ? k : 0][d] : (T)0;
+    }
     int width = 32;
 #pragma unroll
-    for (int half = IB / 2; half >= 1; half /= 2) {
+    for (int half = P / 2; half >= 1; half /= 2) {
         const bool upper = (lane & width) != 0;
 #pragma unroll
         for (int k = 0; k < half; ++k) {
@@ -1410,37 +1431,21 @@ __device__ __forceinline__ Glob<T> *step_set(SysRef S, int k)
     return glob<T>(S.alt) + (size_t)(k % 3) * 6 * S.nalloc;
 }
 
+// Workgroup `local` of a system: its IB elements i.
+template <typename T>
+__device__ __forceinline__ T at_byte(Glob<const T> *p, uint32_t offset)
+{
+    return *reinterpret_cast<Glob<const T> *>(reinterpret_cast<Glob<const char> *>(p) + offset);
+}
+
 // step 0: the forces at the current positions (nb_forces). step k >= 1: the k-th step of a call, from
 // the drift to the next step's; the `last` one leaves the state in the caller's arrays.
-template <typename T, int LAW, bool STEP>
-__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int last)
+template <typename T, int LAW, bool STEP, int IB>
+__device__ __forceinline__ void one_sided_unit(SysRef S, int local, int step, int last, T (*part)[os_ib(sizeof(T) == 8, LAW)][3])
 {
-    constexpr int IB = os_ib(sizeof(T) == 8);
     using V4 = typename Vec4<T>::type;
-    __shared__ union {
-        T part[BT / 64][IB][3];
-        FinishMem fin;
-    } sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool odd = (step & 1) != 0;
-    if (STEP && (int)blockIdx.x >= L.total_units) {
-        // the end of the step before: 256 elements' side of the L1 plane
-        SysRef S = cst(L.sys)[find_sys(L, (int)blockIdx.x - L.total_units, true)];
-        const int local = (int)blockIdx.x - L.total_units - S.ounit_begin;
-        double v[7];
-        sum_records(S, odd ? 0 : S.rec_len, S.n_rec, v, sh.fin.lds);
-        if (tid == 0) plane_of(S, v, sh.fin.pl);
-        __syncthreads();
-        const int i = min(local * BT + tid, S.n - 1);
-        const size_t na = S.nalloc;
-        auto *A = step_set<const T>(S, step - 1);
-        classify(S, local * BT + tid, (T)A[i], (T)A[na + i], (T)A[2 * na + i], sh.fin, false, nullptr,
-                 log_row(S, cst(S.st)->step + step - 1) + 1);
-        return;
-    }
-    const int u = blockIdx.x;
-    SysRef S = cst(L.sys)[find_sys(L, u, false)];
-    const int local = u - S.unit_begin;
     const int n = S.n, n1 = S.n1;
     auto *st = cst(S.st);
     const size_t na = S.nalloc;
@@ -1482,18 +1487,19 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
     Ka.load(st, ls, istar);
     Kb.load(st, ls, istar + 1);
     // UN j of the lane are fetched while the previous ones are worked on
-    constexpr int UN = sizeof(T) == 4 ? 4 : 2;
+    constexpr int UN = sizeof(T) == 4 ? (LAW == 0 ? 4 : (IB <= 6 ? 2 : 1)) : (LAW == 0 ? 2 : 1);
     T px[UN], py[UN], pz[UN];
     V4 pv[UN];
     auto fetch = [&](int j0) {
 #pragma unroll
         for (int q = 0; q < UN; ++q) {
-            const int j = min(j0 + q * BT + tid, n - 1);
-            px[q] = X[j];
-            py[q] = Y[j];
-            pz[q] = Z[j];
+            // 32-bit offsets from uniform bases: one address for the lane's loads of a j
+            const uint32_t at = (uint32_t)min(j0 + q * BT + tid, n - 1) * (uint32_t)sizeof(T);
+            px[q] = at_byte(X, at);
+            py[q] = at_byte(Y, at);
+            pz[q] = at_byte(Z, at);
             pv[q] = V4{};
-            if constexpr (LAW != 0) pv[q] = V4{VX[j], VY[j], VZ[j], 0};
+            if constexpr (LAW != 0) pv[q] = V4{at_byte(VX, at), at_byte(VY, at), at_byte(VZ, at), 0};
         }
     };
     fetch(0);
@@ -1529,10 +1535,10 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
     }
     T sum[3];
     wave_reduce<T, IB>(acc, sum, lane);
-    constexpr int LPE = 64 / IB;  // lanes that hold one element's sums
-    if (lane % LPE == 0) {
+    constexpr int LPE = 64 / pow2_of(IB);  // lanes that hold one element's sums
+    if (lane % LPE == 0 && lane / LPE < IB) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) sh.part[wave][lane / LPE][d] = sum[d];
+        for (int d = 0; d < 3; ++d) part[wave][lane / LPE][d] = sum[d];
     }
     __syncthreads();
     if (wave != 0) return;
@@ -1542,9 +1548,9 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
         const T gm = gm_of<T>(st);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            T t = sh.part[0][lane][d];
+            T t = part[0][lane][d];
 #pragma unroll
-            for (int w = 1; w < BT / 64; ++w) t += sh.part[w][lane][d];
+            for (int w = 1; w < BT / 64; ++w) t += part[w][lane][d];
             a[d] = gm * t;
         }
         if (!STEP || last) {
@@ -1583,7 +1589,7 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
 #pragma unroll
-        for (int w = IB / 2; w >= 1; w /= 2) v[k] += __shfl_xor(v[k], w, 64);
+        for (int w = pow2_of(IB) / 2; w >= 1; w /= 2) v[k] += __shfl_xor(v[k], w, 64);
     }
     if (lane == 0) {
         auto *r = glob<double>(S.rec) + (size_t)((odd ? S.rec_len : 0) + local) * REC_STRIDE;
@@ -1596,6 +1602,60 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
             clear_counts(S, done);
             grow(w, step == 1 ? &w->cur : &w->slot[odd ? 0 : 1], &w->slot[odd ? 1 : 0]);
         }
+    }
+}
+
+template <typename T, int LAW, bool STEP>
+__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int last)
+{
+    constexpr int IB = os_ib(sizeof(T) == 8, LAW);
+    __shared__ union {
+        T part[BT / 64][IB][3];
+        FinishMem fin;
+    } sh;
+    const int tid = threadIdx.x;
+    const bool odd = (step & 1) != 0;
+    if (STEP && (int)blockIdx.x >= L.total_units) {
+        // the end of the step before: 256 elements' side of the L1 plane
+        SysRef S = cst(L.sys)[find_sys(L, (int)blockIdx.x - L.total_units, true)];
+        const int local = (int)blockIdx.x - L.total_units - S.ounit_begin;
+        double v[7];
+        sum_records(S, odd ? 0 : S.rec_len, S.n_rec, v, sh.fin.lds);
+        if (tid == 0) plane_of(S, v, sh.fin.pl);
+        __syncthreads();
+        const int i = min(local * BT + tid, S.n - 1);
+        const size_t na = S.nalloc;
+        auto *A = step_set<const T>(S, step - 1);
+        classify(S, local * BT + tid, (T)A[i], (T)A[na + i], (T)A[2 * na + i], sh.fin, false, nullptr,
+                 log_row(S, cst(S.st)->step + step - 1) + 1);
+        return;
+    }
+    const int u = blockIdx.x;
+    SysRef S = cst(L.sys)[find_sys(L, u, false)];
+    const int local = u - S.unit_begin;
+    auto run = [&](auto ib) {
+        one_sided_unit<T, LAW, STEP, decltype(ib)::value>(S, local, step, last, sh.part);
+    };
+    switch (S.ib) {
+    case 2:
+        if constexpr (sizeof(T) == 8) run(Int<2>{});
+        break;
+    case 3:
+        if constexpr (sizeof(T) == 8) run(Int<3>{});
+        break;
+    case 4: run(Int<4>{}); break;
+    case 5:
+        if constexpr (IB >= 5) run(Int<5>{});
+        break;
+    case 6:
+        if constexpr (IB >= 6) run(Int<6>{});
+        break;
+    case 7:
+        if constexpr (IB >= 7) run(Int<7>{});
+        break;
+    case 8:
+        if constexpr (IB >= 8) run(Int<8>{});
+        break;
     }
 }
 

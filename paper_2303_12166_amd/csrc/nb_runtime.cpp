@@ -50,7 +50,8 @@ struct TileCfg {
     int sym, ch;            // symmetric kernel (Kahan and FP64 modes) and its tiles per chunk
     int rows;               // tile rows per band of the symmetric kernel (1, 2 or 4)
     int64_t n_sort;         // elements the order's sort works on
-    int one_sided, n_rec;   // one-sided force kernel; records of a step
+    int one_sided, ib;      // one-sided force kernel; its elements per workgroup
+    int n_rec;              // records of a step
     int pe_ch, n_peunits;   // potential energy: tiles per chunk, (tile row, chunk) units
     size_t react_floats;    // reaction partials of the symmetric kernel (elements of the mode's type)
 };
@@ -70,11 +71,45 @@ struct Layout;
 Layout layout_for(int mode, int law, const TileCfg &c);
 size_t layout_total(int mode, int law, const TileCfg &c);
 
-// Largest systems of the one-sided force kernel, by FP64 mode and element law: where a step of it
-// and of the symmetric kernel at its finest split cost about the same (FP32 contact law 44.2 and 44.4 us
-// at 9,000 elements, 56.9 and 51.5 at 11,000; eqs. (4)-(6) 43.1 and 49.5 at 7,000, 62.7 and 52.5 at
-// 9,000; FP64 59 and 71 at 7,000, 86.5 and 81 at 9,000, eqs. (4)-(6) 81 and 89, 121 and 110).
-constexpr int64_t ONE_SIDED_MAX[2][2] = {{8960, 8192}, {8192, 8192}};
+// Largest systems of the one-sided force kernel, by FP64 mode and element law. Alone, a system gains
+// up to about 12,000 elements in FP32 (a step of 7,001: 23.8 us against 38 with the symmetric kernel,
+// 11,000: 48 and 52) and 7,100 in FP64 (4,096: 23.5 and 39.6, 7,001: 48.5 and 53). In a large
+// batch it only costs, twice the pairs (32 systems of 4,096 to 8,192 elements, all one-sided: 388
+// us a step in FP32 against 284, 1087 against 651 in FP64), so the limits lie where a large batch
+// loses little.
+constexpr int64_t ONE_SIDED_MAX[2][2] = {{7168, 7168}, {4608, 4608}};
+
+int64_t one_sided_units(int64_t n, int64_t n1, int64_t ib)
+{
+    return (n1 + ib - 1) / ib + (n - n1 + ib - 1) / ib;
+}
+
+// Elements per workgroup of the one-sided force kernel. Every workgroup does the same work, so a step
+// takes as many rounds as the fullest CU has workgroups, and a round's cost goes with ib plus what
+// each workgroup spends beside its pairs (about two and a half elements' worth). The step's
+// further workgroups (n / 256 short ones) count for a quarter. Few rounds leave a SIMD with one
+// wave, which then takes as long as two (FP32; three under eqs. (4)-(6), whose pair is a longer chain).
+// Ten steps with the choice against 8 elements (FP32) or 4 (FP64) throughout, per step: 8.1 -> 7.6 us
+// at 2,048, 24.6 -> 22.6 at 7,001, 26.0 -> 16.1 under eqs. (4)-(6) at 4,096, FP64 15.4 -> 14.2 at
+// 2,048. Over 32 sizes up to 8,960 it is 0.5 % from the best of the choices in the mean (6 %
+// at most) under the contact law, 1 % (8.6 %) under eqs. (4)-(6), 0.1 % (1.4 %) in FP64.
+int one_sided_ib(int64_t n, int64_t n1, int mode, int law)
+{
+    const bool fp64 = mode == NB_FP64;
+    const int64_t least = fp64 ? 1 : (law == 0 ? 2 : 3);
+    int best = 0;
+    int64_t best_cost = INT64_MAX;
+    for (int ib = fp64 ? 2 : 4; ib <= os_ib(fp64, law); ++ib) {
+        const int64_t wgs = one_sided_units(n, n1, ib) + (n + 4 * BT - 1) / (4 * BT);
+        const int64_t rounds = std::max(least, (wgs + CU_COUNT - 1) / CU_COUNT);
+        const int64_t cost = rounds * (2 * ib + 5);
+        if (cost < best_cost) {
+            best = ib;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
 
 // The work split fields of c for ns requested chunks and bands of `rows` tile rows.
 void finish_split(TileCfg &c, int64_t n, int64_t n1, int mode, int law, int ns, int rows)
@@ -107,8 +142,8 @@ void finish_split(TileCfg &c, int64_t n, int64_t n1, int mode, int law, int ns, 
             c.one_sided = 1;
             c.sym = 0;
             c.react_floats = 0;
-            const int64_t ib = os_ib(mode == NB_FP64);
-            c.n_units = (int)((n1 + ib - 1) / ib + (n - n1 + ib - 1) / ib);
+            c.ib = one_sided_ib(n, n1, mode, law);
+            c.n_units = (int)one_sided_units(n, n1, c.ib);
             c.n_rec = c.n_units;
         }
         return;
@@ -549,6 +584,7 @@ void fill_desc(SysDesc &d, const nb_params *p, const nb_buffers *b, const TileCf
     d.rec_len = rec_len(cfg);
     d.alt = cfg.one_sided ? base + lay.alt : nullptr;
     d.one_sided = cfg.one_sided;
+    d.ib = cfg.ib;
     d.pe_part = reinterpret_cast<double *>(base + lay.pe);
     d.l1_log = reinterpret_cast<int32_t *>(base + lay.log);
     d.n = (int32_t)p->n;

@@ -108,3 +108,31 @@ def test_batch_with_other_kernels_equals_alone(mode, law):
     assert crossings > 0
     for s in alone + mix + graph + sta + [empty]:
         s.close()
+
+
+@pytest.mark.parametrize("mode,law", list(BAR))
+@pytest.mark.parametrize("n,q", [(700, 0.4), (2048, 0.5), (2801, 0.9), (3501, 0.2), (3802, 0.6),
+                                 (4501, 0.7), (6401, 0.3)])
+def test_elements_per_workgroup(n, q, mode, law):
+    """Sizes at which a workgroup takes 4 to 8 elements (FP64: 2 to 4), with remainders in both stars:
+    the forces, and those that a step leaves, against the oracle at the step's own positions."""
+    nb = require_gpu()
+    ic = synth.with_velocity_noise(synth.make_binary(n, q, seed=n), 0.05, 3)
+    print_case("elements per workgroup", n, q, mode, law)
+    M, W = nb.MODES[mode], nb.LAWS[law]
+    nb.nb_tile_override(n, n, M, 4096, 1, law=W)
+    try:
+        s, kw = _system(nb, ic, mode, law)
+    finally:
+        nb.nb_tile_override(n, n, M, 0, 1, law=W)
+    a = s.accelerations()
+    ref = _oracle(ic, kw)
+    assert force_error(a, ref) <= BAR[mode, law]
+    s.step(1)
+    after = s.accelerations()
+    p = np.stack([c.cpu().numpy().astype(np.float64) for c in (s.x, s.y, s.z)], axis=1)
+    assert not np.array_equal(p, ic.f32_as_f64()[0])
+    s.close()
+    if kw:  # the force of the step takes the half-step velocities, which no array holds
+        return
+    assert force_error(after, oracle.accel(p, ic.n1, ic.G, ic.m, ic.D1, ic.D2)) <= BAR[mode, law]
