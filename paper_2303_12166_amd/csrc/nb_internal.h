@@ -127,7 +127,8 @@ struct SysDesc {
     int32_t *units;       // n_units pairs (g, c)
     float *react;         // (double * in the FP64 mode)
     int32_t ch, sym;      // tiles per chunk; 1 when the symmetric kernel is used
-    void *vxs, *vys, *vzs;  // sorted velocities (eqs. 4-6 only; null otherwise)
+    void *vxs, *vys, *vzs;  // sorted velocities (eqs. 4-6 and the symmetric kernels' steps)
+    void *as;               // sorted accelerations between a call's steps, 3 * nalloc (sym only)
     int32_t law, rows;    // element law; tile rows per band (1 in the FP64 mode)
 };
 
@@ -140,9 +141,10 @@ struct Launch {
     int32_t total_ounits;  // O(N) units: 256 elements in element order
     int32_t total_tunits;  // tiles: 256 slots in sorted order
     int32_t law;           // element law of every system in the launch (NB_LAW_*)
-    int32_t ounit_base;    // first O(N) unit of the systems outside the one-sided force kernel
+    int32_t ounit_base;    // first O(N) unit of the systems outside the first class below
     int32_t any_big;       // a system has more than COM_FUSE_UNITS units
-    // the table is ordered by force kernel: one-sided systems, then bands of 1, 2 and 4 rows (the
+    int32_t any_empty;     // a system has no elements
+    // the table is ordered by force kernel: one-sided (and empty) systems, then bands of 1, 2 and 4 rows (the
     // plain and FP64 kernels count as 1); they own the force units up to band_end[0] .. band_end[3]
     int32_t band_end[KERNEL_CLASSES];
 };
@@ -165,9 +167,9 @@ hipError_t launch_sort(const SysDesc &d, int mode, void *work, hipStream_t s);
 hipError_t launch_gather(const Launch &L, int mode, hipStream_t s);
 hipError_t launch_forces(const Launch &L, int mode, int step, int last, int max_blocks,
                          hipStream_t s);
-hipError_t launch_combine(const Launch &L, int mode, hipStream_t s);
+hipError_t launch_combine(const Launch &L, int mode, int kick, int last, hipStream_t s);
 hipError_t launch_kick_stats(const Launch &L, int mode, int do_kick, hipStream_t s);
-hipError_t launch_finalize_step(const Launch &L, int do_growth, hipStream_t s);
+hipError_t launch_finalize_step(const Launch &L, int in_step, hipStream_t s);
 hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, int n_steps,
                           hipStream_t s);
 hipError_t launch_diag(const Launch &L, int mode, int with_pe, int n_peunits, hipStream_t s);

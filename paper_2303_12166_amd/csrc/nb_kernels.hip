@@ -417,65 +417,82 @@ __device__ __forceinline__ float float_below(double x)
 __device__ __forceinline__ bool bounded(float x) { return isfinite(x); }
 __device__ __forceinline__ bool bounded(double x) { return fabs(x) < 1.0e100; }
 
+// One element of a tile into its sorted slot (none: `held` is false, the slot keeps its fill values and
+// is left out of the box), and the tile's bounding box. Called by a whole workgroup.
+template <typename T>
+__device__ __forceinline__ void store_sorted(SysRef S, int tile, bool held, bool vel, T x, T y, T z, T vx,
+                                             T vy, T vz, float (*lds)[BT / 64])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int slot = tile * TJ + threadIdx.x;
+    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (held) {
+        glob<T>(S.xs)[slot] = x;
+        glob<T>(S.ys)[slot] = y;
+        glob<T>(S.zs)[slot] = z;
+        if (vel) {
+            glob<T>(S.vxs)[slot] = vx;
+            glob<T>(S.vys)[slot] = vy;
+            glob<T>(S.vzs)[slot] = vz;
+        }
+        v[0] = float_below(x);
+        v[1] = float_below(y);
+        v[2] = float_below(z);
+        v[3] = -float_below(-x);
+        v[4] = -float_below(-y);
+        v[5] = -float_below(-z);
+        // a tile with an element out of range is near everything: only the potential energy's
+        // near form leaves such an element's pairs out
+        if (!(bounded(x) && bounded(y) && bounded(z))) {
+            v[0] = v[1] = v[2] = -INFINITY;
+            v[3] = v[4] = v[5] = INFINITY;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        v[k] = wave_min(v[k]);
+        v[3 + k] = wave_max(v[3 + k]);
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) lds[k][wave] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        const int k = threadIdx.x;
+        float r = 0.0f;
+        if (k < 3 || (k >= 4 && k < 7)) {
+            const int q = k < 3 ? k : k - 1;
+            r = lds[q][0];
+            for (int w = 1; w < BT / 64; ++w) r = q < 3 ? fminf(r, lds[q][w]) : fmaxf(r, lds[q][w]);
+        }
+        glob<float>(S.tbox)[(size_t)tile * 8 + k] = r;
+    }
+    __syncthreads();
+}
+
 // Pulls the current positions (and, under eqs. (4)-(6), velocities) into sorted order and records
-// each tile's bounding box (padding slots keep their fill values and are left out of the box).
+// each tile's bounding box. In the steps of the symmetric kernels k_advance does this.
 template <typename T>
 __global__ __launch_bounds__(BT) void k_gather(Launch L)
 {
     __shared__ float lds[6][BT / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
         SysRef S = cst(L.sys)[find_tile_sys(L, u)];
         const int tile = u - S.tunit_begin;
-        const int slot = tile * TJ + threadIdx.x;
-        const int idx = glob<const int32_t>(S.perm)[slot];
-        float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        const int idx = glob<const int32_t>(S.perm)[tile * TJ + threadIdx.x];
+        T x = 0, y = 0, z = 0, vx = 0, vy = 0, vz = 0;
         if (idx >= 0) {
-            const T x = glob<const T>(S.x)[idx];
-            const T y = glob<const T>(S.y)[idx];
-            const T z = glob<const T>(S.z)[idx];
-            glob<T>(S.xs)[slot] = x;
-            glob<T>(S.ys)[slot] = y;
-            glob<T>(S.zs)[slot] = z;
-            if (S.vxs) {
-                glob<T>(S.vxs)[slot] = glob<const T>(S.vx)[idx];
-                glob<T>(S.vys)[slot] = glob<const T>(S.vy)[idx];
-                glob<T>(S.vzs)[slot] = glob<const T>(S.vz)[idx];
-            }
-            v[0] = float_below(x);
-            v[1] = float_below(y);
-            v[2] = float_below(z);
-            v[3] = -float_below(-x);
-            v[4] = -float_below(-y);
-            v[5] = -float_below(-z);
-            // a tile with an element out of range is near everything: only the potential energy's
-            // near form leaves such an element's pairs out
-            if (!(bounded(x) && bounded(y) && bounded(z))) {
-                v[0] = v[1] = v[2] = -INFINITY;
-                v[3] = v[4] = v[5] = INFINITY;
+            x = glob<const T>(S.x)[idx];
+            y = glob<const T>(S.y)[idx];
+            z = glob<const T>(S.z)[idx];
+            if (S.law != 0) {
+                vx = glob<const T>(S.vx)[idx];
+                vy = glob<const T>(S.vy)[idx];
+                vz = glob<const T>(S.vz)[idx];
             }
         }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            v[k] = wave_min(v[k]);
-            v[3 + k] = wave_max(v[3 + k]);
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) lds[k][wave] = v[k];
-        }
-        __syncthreads();
-        if (threadIdx.x < 8) {
-            const int k = threadIdx.x;
-            float r = 0.0f;
-            if (k < 3 || (k >= 4 && k < 7)) {
-                const int q = k < 3 ? k : k - 1;
-                r = lds[q][0];
-                for (int w = 1; w < BT / 64; ++w) r = q < 3 ? fminf(r, lds[q][w]) : fmaxf(r, lds[q][w]);
-            }
-            glob<float>(S.tbox)[(size_t)tile * 8 + k] = r;
-        }
-        __syncthreads();
+        store_sorted<T>(S, tile, idx >= 0, S.law != 0, x, y, z, vx, vy, vz, lds);
     }
 }
 
@@ -792,22 +809,157 @@ __device__ __forceinline__ size_t react_group_offset(int g, int ntiles, int kr)
            ((size_t)g * (ntiles - 1) - (size_t)kr * (size_t)g * (size_t)(g - 1) / 2);
 }
 
+// ------------------------------------------------------------------ second kick
+
+constexpr int COMBINE_SEGS = 4;  // threads per element of the combine kernels
+
+template <typename T, typename St>
+__device__ __forceinline__ T h_of(St st)
+{
+    if constexpr (sizeof(T) == 4) {
+        return st->h_f;
+    } else {
+        return st->h_d;
+    }
+}
+template <typename T, typename St>
+__device__ __forceinline__ T dt_of(St st)
+{
+    if constexpr (sizeof(T) == 4) {
+        return st->dt_f;
+    } else {
+        return st->dt;
+    }
+}
+template <typename T, typename St>
+__device__ __forceinline__ T gm_of(St st)
+{
+    if constexpr (sizeof(T) == 4) {
+        return st->gm_f;
+    } else {
+        return st->gm_d;
+    }
+}
+
+// Per-unit record of a step: each star's position sums and the count of non-finite elements.
+__device__ __forceinline__ void add_stats(double (&v)[7], double px, double py, double pz,
+                                          double wx, double wy, double wz, bool star2)
+{
+    const int o = star2 ? 3 : 0;
+    v[o + 0] = px;
+    v[o + 1] = py;
+    v[o + 2] = pz;
+    const bool fin = isfinite(px) && isfinite(py) && isfinite(pz) && isfinite(wx) &&
+                     isfinite(wy) && isfinite(wz);
+    v[6] = fin ? 0.0 : 1.0;
+}
+
+// Row of the L1 log of a step: its number, then the counts.
+__device__ __forceinline__ int32_t *log_row(SysRef S, int64_t step)
+{
+    return S.l1_log + 4 * (size_t)(step % L1_LOG_CAP);
+}
+
+// The counts of step number `step` start from nothing.
+__device__ __forceinline__ void clear_counts(SysRef S, int64_t step)
+{
+    DevState *st = S.st;
+    st->n_past = st->fwd = st->bwd = 0;
+    int32_t *row = log_row(S, step);
+    row[0] = (int32_t)step;
+    row[1] = row[2] = row[3] = 0;
+}
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
+
+// The state of a slot's element as the force saw it.
+template <typename T>
+__device__ __forceinline__ void element_state(SysRef S, int slot, T (&x)[3], T (&v)[3])
+{
+    x[0] = glob<const T>(S.xs)[slot];
+    x[1] = glob<const T>(S.ys)[slot];
+    x[2] = glob<const T>(S.zs)[slot];
+    v[0] = glob<const T>(S.vxs)[slot];
+    v[1] = glob<const T>(S.vys)[slot];
+    v[2] = glob<const T>(S.vzs)[slot];
+}
+
+// The second kick of this thread's element idx (none: -1) of tile J with its new acceleration, and the
+// tile's record of the step. Between the steps of a call the elements stay in sorted order (S.xs, S.vxs
+// and S.as): 4-byte writes all over the caller's arrays, six per element and step, cost as much
+// as a pass of their own. The `last` step writes the caller's. Called by a whole workgroup of
+// BT * COMBINE_SEGS threads, of which the first TJ hold the tile's elements; x and v are the
+// element's, loaded before.
+template <typename T>
+__device__ __forceinline__ void kick_record(SysRef S, int J, int idx, const T (&x)[3], const T (&v)[3],
+                                            const T (&a)[3], int last, double (*lds)[BT / 64])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x < TJ) {
+        double r[7] = {0, 0, 0, 0, 0, 0, 0};
+        if (idx >= 0) {
+            const T h = h_of<T>(glob<const DevState>(S.st));
+            const T wx = fma_t(h, a[0], v[0]), wy = fma_t(h, a[1], v[1]), wz = fma_t(h, a[2], v[2]);
+            const int slot = J * TJ + threadIdx.x;
+            if (last) {
+                glob<T>(S.x)[idx] = x[0];
+                glob<T>(S.y)[idx] = x[1];
+                glob<T>(S.z)[idx] = x[2];
+                glob<T>(S.vx)[idx] = wx;
+                glob<T>(S.vy)[idx] = wy;
+                glob<T>(S.vz)[idx] = wz;
+            } else {
+                glob<T>(S.vxs)[slot] = wx;
+                glob<T>(S.vys)[slot] = wy;
+                glob<T>(S.vzs)[slot] = wz;
+                auto *A = glob<T>(S.as) + slot;
+                A[0] = a[0];
+                A[S.nalloc] = a[1];
+                A[2 * (size_t)S.nalloc] = a[2];
+            }
+            add_stats(r, x[0], x[1], x[2], wx, wy, wz, idx >= S.n1);
+        }
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) r[k] += __shfl_xor(r[k], off, 64);
+            if (lane == 0) lds[k][wave] = r[k];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 7) {
+        const int k = threadIdx.x;
+        double t = lds[k][0];
+        for (int w = 1; w < TJ / 64; ++w) t += lds[k][w];
+        glob<double>(S.rec)[(size_t)J * REC_STRIDE + k] = t;
+    }
+    if (threadIdx.x == 0 && J == 0) {
+        // the step that this kick completes
+        const int64_t step = S.st->step + 1;
+        S.st->step = step;
+        clear_counts(S, step);
+    }
+}
+
 // a = G m (sum of the element's own chunk partials, then the reactions of every band with a
-// row before the element's tile, in band order), scattered to the element's own index. KR is the
+// row before the element's tile, in band order). KICK (in a step): the element's second kick and the
+// tile's record follow (kick_record); otherwise a goes to the element's own index. KR is the
 // system's band height. The element's terms (its cj chunk partials, then its ng band reactions)
 // are cut into COMBINE_SEGS contiguous runs, one thread each; a run is a Kahan sum per component
 // in term order, with the three components' loads issued together, eight terms at a time. The
 // runs' results are then added in run order with Kahan compensation by the element's first
 // thread. The order of every addition depends on the system's size alone.
-constexpr int COMBINE_SEGS = 4;
-
-template <int KR>
+template <int KR, bool KICK, bool MANY>
 __device__ __forceinline__ void combine_tile(SysRef S, int J, int e, int k,
-                                             float (*part)[COMBINE_SEGS][TJ])
+                                             int last, float (*part)[COMBINE_SEGS][TJ],
+                                             double (*lds)[BT / 64])
 {
     const int T = S.ntiles;
     const int slot = J * TJ + e;
     const int idx = glob<const int32_t>(S.perm)[slot];
+    float x[3] = {0.f, 0.f, 0.f}, v0[3] = {0.f, 0.f, 0.f}, out[3] = {0.f, 0.f, 0.f};
+    if (KICK && !MANY && k == 0 && idx >= 0) element_state(S, slot, x, v0);
     auto *P = glob<const float>(S.part);
     auto *R = glob<const float>(S.react);
     const size_t na = S.nalloc;
@@ -864,37 +1016,47 @@ __device__ __forceinline__ void combine_tile(SysRef S, int J, int e, int k,
             }
         }
     }
+    if (KICK && MANY && k == 0 && idx >= 0) element_state(S, slot, x, v0);
 #pragma unroll
     for (int d = 0; d < 3; ++d) part[d][k][e] = sum[d] - comp[d];
     __syncthreads();
     if (k == 0 && idx >= 0) {
-        float out[3];
+        const float gm = glob<DevState>(S.st)->gm_f;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             float s = part[d][0][e], c = 0.f;
 #pragma unroll
             for (int q = 1; q < COMBINE_SEGS; ++q) kahan_add(s, c, part[d][q][e]);
-            out[d] = s - c;
+            out[d] = gm * (s - c);
         }
-        const float gm = glob<DevState>(S.st)->gm_f;
-        glob<float>(S.ax)[idx] = gm * out[0];
-        glob<float>(S.ay)[idx] = gm * out[1];
-        glob<float>(S.az)[idx] = gm * out[2];
+        if (!KICK || last) {
+            glob<float>(S.ax)[idx] = out[0];
+            glob<float>(S.ay)[idx] = out[1];
+            glob<float>(S.az)[idx] = out[2];
+        }
     }
-    __syncthreads();  // part is rewritten by the block's next tile
+    if constexpr (KICK) kick_record<float>(S, J, idx, x, v0, out, last, lds);
+    __syncthreads();  // part and lds are rewritten by the block's next tile
 }
 
-__global__ __launch_bounds__(BT * COMBINE_SEGS) void k_combine_sym(Launch L)
+// MANY (more tiles than CUs): 64 registers, so that two workgroups share a CU; with 76 the 258 tiles of
+// 65,536 elements took two rounds (25 us a launch against 23, a batch of 24 systems of 4,096 to
+// 32,768 1125 us a step against 1118). Up to one tile per CU the element's state is loaded
+// ahead of the sums and the registers are free: 34.5 us a step at 7,500 elements against 37.0.
+template <bool KICK, bool MANY>
+__global__ __launch_bounds__(BT * COMBINE_SEGS) __attribute__((amdgpu_waves_per_eu(MANY ? 8 : 4)))
+void k_combine_sym(Launch L, int last)
 {
     __shared__ float part[3][COMBINE_SEGS][TJ];
+    __shared__ double lds[7][BT / 64];
     const int e = threadIdx.x % TJ, k = threadIdx.x / TJ;
     for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
         SysRef S = cst(L.sys)[find_tile_sys(L, u)];
         const int J = u - S.tunit_begin;
         switch (S.rows) {
-        case 1: combine_tile<1>(S, J, e, k, part); break;
-        case 2: combine_tile<2>(S, J, e, k, part); break;
-        default: combine_tile<4>(S, J, e, k, part); break;
+        case 1: combine_tile<1, KICK, MANY>(S, J, e, k, last, part, lds); break;
+        case 2: combine_tile<2, KICK, MANY>(S, J, e, k, last, part, lds); break;
+        default: combine_tile<4, KICK, MANY>(S, J, e, k, last, part, lds); break;
         }
     }
 }
@@ -973,9 +1135,11 @@ __device__ __forceinline__ double pair_s64(double r2, double w, double dx, doubl
 // k_combine_sym's FP64 counterpart for bands of one row: the same runs, in plain FP64 (a run's
 // terms in order, then the runs in order). One thread per element left two waves per SIMD at
 // 50,021 elements, each waiting for one read after the other: 62 us, 1.9 TB/s; four take 29 us, 4.1 TB/s.
-__global__ __launch_bounds__(BT * COMBINE_SEGS) void k_combine_sym64(Launch L)
+template <bool KICK>
+__global__ __launch_bounds__(BT * COMBINE_SEGS) void k_combine_sym64(Launch L, int last)
 {
     __shared__ double part[3][COMBINE_SEGS][TJ];
+    __shared__ double lds[7][BT / 64];
     const int e = threadIdx.x % TJ, k = threadIdx.x / TJ;
     for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
         SysRef S = cst(L.sys)[find_tile_sys(L, u)];
@@ -988,6 +1152,8 @@ __global__ __launch_bounds__(BT * COMBINE_SEGS) void k_combine_sym64(Launch L)
         const size_t na = S.nalloc;
         const int cj = (T - J + S.ch - 1) / S.ch;  // the chunk count of the element's own row
         const int M = cj + J;
+        double x[3] = {0, 0, 0}, v0[3] = {0, 0, 0}, out[3] = {0, 0, 0};
+        if (KICK && k == 0 && idx >= 0) element_state(S, slot, x, v0);
         const int t0 = (int)(((int64_t)M * k) / COMBINE_SEGS);
         const int t1 = (int)(((int64_t)M * (k + 1)) / COMBINE_SEGS);
         double sum[3] = {0.0, 0.0, 0.0};
@@ -1032,19 +1198,22 @@ __global__ __launch_bounds__(BT * COMBINE_SEGS) void k_combine_sym64(Launch L)
         for (int d = 0; d < 3; ++d) part[d][k][e] = sum[d];
         __syncthreads();
         if (k == 0 && idx >= 0) {
-            double out[3];
+            const double gm = glob<DevState>(S.st)->gm_d;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                out[d] = part[d][0][e];
+                double t = part[d][0][e];
 #pragma unroll
-                for (int q = 1; q < COMBINE_SEGS; ++q) out[d] += part[d][q][e];
+                for (int q = 1; q < COMBINE_SEGS; ++q) t += part[d][q][e];
+                out[d] = gm * t;
             }
-            const double gm = glob<DevState>(S.st)->gm_d;
-            glob<double>(S.ax)[idx] = gm * out[0];
-            glob<double>(S.ay)[idx] = gm * out[1];
-            glob<double>(S.az)[idx] = gm * out[2];
+            if (!KICK || last) {
+                glob<double>(S.ax)[idx] = out[0];
+                glob<double>(S.ay)[idx] = out[1];
+                glob<double>(S.az)[idx] = out[2];
+            }
         }
-        __syncthreads();  // part is rewritten by the block's next tile
+        if constexpr (KICK) kick_record<double>(S, J, idx, x, v0, out, last, lds);
+        __syncthreads();  // part and lds are rewritten by the block's next tile
     }
 }
 
@@ -1077,71 +1246,16 @@ __global__ __launch_bounds__(BT) void k_combine_f32(Launch L)
 
 // ------------------------------------------------------------------ leap-frog and L1 plane
 
-template <typename T, typename St>
-__device__ __forceinline__ T h_of(St st)
-{
-    if constexpr (sizeof(T) == 4) {
-        return st->h_f;
-    } else {
-        return st->h_d;
-    }
-}
-template <typename T, typename St>
-__device__ __forceinline__ T dt_of(St st)
-{
-    if constexpr (sizeof(T) == 4) {
-        return st->dt_f;
-    } else {
-        return st->dt;
-    }
-}
-template <typename T, typename St>
-__device__ __forceinline__ T gm_of(St st)
-{
-    if constexpr (sizeof(T) == 4) {
-        return st->gm_f;
-    } else {
-        return st->gm_d;
-    }
-}
-
-// Per-unit record of a step: each star's position sums and the count of non-finite elements.
-__device__ __forceinline__ void add_stats(double (&v)[7], double px, double py, double pz,
-                                          double wx, double wy, double wz, bool star2)
-{
-    const int o = star2 ? 3 : 0;
-    v[o + 0] = px;
-    v[o + 1] = py;
-    v[o + 2] = pz;
-    const bool fin = isfinite(px) && isfinite(py) && isfinite(pz) && isfinite(wx) &&
-                     isfinite(wy) && isfinite(wz);
-    v[6] = fin ? 0.0 : 1.0;
-}
-
-// Row of the L1 log of a step: its number, then the counts.
-__device__ __forceinline__ int32_t *log_row(SysRef S, int64_t step)
-{
-    return S.l1_log + 4 * (size_t)(step % L1_LOG_CAP);
-}
-
-// The counts of step number `step` start from nothing.
-__device__ __forceinline__ void clear_counts(SysRef S, int64_t step)
-{
-    DevState *st = S.st;
-    st->n_past = st->fwd = st->bwd = 0;
-    int32_t *row = log_row(S, step);
-    row[0] = (int32_t)step;
-    row[1] = row[2] = row[3] = 0;
-}
-
 // Optional second kick v += a dt/2, then per-unit FP64 sums of each star's positions and the
-// count of non-finite elements. Systems of the one-sided force kernel do this there.
+// count of non-finite elements. In the steps of a one-sided system the force kernel does this, in those
+// of the symmetric kernels the combine.
 template <typename T>
 __global__ __launch_bounds__(BT) void k_kick_stats(Launch L, int do_kick)
 {
     __shared__ double lds[7][BT / 64];
-    for (int u = L.ounit_base + blockIdx.x; u < L.total_ounits; u += gridDim.x) {
+    for (int u = blockIdx.x; u < L.total_ounits; u += gridDim.x) {
         SysRef S = cst(L.sys)[find_sys(L, u, true)];
+        if (do_kick && S.one_sided) continue;
         const int local = u - S.ounit_begin;
         const int i = local * BT + threadIdx.x;
         double v[7] = {0, 0, 0, 0, 0, 0, 0};
@@ -1270,12 +1384,14 @@ __device__ __forceinline__ void classify(SysRef S, int i, T px, T py, T pz, Fini
                           ((double)py - m.pl.com1[1]) * m.pl.e[1] +
                           ((double)pz - m.pl.com1[2]) * m.pl.e[2];
         past = m.pl.ok && xi < m.pl.xi_cut;
+        const int8_t now = past ? 1 : 0;
+        int8_t old = 2;
         if (!init) {
-            const bool prev = glob<int8_t>(S.side)[i] != 0;
-            fwd = past && !prev;
-            bwd = !past && prev;
+            old = glob<int8_t>(S.side)[i];
+            fwd = past && old == 0;
+            bwd = !past && old != 0;
         }
-        glob<int8_t>(S.side)[i] = past ? 1 : 0;
+        if (old != now) glob<int8_t>(S.side)[i] = now;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c0 = __popcll(__ballot(past)), c1 = __popcll(__ballot(fwd)), c2 = __popcll(__ballot(bwd));
@@ -1355,9 +1471,6 @@ __device__ __forceinline__ double one_sided_s(double dx, double dy, double dz, c
     const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, 1.0e-200)));
     return pair_s64<LAW>(r2, rsqrt_f64(r2), dx, dy, dz, vj.x - vi.x, vj.y - vi.y, vj.z - vi.z, K);
 }
-
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
 
 template <typename T>
 struct Vec4;
@@ -1618,6 +1731,7 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
     if (STEP && (int)blockIdx.x >= L.total_units) {
         // the end of the step before: 256 elements' side of the L1 plane
         SysRef S = cst(L.sys)[find_sys(L, (int)blockIdx.x - L.total_units, true)];
+        if (!S.one_sided) return;  // an empty system
         const int local = (int)blockIdx.x - L.total_units - S.ounit_begin;
         double v[7];
         sum_records(S, odd ? 0 : S.rec_len, S.n_rec, v, sh.fin.lds);
@@ -1992,18 +2106,18 @@ void k_force_rows(Launch L)
 
 // Systems above COM_FUSE_UNITS units: one workgroup each sums the records and finishes the step
 // (every workgroup of k_advance doing so would read n / 256 records n / 256 times).
-__global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int do_growth)
+__global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int in_step)
 {
     __shared__ double lds[7][BT / 64];
     for (int s = blockIdx.x; s < L.n_sys; s += gridDim.x) {
         SysRef S = cst(L.sys)[s];
         if (S.n_ounits <= COM_FUSE_UNITS) continue;
         double v[7];
-        sum_records(S, 0, S.n_ounits, v, lds);
+        sum_records(S, 0, in_step ? S.n_rec : S.n_ounits, v, lds);
         if (threadIdx.x == 0) {
             Plane p;
             plane_of(S, v, p);
-            finish_step(S, p, v[6], do_growth);
+            finish_step(S, p, v[6], in_step);
         }
         __syncthreads();
     }
@@ -2013,26 +2127,49 @@ __global__ __launch_bounds__(BT) void k_finalize_step(Launch L, int do_growth)
 // kick wrote the records (ADV_INIT: only records the sides at creation) -- star centres, L1
 // plane, growth, and the donor elements' side of the plane with the crossings since the last
 // step. `kick`: begins the next step, v += a dt/2, x += v dt. One kernel of a step in place of
-// four: each had a few microseconds of launch and drain (65,536 elements: 784 -> 762 us a step).
+// five: each had a few microseconds of launch and drain. A step of the symmetric kernels is this,
+// the forces and the combine with the second kick; with the sort's gather and the second kick
+// as kernels of their own it took 4.3 us more (38.8 -> 34.5 at 7,500 elements, 81 -> 77 at 16,384).
 // Up to COM_FUSE_UNITS units every workgroup sums the system's records itself, in one order, and
 // its first one records the result. One-sided systems come here at the beginning of a call (their
 // kick and drift go to the first step's set) and at its end, after n_steps.
+// Its first n_o units are 256 elements each in element order; the others (the symmetric kernels' systems)
+// are tiles: the drifted elements also go to their sorted slots there, with the tile's bounding box.
 template <typename T>
-__global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick, int n_steps)
+__global__ __launch_bounds__(BT) void k_advance(Launch L, int n_o, int n_t, int finish, int kick, int n_steps)
 {
     __shared__ FinishMem m;
-    for (int u = L.ounit_base + blockIdx.x; u < L.total_ounits; u += gridDim.x) {
-        SysRef S = cst(L.sys)[find_sys(L, u, true)];
-        const int local = u - S.ounit_begin;
-        const int i = local * BT + threadIdx.x;
-        auto *x = glob<T>(S.x), *y = glob<T>(S.y), *z = glob<T>(S.z);
+    __shared__ float box[6][BT / 64];
+    for (int u = blockIdx.x; u < n_o + n_t; u += gridDim.x) {
+        const bool tiles = u >= n_o;
+        SysRef S = cst(L.sys)[tiles ? find_tile_sys(L, u - n_o) : find_sys(L, u, true)];
+        if (S.one_sided && finish && kick) continue;
+        const int local = tiles ? u - n_o - S.tunit_begin : u - S.ounit_begin;
+        int i = local * BT + threadIdx.x, at = i;
+        if (tiles) {
+            const int idx = glob<const int32_t>(S.perm)[i];
+            i = idx < 0 ? S.n : idx;
+            if (!finish) at = i;  // the call's beginning: from the caller's arrays
+        }
+        const bool sorted = tiles && finish;
+        auto *x = glob<T>(sorted ? S.xs : S.x), *y = glob<T>(sorted ? S.ys : S.y),
+             *z = glob<T>(sorted ? S.zs : S.z);
         const bool call_end = S.one_sided && finish != ADV_INIT;
         const bool odd = call_end && (n_steps & 1) != 0;
-        T px = 0, py = 0, pz = 0;
+        T px = 0, py = 0, pz = 0, vx = 0, vy = 0, vz = 0, a[3] = {0, 0, 0};
         if (i < S.n) {
-            px = x[i];
-            py = y[i];
-            pz = z[i];
+            px = x[at];
+            py = y[at];
+            pz = z[at];
+            if (kick) {
+                const size_t na = S.nalloc;
+                vx = glob<const T>(sorted ? S.vxs : S.vx)[at];
+                vy = glob<const T>(sorted ? S.vys : S.vy)[at];
+                vz = glob<const T>(sorted ? S.vzs : S.vz)[at];
+                a[0] = (sorted ? glob<const T>(S.as) : glob<const T>(S.ax))[at];
+                a[1] = (sorted ? glob<const T>(S.as) + na : glob<const T>(S.ay))[at];
+                a[2] = (sorted ? glob<const T>(S.as) + 2 * na : glob<const T>(S.az))[at];
+            }
         }
         if (finish) {
             DevState *st = S.st;
@@ -2066,19 +2203,21 @@ __global__ __launch_bounds__(BT) void k_advance(Launch L, int finish, int kick, 
         if (kick && i < S.n) {
             auto *st = glob<const DevState>(S.st);
             const T h = h_of<T>(st), dt = dt_of<T>(st);
-            T vx = glob<T>(S.vx)[i], vy = glob<T>(S.vy)[i], vz = glob<T>(S.vz)[i];
-            kick_drift(h, dt, px, vx, (T)glob<const T>(S.ax)[i]);
-            kick_drift(h, dt, py, vy, (T)glob<const T>(S.ay)[i]);
-            kick_drift(h, dt, pz, vz, (T)glob<const T>(S.az)[i]);
+            kick_drift(h, dt, px, vx, a[0]);
+            kick_drift(h, dt, py, vy, a[1]);
+            kick_drift(h, dt, pz, vz, a[2]);
             const size_t na = S.nalloc;
             auto *A = step_set<T>(S, 1);
-            (S.one_sided ? A : x)[i] = px;
-            (S.one_sided ? A + na : y)[i] = py;
-            (S.one_sided ? A + 2 * na : z)[i] = pz;
-            (S.one_sided ? A + 3 * na : glob<T>(S.vx))[i] = vx;
-            (S.one_sided ? A + 4 * na : glob<T>(S.vy))[i] = vy;
-            (S.one_sided ? A + 5 * na : glob<T>(S.vz))[i] = vz;
+            if (!tiles) {
+                (S.one_sided ? A : x)[i] = px;
+                (S.one_sided ? A + na : y)[i] = py;
+                (S.one_sided ? A + 2 * na : z)[i] = pz;
+                (S.one_sided ? A + 3 * na : glob<T>(S.vx))[i] = vx;
+                (S.one_sided ? A + 4 * na : glob<T>(S.vy))[i] = vy;
+                (S.one_sided ? A + 5 * na : glob<T>(S.vz))[i] = vz;
+            }
         }
+        if (kick && tiles) store_sorted<T>(S, local, i < S.n, true, px, py, pz, vx, vy, vz, box);
         __syncthreads();  // m is rewritten by the next unit
     }
 }
@@ -2545,27 +2684,32 @@ hipError_t launch_forces(const Launch &L, int mode, int step, int last, int max_
     return begin == L.total_units ? hipSuccess : hipErrorInvalidValue;
 }
 
-hipError_t launch_combine(const Launch &L, int mode, hipStream_t s)
+hipError_t launch_combine(const Launch &L, int mode, int kick, int last, hipStream_t s)
 {
     if (L.total_tunits == 0) return hipSuccess;
     const dim3 g(grid_for(L.total_tunits)), b(BT);
     if (mode == 0) {
         hipLaunchKernelGGL(k_combine_f32, g, b, 0, s, L);
     } else if (mode == 1) {
-        hipLaunchKernelGGL(k_combine_sym, g, dim3(BT * COMBINE_SEGS), 0, s, L);
+        const bool many = L.total_tunits > CU_COUNT;
+        const auto k = kick ? (many ? k_combine_sym<true, true> : k_combine_sym<true, false>)
+                            : (many ? k_combine_sym<false, true> : k_combine_sym<false, false>);
+        hipLaunchKernelGGL(k, g, dim3(BT * COMBINE_SEGS), 0, s, L, last);
     } else {
-        hipLaunchKernelGGL(k_combine_sym64, g, dim3(BT * COMBINE_SEGS), 0, s, L);
+        const auto k = kick ? k_combine_sym64<true> : k_combine_sym64<false>;
+        hipLaunchKernelGGL(k, g, dim3(BT * COMBINE_SEGS), 0, s, L, last);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_kick_stats(const Launch &L, int mode, int do_kick, hipStream_t s)
 {
-    // systems of the one-sided force kernel kick there; at creation (no kick) every system is here
+    // in a step the plain mode's systems and empty ones: the force kernel or the combine kicks the others
+    if (do_kick && mode != 0 && !L.any_empty) return hipSuccess;
     Launch R = L;
-    if (!do_kick) R.ounit_base = 0;
-    if (R.total_ounits <= R.ounit_base) return hipSuccess;
-    const dim3 g(grid_for(R.total_ounits - R.ounit_base)), b(BT);
+    if (do_kick && mode != 0) R.total_ounits = L.ounit_base;
+    if (R.total_ounits == 0) return hipSuccess;
+    const dim3 g(grid_for(R.total_ounits)), b(BT);
     if (mode == 2) {
         hipLaunchKernelGGL(k_kick_stats<double>, g, b, 0, s, R, do_kick);
     } else {
@@ -2574,24 +2718,26 @@ hipError_t launch_kick_stats(const Launch &L, int mode, int do_kick, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_finalize_step(const Launch &L, int do_growth, hipStream_t s)
+hipError_t launch_finalize_step(const Launch &L, int in_step, hipStream_t s)
 {
     if (!L.any_big) return hipSuccess;
-    hipLaunchKernelGGL(k_finalize_step, dim3(grid_for(L.n_sys)), dim3(BT), 0, s, L, do_growth);
+    hipLaunchKernelGGL(k_finalize_step, dim3(grid_for(L.n_sys)), dim3(BT), 0, s, L, in_step);
     return hipGetLastError();
 }
 
 hipError_t launch_advance(const Launch &L, int mode, int finish, int kick, int n_steps, hipStream_t s)
 {
-    // between two steps of a call only the systems outside the one-sided kernel pass here
-    Launch R = L;
-    if (!(finish && kick)) R.ounit_base = 0;
-    if (R.total_ounits <= R.ounit_base) return hipSuccess;
-    const dim3 g(grid_for(R.total_ounits - R.ounit_base)), b(BT);
+    // the plain mode's systems pass in element order, as every one does at creation; of the others the
+    // one-sided ones at a call's beginning and end, empty ones always, the rest tile by tile
+    const bool sorted = mode != 0 && finish != ADV_INIT;
+    const int n_o = !sorted ? L.total_ounits : (finish && kick && !L.any_empty ? 0 : L.ounit_base);
+    const int n_t = sorted ? L.total_tunits : 0;
+    if (n_o + n_t == 0) return hipSuccess;
+    const dim3 g(grid_for(n_o + n_t)), b(BT);
     if (mode == 2) {
-        hipLaunchKernelGGL(k_advance<double>, g, b, 0, s, R, finish, kick, n_steps);
+        hipLaunchKernelGGL(k_advance<double>, g, b, 0, s, L, n_o, n_t, finish, kick, n_steps);
     } else {
-        hipLaunchKernelGGL(k_advance<float>, g, b, 0, s, R, finish, kick, n_steps);
+        hipLaunchKernelGGL(k_advance<float>, g, b, 0, s, L, n_o, n_t, finish, kick, n_steps);
     }
     return hipGetLastError();
 }

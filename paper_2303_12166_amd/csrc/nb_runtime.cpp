@@ -136,7 +136,7 @@ void finish_split(TileCfg &c, int64_t n, int64_t n1, int mode, int law, int ns, 
         c.n_units = units > INT32_MAX ? -1 : (int)units;
         c.react_floats = (size_t)3 * TJ * (size_t)react_tiles;
         c.one_sided = 0;
-        c.n_rec = c.n_ounits;
+        c.n_rec = c.ntiles;
         if (c.rows == 1 && c.ch == 1 && n <= ONE_SIDED_MAX[mode == NB_FP64][law]) {
             // the finest split of a small system: evaluated one-sided
             c.one_sided = 1;
@@ -218,7 +218,7 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
 }
 
 struct Layout {
-    size_t state, desc, diag, red, rec, alt, sort, pe, log, xs, ys, zs, vxs, vys, vzs, perm, tbox, units, react,
+    size_t state, desc, diag, red, rec, alt, sort, pe, log, xs, ys, zs, vxs, vys, vzs, as, perm, tbox, units, react,
         part, total;
 };
 
@@ -249,10 +249,13 @@ Layout layout_for(int mode, int law, const TileCfg &c)
     L.xs = take((size_t)c.nalloc * elem);
     L.ys = take((size_t)c.nalloc * elem);
     L.zs = take((size_t)c.nalloc * elem);
-    // sorted velocities: only eqs. (4)-(6) read them
-    L.vxs = take(law == NB_LAW_PAPER ? (size_t)c.nalloc * elem : 0);
-    L.vys = take(law == NB_LAW_PAPER ? (size_t)c.nalloc * elem : 0);
-    L.vzs = take(law == NB_LAW_PAPER ? (size_t)c.nalloc * elem : 0);
+    // sorted velocities: eqs. (4)-(6) read them, and the steps of the symmetric kernels keep them and the
+    // accelerations sorted
+    const bool vel = law == NB_LAW_PAPER || c.sym;
+    L.vxs = take(vel ? (size_t)c.nalloc * elem : 0);
+    L.vys = take(vel ? (size_t)c.nalloc * elem : 0);
+    L.vzs = take(vel ? (size_t)c.nalloc * elem : 0);
+    L.as = take(c.sym ? (size_t)3 * (size_t)c.nalloc * elem : 0);
     L.perm = take((size_t)c.nalloc * sizeof(int32_t));
     L.tbox = take((size_t)std::max(c.ntiles, 1) * 8 * sizeof(float));
     L.units = take(c.sym ? (size_t)c.n_units * 2 * sizeof(int32_t) : 0);
@@ -381,7 +384,8 @@ int hip_status(hipError_t e) { return e == hipSuccess ? NB_OK : NB_E_HIP; }
 int launch_force_timed(const Launch &L, int mode, int step, int last, hipStream_t st, bool need_combine,
                        bool allow_timing = true)
 {
-    NB_TRY(launch_gather(L, mode, st));
+    // in the steps of the symmetric kernels k_advance has sorted
+    if (step == 0 || mode == NB_FP32_PLAIN) NB_TRY(launch_gather(L, mode, st));
     hipEvent_t a = nullptr, b = nullptr;
     bool timed = false;
     if (allow_timing) {
@@ -408,13 +412,14 @@ int launch_force_timed(const Launch &L, int mode, int step, int last, hipStream_
         g_timing.pending.emplace_back(a, b);
     }
     if (e != hipSuccess) return NB_E_HIP;
-    if (need_combine) NB_TRY(launch_combine(L, mode, st));
+    if (need_combine) NB_TRY(launch_combine(L, mode, step > 0 ? 1 : 0, last, st));
     return NB_OK;
 }
 
 // k_advance ends one step and begins the next, so a call of n_steps runs it n_steps + 1 times; for
 // one-sided systems the force kernel does both between the steps, and only the call's beginning and
-// end are left to it.
+// end are left to it. The second kick is the force kernel's there, the combine's after the symmetric
+// kernels and a kernel of its own in the plain mode, whose positions are gathered for each evaluation.
 int run_steps(const Launch &L, int mode, int n_steps, bool need_combine, hipStream_t st,
               bool allow_timing = true)
 {
@@ -432,7 +437,7 @@ int run_steps(const Launch &L, int mode, int n_steps, bool need_combine, hipStre
 // Index of a system's force kernel in Launch::band_end.
 int kernel_class(const TileCfg &c)
 {
-    return c.one_sided ? 0 : (c.rows >= 4 ? 3 : (c.rows == 2 ? 2 : 1));
+    return c.one_sided || c.ntiles == 0 ? 0 : (c.rows >= 4 ? 3 : (c.rows == 2 ? 2 : 1));
 }
 
 // Prefix offsets of the next table entry (system s) and the launch totals after it.
@@ -452,6 +457,7 @@ void table_append(Launch &L, const nb_system *s, int32_t &unit_begin, int32_t &o
         L.total_tunits += s->cfg.ntiles;
     }
     if (s->cfg.n_ounits > COM_FUSE_UNITS) L.any_big = 1;
+    if (s->cfg.ntiles == 0) L.any_empty = 1;
 }
 
 Launch single_launch(const nb_system *s)
@@ -567,9 +573,11 @@ void fill_desc(SysDesc &d, const nb_params *p, const nb_buffers *b, const TileCf
     d.ys = base + lay.ys;
     d.zs = base + lay.zs;
     const bool paper = p->law == NB_LAW_PAPER;
-    d.vxs = paper ? base + lay.vxs : nullptr;
-    d.vys = paper ? base + lay.vys : nullptr;
-    d.vzs = paper ? base + lay.vzs : nullptr;
+    const bool vel = paper || cfg.sym;
+    d.vxs = vel ? base + lay.vxs : nullptr;
+    d.vys = vel ? base + lay.vys : nullptr;
+    d.vzs = vel ? base + lay.vzs : nullptr;
+    d.as = cfg.sym ? base + lay.as : nullptr;
     d.law = p->law;
     d.perm = reinterpret_cast<int32_t *>(base + lay.perm);
     d.tbox = reinterpret_cast<float *>(base + lay.tbox);
@@ -808,7 +816,7 @@ int nb_create(const nb_params *p, const nb_buffers *b, void *stream, nb_system *
         if (launch_advance(L, p->mode, ADV_INIT, 0, 0, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (launch_gather(L, p->mode, st) != hipSuccess) { rc = NB_E_HIP; break; }
         if (launch_forces(L, p->mode, 0, 0, g_force_grid.load(), st) != hipSuccess) { rc = NB_E_HIP; break; }
-        if (needs_partials(cfg) && launch_combine(L, p->mode, st) != hipSuccess) {
+        if (needs_partials(cfg) && launch_combine(L, p->mode, 0, 0, st) != hipSuccess) {
             rc = NB_E_HIP;
             break;
         }

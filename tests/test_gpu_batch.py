@@ -117,3 +117,34 @@ def test_batches_on_two_streams_concurrently():
     for m in mixes:
         for s in m:
             s.close()
+
+
+@pytest.mark.parametrize("mode,law", [("kahan", "contact"), ("kahan", "paper"), ("fp64", "contact")])
+def test_more_tiles_than_cus_and_split_calls(mode, law):
+    """More than 256 tiles in a launch (the combine's other form) with an empty system among them, three
+    steps in one call, against each system alone in three calls of one step: bitwise the same."""
+    nb = require_gpu()
+    sizes = [(33023, 0.5), (0, 0.5), (34049, 0.3), (900, 0.8)]
+    print_case("more tiles than CUs", sizes, mode, law)
+
+    def system(n, q):
+        if n == 0:
+            z = np.zeros((0, 3))
+            kw = {"eps": 1e-3, "gamma": 1.0, "beta": 0.5, "law": "paper"} if law == "paper" else {}
+            return nb.System(z, z, 0, G=1.0, m=1e-3, dt=1e-4, D1=0.01, D2=0.01, q=q, mode=mode, **kw)
+        ic = synth.with_velocity_noise(synth.make_binary(n, q, seed=n), 0.05, 5)
+        kw = synth.paper_law_params(ic) if law == "paper" else {}
+        return nb.System.from_ic(ic, mode=mode, **kw)
+
+    together, alone = [system(*s) for s in sizes], [system(*s) for s in sizes]
+    nb.nb_step([s.handle for s in together], 3, together[0].stream)
+    for a in alone:
+        for _ in range(3):
+            a.step(1)
+    for s, a in zip(together, alone):
+        for name in ("x", "y", "z", "vx", "vy", "vz", "ax", "ay", "az", "side"):
+            assert np.array_equal(getattr(s, name).cpu().numpy(), getattr(a, name).cpu().numpy()), name
+        d, e = s.diagnostics(), a.diagnostics()
+        assert d["step"] == e["step"] == 3 and d["n_past_L1"] == e["n_past_L1"]
+        s.close()
+        a.close()
