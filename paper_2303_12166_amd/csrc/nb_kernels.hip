@@ -1718,21 +1718,25 @@ __device__ __forceinline__ void one_sided_unit(SysRef S, int local, int step, in
     }
 }
 
+template <typename T, int LAW>
+union OneSidedMem {
+    T part[BT / 64][os_ib(sizeof(T) == 8, LAW)][3];
+    FinishMem fin;
+};
+
+// Workgroup `block` of the one-sided systems, whose force units end before `end`.
 template <typename T, int LAW, bool STEP>
-__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int last)
+__device__ __forceinline__ void one_sided_block(const Launch &L, int end, int block, int step, int last,
+                                                OneSidedMem<T, LAW> &sh)
 {
     constexpr int IB = os_ib(sizeof(T) == 8, LAW);
-    __shared__ union {
-        T part[BT / 64][IB][3];
-        FinishMem fin;
-    } sh;
     const int tid = threadIdx.x;
     const bool odd = (step & 1) != 0;
-    if (STEP && (int)blockIdx.x >= L.total_units) {
+    if (STEP && block >= end) {
         // the end of the step before: 256 elements' side of the L1 plane
-        SysRef S = cst(L.sys)[find_sys(L, (int)blockIdx.x - L.total_units, true)];
+        SysRef S = cst(L.sys)[find_sys(L, block - end, true)];
         if (!S.one_sided) return;  // an empty system
-        const int local = (int)blockIdx.x - L.total_units - S.ounit_begin;
+        const int local = block - end - S.ounit_begin;
         double v[7];
         sum_records(S, odd ? 0 : S.rec_len, S.n_rec, v, sh.fin.lds);
         if (tid == 0) plane_of(S, v, sh.fin.pl);
@@ -1744,9 +1748,8 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
                  log_row(S, cst(S.st)->step + step - 1) + 1);
         return;
     }
-    const int u = blockIdx.x;
-    SysRef S = cst(L.sys)[find_sys(L, u, false)];
-    const int local = u - S.unit_begin;
+    SysRef S = cst(L.sys)[find_sys(L, block, false)];
+    const int local = block - S.unit_begin;
     auto run = [&](auto ib) {
         one_sided_unit<T, LAW, STEP, decltype(ib)::value>(S, local, step, last, sh.part);
     };
@@ -1771,6 +1774,13 @@ __global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int 
         if constexpr (IB >= 8) run(Int<8>{});
         break;
     }
+}
+
+template <typename T, int LAW, bool STEP>
+__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int last)
+{
+    __shared__ OneSidedMem<T, LAW> sh;
+    one_sided_block<T, LAW, STEP>(L, L.total_units, blockIdx.x, step, last, sh);
 }
 
 // ------------------------------------------------------------------ symmetric force kernel: code
@@ -2099,6 +2109,33 @@ void k_force_rows(Launch L)
             for (int I0 = BAND * grp; I0 < min(S.ntiles, BAND * (grp + 1)); I0 += R)
                 rows_unit<T, LAW, R, BAND>(S, grp, I0, c, sh.mem, sh.red);
         }
+    }
+}
+
+// One step's forces of one-sided systems and of those in bands of one row, in one launch: the first
+// workgroups take a band unit each (`unit_base` to `total_units`), the others are the one-sided
+// kernel's. As two launches either drains before the other begins: 24 systems of 4,096 to 32,768
+// elements 1103 us a step as two, 1089 as one, four of 2,048 to 8,192 65 and 55, in FP64 118 and
+// 103. Not for FP64 under eqs. (4)-(6), where a band unit's 236 registers would leave the one-sided
+// workgroups two waves to a SIMD (32 systems of 2,048 to 8,192: 740 as two launches, 765 as one).
+template <typename T, int LAW>
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(rows_waves(sizeof(T) == 8, LAW, 1))))
+void k_force_mixed(Launch L, int step, int last)
+{
+    union Shared {
+        RowsMem<T> mem[LAW == 0 ? 4 : 8];
+        T red[4][3][TJ];
+        OneSidedMem<T, LAW> one;
+    };
+    __shared__ __attribute__((aligned(16))) char raw[sizeof(Shared)];
+    Shared &sh = *reinterpret_cast<Shared *>(raw);
+    const int u = L.unit_base + blockIdx.x;
+    if (u < L.total_units) {
+        SysRef S = cst(L.sys)[find_sys(L, u, false)];
+        const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
+        rows_unit<T, LAW, 1, 1>(S, gc[0], gc[0], gc[1], sh.mem, sh.red);
+    } else {
+        one_sided_block<T, LAW, true>(L, L.unit_base, u - L.total_units, step, last, sh.one);
     }
 }
 
@@ -2636,6 +2673,23 @@ hipError_t launch_forces(const Launch &L, int mode, int step, int last, int max_
         R.unit_base = begin;
         R.total_units = end;
         const dim3 g = grid(end - begin), blk(BT);
+        const int end1 = L.band_end[1], all = end1 + (step > 1 ? L.ounit_base : 0);
+        if (b == 0 && step > 0 && end1 > end && max_blocks <= 0 && !(mode == 2 && L.law != 0)) {
+            R.unit_base = end;
+            R.total_units = end1;
+            const dim3 gs(all);
+            if (mode == 2) {
+                hipLaunchKernelGGL((k_force_mixed<double, 0>), gs, blk, 0, s, R, step, last);
+            } else if (L.law == 0) {
+                hipLaunchKernelGGL((k_force_mixed<float, 0>), gs, blk, 0, s, R, step, last);
+            } else {
+                hipLaunchKernelGGL((k_force_mixed<float, 1>), gs, blk, 0, s, R, step, last);
+            }
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            begin = end1;
+            continue;
+        }
         if (b == 0) {
             // one workgroup per unit whatever the launch shape, and from a call's second step on
             // one per 256 elements for the end of the step before

@@ -75,9 +75,10 @@ size_t layout_total(int mode, int law, const TileCfg &c);
 // up to about 12,000 elements in FP32 (a step of 7,001: 23.8 us against 38 with the symmetric kernel,
 // 11,000: 48 and 52) and 7,100 in FP64 (4,096: 23.5 and 39.6, 7,001: 48.5 and 53). In a large
 // batch it only costs, twice the pairs (32 systems of 4,096 to 8,192 elements, all one-sided: 388
-// us a step in FP32 against 284, 1087 against 651 in FP64), so the limits lie where a large batch
-// loses little.
-constexpr int64_t ONE_SIDED_MAX[2][2] = {{7168, 7168}, {4608, 4608}};
+// us a step in FP32 against 284, 1087 against 651 in FP64), so the limits lie where such a batch
+// still takes no more than with the passes that every small system once had (350 us; 354 with these
+// limits, 723 and 657 in FP64, 518 and 517 under eqs. (4)-(6)).
+constexpr int64_t ONE_SIDED_MAX[2][2] = {{7168, 7168}, {4608, 3584}};
 
 int64_t one_sided_units(int64_t n, int64_t n1, int64_t ib)
 {
