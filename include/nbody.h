@@ -152,7 +152,7 @@ int nb_step(nb_system *const *sys, int32_t n_sys, int32_t n_steps, void *stream)
 
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): nb_step with the multi-system segment table kept in a fixed array of
- * NB_STATIC_MAX_SYS entries in each GPU's memory (76 KB, held by the library until the
+ * NB_STATIC_MAX_SYS entries in each GPU's memory (84 KB, held by the library until the
  * process ends) instead of a table the library allocates. The same work and bitwise the same
  * results as nb_step(sys, n_sys, n_steps, stream); any n_sys from 1 to NB_STATIC_MAX_SYS.
  * Allocates no device or host memory and synchronises nothing: the table is rewritten on the

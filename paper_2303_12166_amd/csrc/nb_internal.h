@@ -128,7 +128,8 @@ struct SysDesc {
     float *react;         // (double * in the FP64 mode)
     int32_t ch, sym;      // tiles per chunk; 1 when the symmetric kernel is used
     void *vxs, *vys, *vzs;  // sorted velocities (eqs. 4-6 and the symmetric kernels' steps)
-    void *as;               // sorted accelerations between a call's steps, 3 * nalloc (sym only)
+    void *as;               // sorted accelerations between a call's steps, 3 * nalloc (sym only; the
+                            // contact law: chunk 0 of `part`)
     int32_t law, rows;    // element law; tile rows per band (1 in the FP64 mode)
 };
 

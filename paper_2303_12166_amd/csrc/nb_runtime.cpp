@@ -250,13 +250,15 @@ Layout layout_for(int mode, int law, const TileCfg &c)
     L.xs = take((size_t)c.nalloc * elem);
     L.ys = take((size_t)c.nalloc * elem);
     L.zs = take((size_t)c.nalloc * elem);
-    // sorted velocities: eqs. (4)-(6) read them, and the steps of the symmetric kernels keep them and the
-    // accelerations sorted
+    // sorted velocities: eqs. (4)-(6) read them, and the steps of the symmetric kernels keep them and
+    // the accelerations sorted. Under the contact law the accelerations take the place of the first
+    // chunk's partials, which the combine has read by then and the next forces write anew; under eqs.
+    // (4)-(6) they have arrays of their own (that law's workspace is three sorted arrays larger).
     const bool vel = law == NB_LAW_PAPER || c.sym;
     L.vxs = take(vel ? (size_t)c.nalloc * elem : 0);
     L.vys = take(vel ? (size_t)c.nalloc * elem : 0);
     L.vzs = take(vel ? (size_t)c.nalloc * elem : 0);
-    L.as = take(c.sym ? (size_t)3 * (size_t)c.nalloc * elem : 0);
+    L.as = take(law == NB_LAW_PAPER && c.sym ? (size_t)3 * (size_t)c.nalloc * elem : 0);
     L.perm = take((size_t)c.nalloc * sizeof(int32_t));
     L.tbox = take((size_t)std::max(c.ntiles, 1) * 8 * sizeof(float));
     L.units = take(c.sym ? (size_t)c.n_units * 2 * sizeof(int32_t) : 0);
@@ -578,7 +580,7 @@ void fill_desc(SysDesc &d, const nb_params *p, const nb_buffers *b, const TileCf
     d.vxs = vel ? base + lay.vxs : nullptr;
     d.vys = vel ? base + lay.vys : nullptr;
     d.vzs = vel ? base + lay.vzs : nullptr;
-    d.as = cfg.sym ? base + lay.as : nullptr;
+    d.as = cfg.sym ? base + (paper ? lay.as : lay.part) : nullptr;
     d.law = p->law;
     d.perm = reinterpret_cast<int32_t *>(base + lay.perm);
     d.tbox = reinterpret_cast<float *>(base + lay.tbox);
