@@ -52,9 +52,18 @@ WORKLOADS = {
     "c4": dict(n=131072, q=0.8, mode="kahan", steps=200, warmup=5),
 }
 
-# force kernel of each mode; the FP32 Kahan kernels are instantiated per band height (%d)
-KERNEL_NAMES = {"kahan": "k_force_sym<%d>", "plain": "k_force_f32", "fp64": "k_force_sym64<0>"}
-PAPER_KERNEL_NAMES = {"kahan": "k_force_sym_paper<%d>", "fp64": "k_force_sym64<1>"}
+# the symmetric force kernel holds one or two tile rows at a time, by the band height; the plain mode
+# has a kernel of its own
+ROWS_HELD = {1: 1, 2: 2, 4: 2}
+
+
+def force_kernel(mode: str, law: int, rows: int) -> str:
+    if mode == "plain":
+        return "k_force_f32"
+    return "k_force_rows<%s, %d, %d, %d>" % ("double" if mode == "fp64" else "float", law,
+                                             ROWS_HELD[rows], rows)
+
+
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "force_counters.json")
 # the sources that decide the kernels' machine code: the kernels and their compile-time knobs
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2303_12166_amd", "csrc", f)
@@ -691,12 +700,10 @@ def main() -> int:
     peak = PEAK_FP64_TFLOPS if mode == "fp64" else PEAK_FP32_TFLOPS
     counters = counter_record(args.workload + (":paper" if law else ""), mode, cfg)
     achieved = FLOPS_PER_INTERACTION * inter / avg_s / 1e12 if avg_s > 0 else 0.0
-    kernel = (PAPER_KERNEL_NAMES if law else KERNEL_NAMES)[mode]
-    if "%d" in kernel:
-        kernel = kernel % cfg["rows"]
+    kernel = force_kernel(mode, 1 if law else 0, cfg["rows"])
     # pairs the kernel evaluates: N^2 / 2 with the symmetric kernels (each unordered pair once),
     # N^2 one-sided
-    evaluated = inter / 2 if kernel.startswith("k_force_sym") else inter
+    evaluated = inter / 2 if kernel.startswith("k_force_rows") else inter
     executed = FLOPS_PER_INTERACTION * evaluated / avg_s / 1e12 if avg_s > 0 else 0.0
     roofline = {
         "bound": "alu",

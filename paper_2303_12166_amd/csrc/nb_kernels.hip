@@ -5,8 +5,8 @@
 // the pair sum is not a dense contraction, so there is no MFMA here. The kernels that evaluate it:
 //   - k_force_rows<T, LAW, R, BAND> (FP32 Kahan and FP64 modes): each unordered pair once, 4 R i elements
 //     per lane in registers and the j sums rotating across the wave (see below);
-//   - k_force_one_sided<T, LAW> (the same modes, small systems): every ordered pair, in element
-//     order, with the second kick;
+//   - k_force_one_sided<T, LAW, STEP> (the same modes, small systems): every ordered pair, in element
+//     order, and in a step everything else of it; k_force_mixed runs both in one launch;
 //   - k_force_f32 (FP32, plain mode): one-sided, one i element per lane, the block streams
 //     256-element SoA j tiles through LDS (broadcast ds_read_b128), one FP32 running sum.
 // The first and the last work on a Morton-sorted, star-by-star padded copy of the positions and
@@ -122,7 +122,7 @@ constexpr double PI_D = 3.14159265358979323846;
 // around it, a wave that reaches one is picked at once and they pair up: the 15 instructions of a
 // contact-law pair issue at 94 lanes per clock per CU at four waves per SIMD and 98 at eight (81
 // and 83 without; 99 is what the parts allow: 14 at 115 and one at 32). The chip answers with a
-// lower clock (2.09 against 2.22 GHz in k_force_sym<4>), so at N = 262,144 the evaluation gains 3.6 %
+// lower clock (2.09 against 2.22 GHz in the symmetric kernel), so at N = 262,144 the evaluation gains 3.6 %
 // (10.95 -> 10.55 ms; eqs. (4)-(6) 14.67 -> 14.34), at 40,009 under eqs. (4)-(6) 5 %, and
 // k_force_f32 at N = 131,072, at two waves per SIMD, 13 % (8.12 -> 7.07 ms before its staging). s_setprio after the
 // transcendental is also the wait state that its first use needs.
