@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace nbk {
@@ -46,6 +47,14 @@ constexpr float SENTINEL_F32 = 1.0e18f;
 constexpr double SENTINEL_F64 = 1.0e150;
 constexpr float FAR_MARGIN = 2.0e-5f;  // relative margin on D^2 for the far-tile test
 
+// Squared gap in FP32 from which two boxes are far for the diameter D. Positions and diameters may be
+// in any unit: where D^2 leaves the range in which FP32 squares keep that margin, no gap is far.
+__host__ __device__ inline float far_limit(double D)
+{
+    const double d2 = D * D * (1.0 + (double)FAR_MARGIN);
+    return d2 > 1.0e-30 && d2 < 1.0e38 ? (float)d2 : INFINITY;
+}
+
 // Pair classes: 0 = star 1 with star 1, 1 = across the stars, 2 = star 2 with star 2.
 
 // What the donor growth changes: the donor's element diameter and the force constants that follow.
@@ -53,7 +62,7 @@ struct LawState {
     double D2;               // FP64 master
     double c1d[3], c2d[3];   // 11 / D^3 and 10 / D^2 per pair class
     float c1f[3], c2f[3];    // FP32 copies used by the FP32 kernels
-    float far2f[3];          // (1 + FAR_MARGIN) D^2 per pair class
+    float far2f[3];          // far_limit(D) per pair class
     float lD_f[3];           // D per pair class
     int32_t growth_stopped, pad;
 };

@@ -510,7 +510,8 @@ __device__ __forceinline__ bool far_tile(Const<float> *bx, const float (&lo)[3],
     const float gx = fmaxf(0.0f, fmaxf(bx[0] - hi[0], lo[0] - bx[4]));
     const float gy = fmaxf(0.0f, fmaxf(bx[1] - hi[1], lo[1] - bx[5]));
     const float gz = fmaxf(0.0f, fmaxf(bx[2] - hi[2], lo[2] - bx[6]));
-    const float gap2 = gx * gx + gy * gy + gz * gz;
+    // a square above FP32's range is still below a limit of infinity
+    const float gap2 = fminf(gx * gx + gy * gy + gz * gz, 3.0e38f);
     return __builtin_amdgcn_readfirstlane(gap2 >= far2 ? 1 : 0) != 0;
 }
 
@@ -1338,7 +1339,7 @@ __device__ __forceinline__ void grow(const DevState *st, const LawState *from, L
                 w.c2d[k] = 10.0 / (D * D);
                 w.c1f[k] = (float)w.c1d[k];
                 w.c2f[k] = (float)w.c2d[k];
-                w.far2f[k] = (float)(D * D * (1.0 + (double)FAR_MARGIN));
+                w.far2f[k] = far_limit(D);
                 w.lD_f[k] = (float)D;
             }
         } else {

@@ -632,7 +632,7 @@ void fill_state(DevState &init, const nb_params *p)
         init.cur.c2d[k] = 10.0 / (Ds[k] * Ds[k]);
         init.cur.c1f[k] = (float)init.cur.c1d[k];
         init.cur.c2f[k] = (float)init.cur.c2d[k];
-        init.cur.far2f[k] = (float)(Ds[k] * Ds[k] * (1.0 + (double)FAR_MARGIN));
+        init.cur.far2f[k] = far_limit(Ds[k]);
     }
     init.gm_d = p->G * p->m;
     init.h_d = 0.5 * p->dt;
