@@ -1854,46 +1854,75 @@ struct Rows {
 // The wave's 64 j against the elements [K0, K0 + NK) of every lane, with (REACT) their reaction added
 // to aj, or one-sided (a row's own tile, where the self pair is at step 0 of element K0 + wave).
 // vi: the elements' half-step velocities (eqs. 4-6, near form only).
+// Two rows in FP32: a reaction is summed in four runs of 16 steps (128 terms), added in order through
+// `runs`, because a running FP32 sum loses with its length what no later compensation brings back.
+// With one run of 512 terms the forces at 32,768 elements were off by 7.3e-8 of the largest (root
+// mean square; 6.6e-8 with the four waves' runs of 256 of the kernel before), so 4.3e-8, at the
+// same speed (10.17 and 10.15 ms a step at 262,144). One row's single run of 256 terms stays below
+// that kernel's error, and the same cut would cost it 2 % (700 -> 716 us, two steps of 40,009
+// elements under eqs. (4)-(6)).
 template <typename T, int LAW, int NI, int K0, int NK, bool NEAR, bool REACT, typename Law, typename V4>
 __device__ __forceinline__ void rows_tile(const RowsMem<T> &P, const RowsMem<T> &V, Rows<T, NI> &B,
                                           const Law *K, const V4 *vi, int lane, int wave,
-                                          T (&aj)[3])
+                                          T (*runs)[64], T (&aj)[3])
 {
     // (unrolled, the near form of eqs. (4)-(6) with its branches spills inside the loop)
     constexpr int U = LAW != 0 && NEAR ? 1 : (sizeof(T) == 4 ? 4 : 2);
+    constexpr int RUN = sizeof(T) == 4 && NI > 4 ? 16 : 64;  // steps
     const int rot_addr = ((lane + 63) & 63) << 2;  // byte address of lane l - 1 (mod 64)
+    T run[3] = {0, 0, 0};
     V4 p = P.get(lane + 64);
 #pragma unroll 1
-    for (int s0 = 0; s0 < 64; s0 += U) {
-        const int at = lane + 64 - s0 - U;
+    for (int q0 = 0; q0 < 64; q0 += RUN) {
+#pragma unroll 1
+        for (int s0 = q0; s0 < q0 + RUN; s0 += U) {
+            const int at = lane + 64 - s0 - U;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const V4 pn = P.get(at + U - u - 1);
-            V4 vj{};
-            if constexpr (LAW != 0 && NEAR) vj = V.get(at + U - u);
+            for (int u = 0; u < U; ++u) {
+                const V4 pn = P.get(at + U - u - 1);
+                V4 vj{};
+                if constexpr (LAW != 0 && NEAR) vj = V.get(at + U - u);
 #pragma unroll
-            for (int k = K0; k < K0 + NK; ++k) {
-                const T dx = p.x - B.x[k], dy = p.y - B.y[k], dz = p.z - B.z[k];
-                V4 v{};
-                if constexpr (LAW != 0 && NEAR) v = vi[k - K0];
-                T s = pair_at<LAW, NEAR>(dx, dy, dz, vj, v, K[k / 4]);
-                if constexpr (LAW != 0 && !REACT) s = u == 0 && s0 == 0 && k - K0 == wave ? (T)0 : s;
-                B.a[k][0] = fma_t(s, dx, B.a[k][0]);
-                B.a[k][1] = fma_t(s, dy, B.a[k][1]);
-                B.a[k][2] = fma_t(s, dz, B.a[k][2]);
-                if constexpr (REACT) {
-                    aj[0] = fma_t(s, dx, aj[0]);
-                    aj[1] = fma_t(s, dy, aj[1]);
-                    aj[2] = fma_t(s, dz, aj[2]);
+                for (int k = K0; k < K0 + NK; ++k) {
+                    const T dx = p.x - B.x[k], dy = p.y - B.y[k], dz = p.z - B.z[k];
+                    V4 v{};
+                    if constexpr (LAW != 0 && NEAR) v = vi[k - K0];
+                    T s = pair_at<LAW, NEAR>(dx, dy, dz, vj, v, K[k / 4]);
+                    if constexpr (LAW != 0 && !REACT)
+                        s = u == 0 && s0 == 0 && k - K0 == wave ? (T)0 : s;
+                    B.a[k][0] = fma_t(s, dx, B.a[k][0]);
+                    B.a[k][1] = fma_t(s, dy, B.a[k][1]);
+                    B.a[k][2] = fma_t(s, dz, B.a[k][2]);
+                    if constexpr (REACT) {
+                        run[0] = fma_t(s, dx, run[0]);
+                        run[1] = fma_t(s, dy, run[1]);
+                        run[2] = fma_t(s, dz, run[2]);
+                    }
+                    if constexpr (LAW == 0 && sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
                 }
-                if constexpr (LAW == 0 && sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (sizeof(T) == 4) asm volatile("" ::"v"(p.w));
-            if constexpr (REACT) {
+                if constexpr (sizeof(T) == 4) asm volatile("" ::"v"(p.w));
+                if constexpr (REACT) {
 #pragma unroll
-                for (int d = 0; d < 3; ++d) aj[d] = xbar_ror1(aj[d], rot_addr);
+                    for (int d = 0; d < 3; ++d) run[d] = xbar_ror1(run[d], rot_addr);
+                }
+                p = pn;
             }
-            p = pn;
+        }
+        if constexpr (REACT) {
+            // the lane holds the run of element l - q0 - RUN, in the end its own
+            const int e = (lane - q0 - RUN) & 63;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const T t = q0 == 0 ? run[d] : runs[d][e] + run[d];
+                if (q0 + RUN < 64) {
+                    runs[d][e] = t;
+                    run[d] = 0;
+                } else {
+                    aj[d] += t;
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
     }
 }
@@ -1903,7 +1932,8 @@ __device__ __forceinline__ void rows_tile(const RowsMem<T> &P, const RowsMem<T> 
 template <typename T, int LAW, int R, int r0, typename Law>
 __device__ __forceinline__ void near_rows(SysRef S, const RowsMem<T> &P,
                                           const RowsMem<T> &V, Rows<T, 4 * R> &B, const Law *K,
-                                          int I0, int k, int lane, int wave, T (&aj)[3])
+                                          int I0, int k, int lane, int wave, T (*runs)[64],
+                                          T (&aj)[3])
 {
     using V4 = typename Vec4<T>::type;
     if (r0 <= k) {
@@ -1921,19 +1951,20 @@ __device__ __forceinline__ void near_rows(SysRef S, const RowsMem<T> &P,
         if (r0 == k) {
             T none[3] = {0, 0, 0};
             rows_tile<T, LAW, 4 * R, 4 * r0, 4, true, false, Law, V4>(P, V, B, K, vi, lane, wave,
-                                                                      none);
+                                                                      runs, none);
         } else {
-            rows_tile<T, LAW, 4 * R, 4 * r0, 4, true, true, Law, V4>(P, V, B, K, vi, lane, wave, aj);
+            rows_tile<T, LAW, 4 * R, 4 * r0, 4, true, true, Law, V4>(P, V, B, K, vi, lane, wave,
+                                                                     runs, aj);
         }
     }
-    if constexpr (r0 + 1 < R) near_rows<T, LAW, R, r0 + 1>(S, P, V, B, K, I0, k, lane, wave, aj);
+    if constexpr (r0 + 1 < R) near_rows<T, LAW, R, r0 + 1>(S, P, V, B, K, I0, k, lane, wave, runs, aj);
 }
 
 // R rows of a unit: rows I0 .. I0 + R - 1 of band grp (BAND rows high) against chunk c of the band's
 // tiles. Where the band's rows before I0 have left reactions, these rows' are added to them.
 template <typename T, int LAW, int R, int BAND>
 __device__ __forceinline__ void rows_unit(SysRef S, int grp, int I0, int c, RowsMem<T> *mem,
-                                          T (*red)[3][TJ])
+                                          T (*runs)[3][64], T (*red)[3][TJ])
 {
     constexpr int NI = 4 * R;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -2025,12 +2056,14 @@ __device__ __forceinline__ void rows_unit(SysRef S, int grp, int I0, int c, Rows
         }
         if (k >= R && far_tile(cst(S.tbox) + (size_t)t * 8, lo, hi,
                                jstar ? far2b : far2a)) {
-            rows_tile<T, LAW, NI, 0, NI, false, true, Law, V4>(P, V, B, K, nullptr, lane, wave, aj);
+            rows_tile<T, LAW, NI, 0, NI, false, true, Law, V4>(P, V, B, K, nullptr, lane, wave,
+                                                                 runs[wave], aj);
         } else if (LAW == 0 && k >= R) {
-            rows_tile<T, LAW, NI, 0, NI, true, true, Law, V4>(P, V, B, K, nullptr, lane, wave, aj);
+            rows_tile<T, LAW, NI, 0, NI, true, true, Law, V4>(P, V, B, K, nullptr, lane, wave,
+                                                                 runs[wave], aj);
         } else {
             // one row at a time, so that only a row's velocities are held
-            near_rows<T, LAW, R, 0>(S, P, V, B, K, I0, k, lane, wave, aj);
+            near_rows<T, LAW, R, 0>(S, P, V, B, K, I0, k, lane, wave, runs[wave], aj);
         }
         if (k > 0) {
 #pragma unroll
@@ -2094,7 +2127,10 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(rows_waves(s
 void k_force_rows(Launch L)
 {
     union Shared {
-        RowsMem<T> mem[LAW == 0 ? 4 : 8];
+        struct {
+            RowsMem<T> mem[LAW == 0 ? 4 : 8];
+            T runs[4][3][64];
+        } w;
         T red[4][3][TJ];
     };
     __shared__ __attribute__((aligned(16))) char raw[sizeof(Shared)];
@@ -2104,11 +2140,11 @@ void k_force_rows(Launch L)
         const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
         const int grp = gc[0], c = gc[1];
         if constexpr (BAND == R) {
-            rows_unit<T, LAW, R, BAND>(S, grp, R * grp, c, sh.mem, sh.red);
+            rows_unit<T, LAW, R, BAND>(S, grp, R * grp, c, sh.w.mem, sh.w.runs, sh.red);
         } else {
 #pragma unroll 1
             for (int I0 = BAND * grp; I0 < min(S.ntiles, BAND * (grp + 1)); I0 += R)
-                rows_unit<T, LAW, R, BAND>(S, grp, I0, c, sh.mem, sh.red);
+                rows_unit<T, LAW, R, BAND>(S, grp, I0, c, sh.w.mem, sh.w.runs, sh.red);
         }
     }
 }
@@ -2124,7 +2160,10 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(rows_waves(s
 void k_force_mixed(Launch L, int step, int last)
 {
     union Shared {
-        RowsMem<T> mem[LAW == 0 ? 4 : 8];
+        struct {
+            RowsMem<T> mem[LAW == 0 ? 4 : 8];
+            T runs[4][3][64];
+        } w;
         T red[4][3][TJ];
         OneSidedMem<T, LAW> one;
     };
@@ -2134,7 +2173,7 @@ void k_force_mixed(Launch L, int step, int last)
     if (u < L.total_units) {
         SysRef S = cst(L.sys)[find_sys(L, u, false)];
         const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
-        rows_unit<T, LAW, 1, 1>(S, gc[0], gc[0], gc[1], sh.mem, sh.red);
+        rows_unit<T, LAW, 1, 1>(S, gc[0], gc[0], gc[1], sh.w.mem, sh.w.runs, sh.red);
     } else {
         one_sided_block<T, LAW, true>(L, L.unit_base, u - L.total_units, step, last, sh.one);
     }
