@@ -205,18 +205,20 @@ __global__ __launch_bounds__(BT) void k_zero_sorted(T *xs, T *ys, T *zs, int nal
 // tile, its prefix sums per digit, and the scatter. The arrays it works in are those of the sorted
 // copy, which is rebuilt before anything reads it. Launches bound it (fifteen, a few microseconds
 // each) up to some 100,000 elements; a read-back and a comparison sort on the host took 1.37 ms at
-// 32,768 elements and 13.2 ms at 262,144 (nb_resort), this 0.08 and 0.09.
+// 32,768 elements and 13.2 ms at 262,144 (nb_resort), this 0.08 and 0.09. Systems of one sort tile take
+// one launch (k_sort_small).
 
-// Per workgroup: each star's smallest and largest finite coordinates.
+// Each star's smallest and largest finite coordinates (per star: min x, y, z, then -max x, y, z) over
+// the elements i0, i0 + stride, .. of every thread. Called by a whole workgroup; the
+// result is in `box`, written by its first twelve threads.
 template <typename T>
-__global__ __launch_bounds__(BT) void k_sort_bounds(const T *x, const T *y, const T *z, int n, int n1,
-                                                    double *out)
+__device__ __forceinline__ void star_bounds(const T *x, const T *y, const T *z, int n, int n1, int i0,
+                                            int stride, double (*lds)[BT / 64], double *box)
 {
-    __shared__ double lds[12][BT / 64];
-    double v[12];  // per star: min x, y, z, then -max x, y, z
+    double v[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) v[k] = 1e300;
-    for (int i = blockIdx.x * BT + threadIdx.x; i < n; i += gridDim.x * BT) {
+    for (int i = i0; i < n; i += stride) {
         const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -239,8 +241,17 @@ __global__ __launch_bounds__(BT) void k_sort_bounds(const T *x, const T *y, cons
     __syncthreads();
     if (threadIdx.x < 12) {
         const int k = threadIdx.x;
-        out[12 * blockIdx.x + k] = fmin(fmin(lds[k][0], lds[k][1]), fmin(lds[k][2], lds[k][3]));
+        box[k] = fmin(fmin(lds[k][0], lds[k][1]), fmin(lds[k][2], lds[k][3]));
     }
+}
+
+template <typename T>
+__global__ __launch_bounds__(BT) void k_sort_bounds(const T *x, const T *y, const T *z, int n, int n1,
+                                                    double *out)
+{
+    __shared__ double lds[12][BT / 64];
+    star_bounds(x, y, z, n, n1, blockIdx.x * BT + threadIdx.x, gridDim.x * BT, lds,
+                out + 12 * blockIdx.x);
 }
 
 __device__ __forceinline__ uint32_t spread10(uint32_t v)
@@ -251,6 +262,24 @@ __device__ __forceinline__ uint32_t spread10(uint32_t v)
     v = (v | (v << 4)) & 0x030c30c3u;
     v = (v | (v << 2)) & 0x09249249u;
     return v;
+}
+
+// Star and Morton code of a position inside its star's box.
+__device__ __forceinline__ uint32_t sort_key(double x, double y, double z, int star, const double *box)
+{
+    const double p[3] = {x, y, z};
+    uint32_t key = (uint32_t)star << 30;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double lo = box[6 * star + d], hi = -box[6 * star + 3 + d];
+        const double span = hi > lo ? hi - lo : 1.0;
+        double f = isfinite(p[d]) ? (p[d] - lo) / span : 0.0;
+        f = f < 0.0 ? 0.0 : f;
+        f = 1.0 < f ? 1.0 : f;
+        f = f * 1024.0;
+        key |= spread10((uint32_t)(f < 1023.0 ? f : 1023.0)) << d;
+    }
+    return key;
 }
 
 template <typename T>
@@ -273,21 +302,7 @@ __global__ __launch_bounds__(BT) void k_sort_keys(const T *x, const T *y, const 
     }
     __syncthreads();
     const int i = blockIdx.x * BT + threadIdx.x;
-    if (i >= n) return;
-    const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
-    const int star = i >= n1 ? 1 : 0;
-    uint32_t key = (uint32_t)star << 30;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const double lo = box[6 * star + d], hi = -box[6 * star + 3 + d];
-        const double span = hi > lo ? hi - lo : 1.0;
-        double f = isfinite(p[d]) ? (p[d] - lo) / span : 0.0;
-        f = f < 0.0 ? 0.0 : f;
-        f = 1.0 < f ? 1.0 : f;
-        f = f * 1024.0;
-        key |= spread10((uint32_t)(f < 1023.0 ? f : 1023.0)) << d;
-    }
-    keys[i] = key;
+    if (i < n) keys[i] = sort_key((double)x[i], (double)y[i], (double)z[i], i >= n1 ? 1 : 0, box);
 }
 
 // Digit counts of one tile, stored digit by digit (entry digit n_tiles + tile).
@@ -343,9 +358,28 @@ __global__ __launch_bounds__(BT) void k_sort_scan(uint32_t *hist, int n_tiles, u
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
+// The place of this lane's element (none: not `valid`) among the wave's elements of the same digit, of
+// which `at` holds the next free place: the lanes before it that hold the same digit come first.
+__device__ __forceinline__ uint32_t next_place(volatile uint32_t *at, uint32_t digit, bool valid,
+                                               int lane)
+{
+    unsigned long long same = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const unsigned long long one = __ballot((digit >> b) & 1u);
+        same &= (digit >> b) & 1u ? one : ~one;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    uint32_t pos = 0;
+    if (valid) pos = at[digit] + rank;
+    __builtin_amdgcn_wave_barrier();
+    if (valid && rank == 0) at[digit] = pos + __popcll(same);
+    __builtin_amdgcn_wave_barrier();
+    return pos;
+}
+
 // Moves one tile's elements to their places, in order within a digit: every wave takes a run of the
-// tile, 64 elements at a time, an element's place among equal digits of the 64 being the number
-// of lanes before it that hold the same one. vals_in null: the index itself (first pass). keys_out
+// tile, 64 elements at a time (next_place). vals_in null: the index itself (first pass). keys_out
 // null: the last pass, where the values become the order of the slots.
 __global__ __launch_bounds__(BT) void k_sort_scatter(const uint32_t *keys_in, const int32_t *vals_in,
                                                      uint32_t *keys_out, int32_t *vals_out, int n,
@@ -381,18 +415,7 @@ __global__ __launch_bounds__(BT) void k_sort_scatter(const uint32_t *keys_in, co
         const int i = base + 64 * r + lane;
         const bool valid = i < n;
         const uint32_t digit = (key[r] >> shift) & 255u;
-        unsigned long long same = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const unsigned long long one = __ballot((digit >> b) & 1u);
-            same &= (digit >> b) & 1u ? one : ~one;
-        }
-        const int rank = __popcll(same & ((1ull << lane) - 1ull));
-        uint32_t pos = 0;
-        if (valid) pos = at[wave][digit] + rank;
-        __builtin_amdgcn_wave_barrier();
-        if (valid && rank == 0) at[wave][digit] = pos + __popcll(same);
-        __builtin_amdgcn_wave_barrier();
+        const uint32_t pos = next_place(at[wave], digit, valid, lane);
         if (valid) {
             const int32_t val = vals_in ? vals_in[i] : i;
             if (keys_out) {
@@ -402,6 +425,84 @@ __global__ __launch_bounds__(BT) void k_sort_scatter(const uint32_t *keys_in, co
                 vals_out[(int)pos < n1 ? pos : p1 + (pos - n1)] = val;
             }
         }
+    }
+}
+
+// The whole order of a system of at most one sort tile, with what k_reset_sorted does, by one workgroup:
+// the same passes in LDS. As fifteen launches nb_resort took 85 us at 64 to 2,048 elements, more
+// than the host's sort below 1,500 (60 us at 64).
+template <typename T>
+__global__ __launch_bounds__(BT) void k_sort_small(const T *x, const T *y, const T *z, int n, int n1,
+                                                   int p1, int nalloc, T *xs, T *ys, T *zs,
+                                                   int32_t *perm, T value)
+{
+    constexpr int ROWS = SORT_TILE / BT;
+    __shared__ double lds[12][BT / 64];
+    __shared__ double box[12];
+    __shared__ uint32_t wsum[BT / 64];
+    __shared__ volatile uint32_t at[BT / 64][256];
+    __shared__ uint32_t keys[SORT_TILE], vals[SORT_TILE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int base = wave * (SORT_TILE / 4);
+    star_bounds(x, y, z, n, n1, tid, BT, lds, box);
+    __syncthreads();
+    uint32_t key[ROWS], val[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int i = base + 64 * r + lane;
+        key[r] = i < n ? sort_key((double)x[i], (double)y[i], (double)z[i], i >= n1 ? 1 : 0, box) : 0u;
+        val[r] = i;
+    }
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = 8 * pass;
+#pragma unroll
+        for (int w = 0; w < BT / 64; ++w) at[w][tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if (base + 64 * r + lane < n)
+                atomicAdd(const_cast<uint32_t *>(&at[wave][(key[r] >> shift) & 255u]), 1u);
+        }
+        __syncthreads();
+        uint32_t count = 0, total;
+#pragma unroll
+        for (int w = 0; w < BT / 64; ++w) count += at[w][tid];
+        uint32_t place = scan256(count, wsum, total);
+#pragma unroll
+        for (int w = 0; w < BT / 64; ++w) {
+            const uint32_t c = at[w][tid];
+            at[w][tid] = place;
+            place += c;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const bool valid = base + 64 * r + lane < n;
+            const uint32_t pos = next_place(at[wave], (key[r] >> shift) & 255u, valid, lane);
+            if (!valid) continue;
+            if (pass < 3) {
+                keys[pos] = key[r];
+                vals[pos] = val[r];
+            } else {
+                perm[(int)pos < n1 ? pos : p1 + (pos - n1)] = (int32_t)val[r];
+            }
+        }
+        if (pass == 3) break;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int i = base + 64 * r + lane;
+            if (i < n) {
+                key[r] = keys[i];
+                val[r] = vals[i];
+            }
+        }
+    }
+    for (int k = tid; k < nalloc; k += BT) {
+        xs[k] = value;
+        ys[k] = value;
+        zs[k] = value;
+        if ((k >= n1 && k < p1) || k >= p1 + (n - n1)) perm[k] = -1;
     }
 }
 
@@ -2655,8 +2756,25 @@ static void sort_keys(const SysDesc &d, double *bounds, uint32_t *keys, hipStrea
                        keys);
 }
 
+template <typename T>
+static void sort_small(const SysDesc &d, T value, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_sort_small<T>, dim3(1), dim3(BT), 0, s, static_cast<const T *>(d.x),
+                       static_cast<const T *>(d.y), static_cast<const T *>(d.z), d.n, d.n1, d.p1,
+                       d.nalloc, static_cast<T *>(d.xs), static_cast<T *>(d.ys), static_cast<T *>(d.zs),
+                       d.perm, value);
+}
+
 hipError_t launch_sort(const SysDesc &d, int mode, void *work, hipStream_t s)
 {
+    if (d.n > 0 && d.n <= SORT_TILE) {
+        if (mode == 2) {
+            sort_small<double>(d, SENTINEL_F64, s);
+        } else {
+            sort_small<float>(d, SENTINEL_F32, s);
+        }
+        return hipGetLastError();
+    }
     if (d.n > 0) {
         double *bounds = static_cast<double *>(work);
         uint32_t *totals = reinterpret_cast<uint32_t *>(bounds + 12 * SORT_BOUNDS);

@@ -87,3 +87,12 @@ def test_order_is_the_stable_morton_order(n, n1, kind, mode):
     s.resort()
     assert np.array_equal(nb.nb_sorted_order(s.handle, s.stream), _reference(moved, n1))
     s.close()
+
+
+@pytest.mark.parametrize("mode", ["kahan", "fp64"])
+@pytest.mark.parametrize("n,n1,kind", [
+    (2, 1, "plain"), (65, 64, "ties"), (512, 0, "flat"), (513, 300, "ties"), (1023, 511, "non-finite"),
+    (1536, 1025, "range"), (1537, 3, "ties"), (2047, 2000, "non-finite"), (2048, 1, "ties")])
+def test_order_of_one_sort_tile(n, n1, kind, mode):
+    """Systems of at most 2048 elements are sorted by one workgroup: edges of its waves' 512 elements."""
+    test_order_is_the_stable_morton_order(n, n1, kind, mode)
