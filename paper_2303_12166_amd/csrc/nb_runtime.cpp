@@ -205,8 +205,11 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
     }
     finish_split(c, n, n1, mode, law, ns, rows);
     // over the workspace budget: taller bands first (FP32 Kahan), then fewer, longer chunks,
-    // until the layout fits or cannot shrink further
-    while (budget > 0 && c.sym && c.n_units >= 0 && layout_total(mode, law, c) > budget) {
+    // until the layout fits or cannot shrink further (a small system leaves the one-sided kernel
+    // with the first of them, and keeps it where no symmetric layout fits or is smaller)
+    const TileCfg asked = c;
+    while (budget > 0 && (c.sym || c.one_sided) && c.n_units >= 0 &&
+           layout_total(mode, law, c) > budget) {
         if (mode == NB_FP32_KAHAN && c.rows < MAX_BAND) {
             finish_split(c, n, n1, mode, law, c.nsplit, c.rows * 2);
         } else if (c.nsplit > 1) {
@@ -215,6 +218,9 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
             break;
         }
     }
+    if (asked.one_sided && !c.one_sided && layout_total(mode, law, c) > budget &&
+        layout_total(mode, law, asked) <= layout_total(mode, law, c))
+        return asked;
     return c;
 }
 

@@ -301,3 +301,34 @@ def test_huge_systems_report_nomem_instead_of_overflowing(nb):
         with pytest.raises(nb.NbError) as e:
             nb.nb_scratch_bytes(_params(nb, mode=mode, **big))
         assert e.value.status == nb.NB_E_NOMEM
+
+
+@pytest.mark.parametrize("mode,law,n", [("kahan", "contact", 300), ("kahan", "contact", 2048),
+                                        ("kahan", "contact", 7001), ("kahan", "paper", 3001),
+                                        ("fp64", "contact", 2048), ("fp64", "contact", 3000),
+                                        ("fp64", "paper", 2001)])
+def test_workspace_budget_of_small_systems(nb, mode, law, n):
+    """Small systems in their finest split (the one-sided kernel's) follow the budget too: coarsened until
+    they fit or to the smallest workspace of any split, and the requested split without one."""
+    M, W = nb.MODES[mode], nb.LAWS[law]
+    p = _params(nb, n=n, n1=n - n // 3, mode=M, law=W,
+                **(dict(eps=0.001, gamma=1.0, beta=0.5) if law == "paper" else {}))
+
+    def bytes_of(nsplit, rows):
+        nb.nb_tile_override(n, n, M, nsplit, rows, law=W)
+        return nb.nb_scratch_bytes(p)
+
+    try:
+        least = min(bytes_of(ns, rows) for ns in (1, 2, 4, 8, 4096)
+                    for rows in ((1, 2, 4) if mode == "kahan" else (1,)))
+        full = bytes_of(4096, 1)  # one tile per chunk
+        for budget in (1, least - 1, least, (least + full) // 2, full):
+            nb.nb_set_workspace_budget(budget)
+            got = nb.nb_scratch_bytes(p)
+            assert got <= budget or got == least, (budget, got, least, full)
+            assert budget < full or got == full
+        nb.nb_set_workspace_budget(0)
+        assert nb.nb_scratch_bytes(p) == full
+    finally:
+        nb.nb_set_workspace_budget(0)
+        nb.nb_tile_override(n, n, M, 0, 1, law=W)
