@@ -1878,11 +1878,32 @@ __device__ __forceinline__ void one_sided_block(const Launch &L, int end, int bl
     }
 }
 
-template <typename T, int LAW, bool STEP>
-__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int last)
+// LOOP: a persistent launch, each workgroup takes units blockIdx, blockIdx + grid, .. of `total`. A kernel
+// of its own: the loop costs 15 to 33 registers, a wave per SIMD.
+template <typename T, int LAW, bool STEP, bool LOOP>
+__global__ __launch_bounds__(BT) void k_force_one_sided(Launch L, int step, int last, int total)
 {
     __shared__ OneSidedMem<T, LAW> sh;
-    one_sided_block<T, LAW, STEP>(L, L.total_units, blockIdx.x, step, last, sh);
+    if constexpr (LOOP) {
+        for (int b = blockIdx.x; b < total; b += gridDim.x) {
+            one_sided_block<T, LAW, STEP>(L, L.total_units, b, step, last, sh);
+            __syncthreads();  // sh is rewritten by the next
+        }
+    } else {
+        one_sided_block<T, LAW, STEP>(L, L.total_units, blockIdx.x, step, last, sh);
+    }
+}
+
+template <typename T, int LAW>
+static hipError_t launch_one_sided(const Launch &L, int step, int last, int max_blocks, hipStream_t s)
+{
+    // from a call's second step on also one unit per 256 elements for the end of the step before
+    const int total = L.total_units + (step > 1 ? L.ounit_base : 0);
+    const bool loop = max_blocks > 0 && max_blocks < total;
+    const auto k = step > 0 ? (loop ? k_force_one_sided<T, LAW, true, true> : k_force_one_sided<T, LAW, true, false>)
+                            : (loop ? k_force_one_sided<T, LAW, false, true> : k_force_one_sided<T, LAW, false, false>);
+    hipLaunchKernelGGL(k, dim3(loop ? max_blocks : total), dim3(BT), 0, s, L, step, last, total);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ symmetric force kernel: code
@@ -2849,20 +2870,13 @@ hipError_t launch_forces(const Launch &L, int mode, int step, int last, int max_
             continue;
         }
         if (b == 0) {
-            // one workgroup per unit whatever the launch shape, and from a call's second step on
-            // one per 256 elements for the end of the step before
             if (mode == 0) return hipErrorInvalidValue;
-            const dim3 gs(end + (step > 1 ? L.ounit_base : 0));
-            switch ((mode == 2 ? 4 : 0) + L.law * 2 + (step > 0 ? 1 : 0)) {
-            case 0: hipLaunchKernelGGL((k_force_one_sided<float, 0, false>), gs, blk, 0, s, R, 0, 0); break;
-            case 1: hipLaunchKernelGGL((k_force_one_sided<float, 0, true>), gs, blk, 0, s, R, step, last); break;
-            case 2: hipLaunchKernelGGL((k_force_one_sided<float, 1, false>), gs, blk, 0, s, R, 0, 0); break;
-            case 3: hipLaunchKernelGGL((k_force_one_sided<float, 1, true>), gs, blk, 0, s, R, step, last); break;
-            case 4: hipLaunchKernelGGL((k_force_one_sided<double, 0, false>), gs, blk, 0, s, R, 0, 0); break;
-            case 5: hipLaunchKernelGGL((k_force_one_sided<double, 0, true>), gs, blk, 0, s, R, step, last); break;
-            case 6: hipLaunchKernelGGL((k_force_one_sided<double, 1, false>), gs, blk, 0, s, R, 0, 0); break;
-            default: hipLaunchKernelGGL((k_force_one_sided<double, 1, true>), gs, blk, 0, s, R, step, last); break;
-            }
+            const hipError_t e =
+                mode == 2 ? (L.law == 0 ? launch_one_sided<double, 0>(R, step, last, max_blocks, s)
+                                        : launch_one_sided<double, 1>(R, step, last, max_blocks, s))
+                          : (L.law == 0 ? launch_one_sided<float, 0>(R, step, last, max_blocks, s)
+                                        : launch_one_sided<float, 1>(R, step, last, max_blocks, s));
+            if (e != hipSuccess) return e;
         } else if (mode == 0) {
             if (L.law != 0 || b != 1) return hipErrorInvalidValue;  // no eqs. (4)-(6), no bands
             if (end - begin > CU_COUNT) {
