@@ -71,14 +71,19 @@ struct Layout;
 Layout layout_for(int mode, int law, const TileCfg &c);
 size_t layout_total(int mode, int law, const TileCfg &c);
 
-// Largest systems of the one-sided force kernel, by FP64 mode and element law. Alone, a system gains
-// up to about 12,000 elements in FP32 (a step of 7,001: 23.8 us against 38 with the symmetric kernel,
-// 11,000: 48 and 52) and 7,100 in FP64 (4,096: 23.5 and 39.6, 7,001: 48.5 and 53). In a large
-// batch it only costs, twice the pairs (32 systems of 4,096 to 8,192 elements, all one-sided: 388
-// us a step in FP32 against 284, 1087 against 651 in FP64), so the limits lie where such a batch
-// still takes no more than with the passes that every small system once had (350 us; 354 with these
-// limits, 723 and 657 in FP64, 518 and 517 under eqs. (4)-(6)).
-constexpr int64_t ONE_SIDED_MAX[2][2] = {{7168, 7168}, {4608, 3584}};
+// Largest systems of the one-sided force kernel, by FP64 mode and element law. It evaluates every pair
+// twice, and a system's kernel is fixed by its size (its sums have to be the same alone and in any
+// batch), so each limit trades a system alone against large batches. Steps in us, one-sided and with
+// the symmetric kernels (graphs of five steps):
+//   alone            FP32 2,048 12 and 32, 7,168 31 and 38; FP64 2,048 15 and 37, 4,096 25 and 40
+//   32 of one size   FP32 2,048 77 and 70, 7,168 512 and 368; FP64 2,048 174 and 118, 4,096 478 and 310
+// FP64: a batch of 32 systems spread over 2,048 to 8,192 elements takes no longer than the passes that
+// every system once had (430 us; 419 with the limit at 4,096, 453 at 4,608. Eqs. (4)-(6) 557; 532
+// with 2,560, 542 with 3,584, and 32 of 2,048 to 4,096 elements 322; 312 with 2,560, 365 with 3,072).
+// FP32: that batch takes 4 to 7 % longer than it once did (248; 259 with 7,168, 232 with 6,144, 188
+// without the kernel; eqs. (4)-(6) 362; 386, 333, 231), which is accepted for the fifth
+// to third that a system of 6,145 to 7,168 elements saves alone.
+constexpr int64_t ONE_SIDED_MAX[2][2] = {{7168, 7168}, {4096, 2560}};
 
 int64_t one_sided_units(int64_t n, int64_t n1, int64_t ib)
 {

@@ -332,3 +332,22 @@ def test_workspace_budget_of_small_systems(nb, mode, law, n):
     finally:
         nb.nb_set_workspace_budget(0)
         nb.nb_tile_override(n, n, M, 0, 1, law=W)
+
+
+@pytest.mark.parametrize("mode,law,limit", [("kahan", "contact", 7168), ("kahan", "paper", 7168),
+                                            ("fp64", "contact", 4096), ("fp64", "paper", 2560)])
+def test_one_sided_limits(nb, mode, law, limit):
+    """The largest system of the one-sided kernel, by its workspace in the finest split: the symmetric
+    kernels' chunk partials alone (one tile per chunk) are larger than all of the one-sided layout."""
+    M, W = nb.MODES[mode], nb.LAWS[law]
+    kw = dict(eps=0.001, gamma=1.0, beta=0.5) if law == "paper" else {}
+    for n in (limit, limit + 1):
+        n1 = n - n // 3
+        tiles = -(-n1 // 256) + -(-(n - n1) // 256)
+        partials = tiles * 3 * tiles * 256 * (8 if mode == "fp64" else 4)
+        nb.nb_tile_override(n, n, M, 4096, 1, law=W)
+        try:
+            need = nb.nb_scratch_bytes(_params(nb, n=n, n1=n1, mode=M, law=W, **kw))
+        finally:
+            nb.nb_tile_override(n, n, M, 0, 1, law=W)
+        assert (need < partials) == (n <= limit), (n, need, partials)
