@@ -57,7 +57,10 @@ class System:
             # one upload of the rows, turned into three contiguous columns on the device
             if not n:
                 return [torch.zeros(1, **k) for _ in range(3)]
-            rows = torch.from_numpy(np.ascontiguousarray(a[:, :3])).to(self.device)
+            host = np.ascontiguousarray(a[:, :3])
+            if not host.flags.writeable:  # torch warns of such an array
+                host = host.copy()
+            rows = torch.from_numpy(host).to(self.device)
             return list(rows.t().to(dtype).contiguous())
 
         # every upload and allocation is ordered on the system's stream
