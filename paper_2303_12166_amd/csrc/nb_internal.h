@@ -22,7 +22,7 @@ constexpr int CU_COUNT = 256;    // compute units of the card
 constexpr int BT = 256;          // threads per block, every kernel
 constexpr int TJ = 256;          // j elements staged in LDS per tile (one per thread)
 constexpr int MAX_BAND = 4;      // tallest band of the FP32 symmetric kernel (tile rows per lane)
-constexpr int RED_STRIDE = 32;   // doubles per O(N)-unit partial record of the read-backs
+constexpr int RED_STRIDE = 16;   // doubles per O(N)-unit partial record of the read-backs
 constexpr int REC_STRIDE = 8;    // doubles per record of a step (position sums, non-finite count)
 constexpr int COM_FUSE_UNITS = 256;  // largest system (in units of 256 elements) whose records
                                      // every workgroup of k_advance sums for itself
@@ -31,8 +31,8 @@ constexpr int COM_FUSE_UNITS = 256;  // largest system (in units of 256 elements
 constexpr int os_ib(bool fp64, int law) { return fp64 ? 4 : (law == 0 ? 8 : 7); }
 constexpr int KERNEL_CLASSES = 4;    // force kernels of a launch: one-sided, bands of 1, 2, 4 rows
 constexpr int ADV_INIT = 2;      // k_advance: record the sides at creation
-constexpr int RED_DIAG = 16;     // record slots [16, 32): diagnostics sums
-constexpr int RED_RET = 26;      // record slots [26, 31): retention sums (after the diagnostics)
+constexpr int RED_DIAG = 0;      // record slots [0, 10): diagnostics sums
+constexpr int RED_RET = 10;      // record slots [10, 15): retention sums
 constexpr int SORT_TILE = 2048;  // elements per workgroup of a pass of the order's sort
 constexpr int SORT_BOUNDS = 64;  // most workgroups that find the stars' bounding boxes
 constexpr size_t sort_work_bytes(int64_t n)
@@ -111,7 +111,7 @@ struct SysDesc {
     void *xs, *ys, *zs;   // sorted positions, nalloc slots
     int32_t *perm;        // nalloc: element index of each sorted slot, -1 for padding
     float *tbox;          // ntiles * 8: min xyz, pad, max xyz, pad of each j tile
-    void *part;         // j-split partial sums, nsplit * 3 * nalloc values (nsplit > 1 only)
+    void *part;         // chunk partial sums, nsplit * 3 * nalloc values (symmetric kernels only)
     double *red;        // n_ounits * RED_STRIDE doubles
     double *rec;        // records of a step, rec_len * REC_STRIDE doubles (one-sided: twice, the
                         // second for odd steps of a call)

@@ -691,10 +691,9 @@ __device__ __forceinline__ void plain_tile(const float *sx, const float *sy, con
 }
 
 // One force unit of the plain mode: the 256 elements from ib 256 in sorted order without padding, one
-// per lane, against j chunk `c` (a run of whole tiles), one running FP32 sum per element in tile
-// order.
+// per lane, against every tile, one running FP32 sum per element in tile order.
 template <bool PRIO>
-__device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c, float (*sh)[3][TJ])
+__device__ __forceinline__ void force_unit_f32(SysRef S, int ib, float (*sh)[3][TJ])
 {
     const int tid = threadIdx.x;
     auto *__restrict__ XS = glob<const float>(S.xs);
@@ -724,22 +723,15 @@ __device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c, float (*
     float eps;  // in a vector register: a literal halves the issue rate
     asm("v_mov_b32 %0, 0x179abe15" : "=v"(eps));  // 1e-24
 
-    // chunk c covers tiles [c ntiles / nsplit, (c + 1) ntiles / nsplit): sizes differ by <= 1
-    const int t0 = (int)(((int64_t)c * S.ntiles) / S.nsplit);
-    const int t1 = (int)(((int64_t)(c + 1) * S.ntiles) / S.nsplit);
-    float px = 0.f, py = 0.f, pz = 0.f;
-    if (t0 < t1) {
-        px = XS[t0 * TJ + tid];
-        py = YS[t0 * TJ + tid];
-        pz = ZS[t0 * TJ + tid];
-    }
-    for (int t = t0; t < t1; ++t) {
-        const int buf = (t - t0) & 1;
+    const int ntiles = S.ntiles;
+    float px = XS[tid], py = YS[tid], pz = ZS[tid];
+    for (int t = 0; t < ntiles; ++t) {
+        const int buf = t & 1;
         sh[buf][0][tid] = px;
         sh[buf][1][tid] = py;
         sh[buf][2][tid] = pz;
         __syncthreads();
-        if (t + 1 < t1) {
+        if (t + 1 < ntiles) {
             px = XS[(t + 1) * TJ + tid];
             py = YS[(t + 1) * TJ + tid];
             pz = ZS[(t + 1) * TJ + tid];
@@ -756,20 +748,11 @@ __device__ __forceinline__ void force_unit_f32(SysRef S, int ib, int c, float (*
     __syncthreads();  // the next unit of this block reuses both LDS buffers
 
     if (!real) return;
-    if (S.nsplit == 1) {
-        const int idx = glob<const int32_t>(S.perm)[slot];
-        const float gm = st->gm_f;
-        glob<float>(S.ax)[idx] = gm * ax;
-        glob<float>(S.ay)[idx] = gm * ay;
-        glob<float>(S.az)[idx] = gm * az;
-    } else {
-        auto *P = glob<float>(S.part);
-        const size_t na = S.nalloc;
-        const size_t b = (size_t)c * 3 * na + slot;
-        P[b] = ax;
-        P[b + na] = ay;
-        P[b + 2 * na] = az;
-    }
+    const int idx = glob<const int32_t>(S.perm)[slot];
+    const float gm = st->gm_f;
+    glob<float>(S.ax)[idx] = gm * ax;
+    glob<float>(S.ay)[idx] = gm * ay;
+    glob<float>(S.az)[idx] = gm * az;
 }
 
 template <bool PRIO>
@@ -778,12 +761,8 @@ void k_force_f32(Launch L)
 {
     __shared__ __attribute__((aligned(16))) float sh[2][3][TJ];
     for (int u = L.unit_base + blockIdx.x; u < L.total_units; u += gridDim.x) {
-        const int s = find_sys(L, u, false);
-        SysRef S = cst(L.sys)[s];
-        const int local = u - S.unit_begin;
-        const int ib = local / S.nsplit;
-        const int c = local - ib * S.nsplit;
-        force_unit_f32<PRIO>(S, ib, c, sh);
+        SysRef S = cst(L.sys)[find_sys(L, u, false)];
+        force_unit_f32<PRIO>(S, u - S.unit_begin, sh);
     }
 }
 
@@ -1316,33 +1295,6 @@ __global__ __launch_bounds__(BT * COMBINE_SEGS) void k_combine_sym64(Launch L, i
         }
         if constexpr (KICK) kick_record<double>(S, J, idx, x, v0, out, last, lds);
         __syncthreads();  // part and lds are rewritten by the block's next tile
-    }
-}
-
-// ------------------------------------------------------------------ j-split combine
-
-// Plain mode: sums the chunk partials of each sorted slot in chunk order (plain FP32) and
-// scatters a = G m sum to the element's own index.
-__global__ __launch_bounds__(BT) void k_combine_f32(Launch L)
-{
-    for (int u = blockIdx.x; u < L.total_tunits; u += gridDim.x) {
-        SysRef S = cst(L.sys)[find_tile_sys(L, u)];
-        if (S.nsplit == 1) continue;
-        const int slot = (u - S.tunit_begin) * TJ + threadIdx.x;
-        const int idx = glob<const int32_t>(S.perm)[slot];
-        if (idx < 0) continue;
-        auto *P = glob<const float>(S.part);
-        const size_t na = S.nalloc;
-        float out[3];
-        for (int d = 0; d < 3; ++d) {
-            float sum = 0.0f;
-            for (int c = 0; c < S.nsplit; ++c) sum += P[(size_t)c * 3 * na + d * na + slot];
-            out[d] = sum;
-        }
-        const float gm = glob<DevState>(S.st)->gm_f;
-        glob<float>(S.ax)[idx] = gm * out[0];
-        glob<float>(S.ay)[idx] = gm * out[1];
-        glob<float>(S.az)[idx] = gm * out[2];
     }
 }
 
@@ -2913,10 +2865,9 @@ hipError_t launch_forces(const Launch &L, int mode, int step, int last, int max_
 hipError_t launch_combine(const Launch &L, int mode, int kick, int last, hipStream_t s)
 {
     if (L.total_tunits == 0) return hipSuccess;
-    const dim3 g(grid_for(L.total_tunits)), b(BT);
-    if (mode == 0) {
-        hipLaunchKernelGGL(k_combine_f32, g, b, 0, s, L);
-    } else if (mode == 1) {
+    if (mode == 0) return hipErrorInvalidValue;  // no partial sums
+    const dim3 g(grid_for(L.total_tunits));
+    if (mode == 1) {
         const bool many = L.total_tunits > CU_COUNT;
         const auto k = kick ? (many ? k_combine_sym<true, true> : k_combine_sym<true, false>)
                             : (many ? k_combine_sym<false, true> : k_combine_sym<false, false>);

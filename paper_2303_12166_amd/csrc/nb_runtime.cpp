@@ -156,12 +156,11 @@ void finish_split(TileCfg &c, int64_t n, int64_t n1, int mode, int law, int ns, 
     }
     c.one_sided = 0;
     c.n_rec = c.n_ounits;
-    // chunk c covers tiles [c ntiles / nsplit, (c + 1) ntiles / nsplit)
-    c.nsplit = c.ntiles > 0 ? std::max(1, std::min(ns, c.ntiles)) : 1;
-    c.jchunk = c.ntiles > 0 ? (c.ntiles + c.nsplit - 1) / c.nsplit * TJ : TJ;
+    // the plain mode and empty systems: one running sum per element over every tile
+    c.nsplit = 1;
+    c.jchunk = std::max(c.ntiles, 1) * TJ;
     c.n_iblocks = (int)((n + BT - 1) / BT);  // the real elements, not the padded slots
-    const int64_t units = (int64_t)c.n_iblocks * c.nsplit;
-    c.n_units = units > INT32_MAX ? -1 : (int)units;
+    c.n_units = c.n_iblocks;
 }
 
 // Chunks of the potential-energy sum: about 8192 (tile row, chunk) units, half of them empty
@@ -237,7 +236,7 @@ struct Layout {
 int rec_len(const TileCfg &c) { return std::max(std::max(c.n_ounits, c.n_rec), 1); }
 
 // Whether the force kernel leaves partial sums for a combine.
-bool needs_partials(const TileCfg &c) { return !c.one_sided && (c.nsplit > 1 || c.sym); }
+bool needs_partials(const TileCfg &c) { return c.sym != 0; }
 
 Layout layout_for(int mode, int law, const TileCfg &c)
 {
