@@ -1995,7 +1995,7 @@ __device__ __forceinline__ void rows_tile(const RowsMem<T> &P, const RowsMem<T> 
                     aj[d] += t;
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
     }
@@ -2203,7 +2203,7 @@ void k_force_rows(Launch L)
     union Shared {
         struct {
             RowsMem<T> mem[LAW == 0 ? 4 : 8];
-            T runs[4][3][64];
+            T runs[R > 1 ? 4 : 1][3][64];
         } w;
         T red[4][3][TJ];
     };
@@ -2234,10 +2234,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(rows_waves(s
 void k_force_mixed(Launch L, int step, int last)
 {
     union Shared {
-        struct {
-            RowsMem<T> mem[LAW == 0 ? 4 : 8];
-            T runs[4][3][64];
-        } w;
+        RowsMem<T> mem[LAW == 0 ? 4 : 8];
         T red[4][3][TJ];
         OneSidedMem<T, LAW> one;
     };
@@ -2247,7 +2244,7 @@ void k_force_mixed(Launch L, int step, int last)
     if (u < L.total_units) {
         SysRef S = cst(L.sys)[find_sys(L, u, false)];
         const auto *gc = cst(S.units) + 2 * (size_t)(u - S.unit_begin);
-        rows_unit<T, LAW, 1, 1>(S, gc[0], gc[0], gc[1], sh.w.mem, sh.w.runs, sh.red);
+        rows_unit<T, LAW, 1, 1>(S, gc[0], gc[0], gc[1], sh.mem, nullptr, sh.red);
     } else {
         one_sided_block<T, LAW, true>(L, L.unit_base, u - L.total_units, step, last, sh.one);
     }
