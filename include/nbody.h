@@ -61,7 +61,11 @@ extern "C" {
 
 /* precision modes of the force evaluation */
 #define NB_FP32_PLAIN 0 /* FP32, one running sum per element over all j in order */
-#define NB_FP32_KAHAN 1 /* FP32 tile partials, compensated (Kahan) sum across tiles */
+#define NB_FP32_KAHAN 1 /* FP32 in short sums. Symmetric kernels: FP32 partials (64 terms of a tile per
+                           element, reactions in runs of at most 256), added across tiles, chunks and
+                           bands with Kahan compensation. One-sided kernel (systems of at most 7168
+                           elements in their finest split): n / 256 terms per lane, then the lanes
+                           and waves pairwise in a fixed order, without compensation */
 #define NB_FP64 2       /* FP64 throughout (reference mode) */
 
 typedef struct nb_system nb_system; /* opaque, host-side, owned by the library */
@@ -261,7 +265,8 @@ int nb_tile_override(int64_t n_lo, int64_t n_hi, int32_t mode, int32_t law, int3
  * when a system's split, built-in or overridden, would need more than `bytes` of workspace, the
  * split is coarsened step by step, first to taller bands (FP32 Kahan mode: 1, 2, then 4 rows),
  * then to half as many chunks, until the workspace fits or cannot shrink further (the workspace
- * also holds the sorted state, so a budget below that is never met). 0 (the default) sets no
+ * also holds the sorted state, so a budget below that is never met). Small systems leave the
+ * one-sided kernel's split with the first of these steps. 0 (the default) sets no
  * budget. The split of a system, and with it the order of its sums, is fixed when it is created.
  * Always NB_OK. */
 int nb_set_workspace_budget(size_t bytes);

@@ -1931,10 +1931,10 @@ struct Rows {
 // Two rows in FP32: a reaction is summed in four runs of 16 steps (128 terms), added in order through
 // `runs`, because a running FP32 sum loses with its length what no later compensation brings back.
 // With one run of 512 terms the forces at 32,768 elements were off by 7.3e-8 of the largest (root
-// mean square; 6.6e-8 with the four waves' runs of 256 of the kernel before), so 4.3e-8, at the
-// same speed (10.17 and 10.15 ms a step at 262,144). One row's single run of 256 terms stays below
-// that kernel's error, and the same cut would cost it 2 % (700 -> 716 us, two steps of 40,009
-// elements under eqs. (4)-(6)).
+// mean square; 6.6e-8 with the four waves' runs of 256 of the kernel before), so 4.3e-8, for half a
+// percent (10.46 -> 10.51 ms a step at 262,144, 1419 -> 1426 us for two at 65,536). One row's single
+// run of 256 terms stays below that kernel's error, and the same cut would cost it 2 % (700 -> 716 us,
+// two steps of 40,009 elements under eqs. (4)-(6)).
 template <typename T, int LAW, int NI, int K0, int NK, bool NEAR, bool REACT, typename Law, typename V4>
 __device__ __forceinline__ void rows_tile(const RowsMem<T> &P, const RowsMem<T> &V, Rows<T, NI> &B,
                                           const Law *K, const V4 *vi, int lane, int wave,

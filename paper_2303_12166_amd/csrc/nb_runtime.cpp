@@ -77,6 +77,8 @@ size_t layout_total(int mode, int law, const TileCfg &c);
 // the symmetric kernels (graphs of five steps):
 //   alone            FP32 2,048 12 and 32, 7,168 31 and 38; FP64 2,048 15 and 37, 4,096 25 and 40
 //   32 of one size   FP32 2,048 77 and 70, 7,168 512 and 368; FP64 2,048 174 and 118, 4,096 478 and 310
+//   128 of one size  FP32 2,048 271 and 183, 4,096 731 and 500; FP64 1,024 250 and 148, 2,048 587 and 362
+// (with the passes that every system once had: alone 56 to 80, 128 of 2,048 235 and 380 in FP64).
 // FP64: a batch of 32 systems spread over 2,048 to 8,192 elements takes no longer than the passes that
 // every system once had (430 us; 419 with the limit at 4,096, 453 at 4,608. Eqs. (4)-(6) 557; 532
 // with 2,560, 542 with 3,584, and 32 of 2,048 to 4,096 elements 322; 312 with 2,560, 365 with 3,072).
@@ -190,10 +192,11 @@ TileCfg tile_config(int64_t n, int64_t n1, int mode, int law)
     int ns = 1, rows = 1;
     size_t budget = 0;
     if (mode != NB_FP32_PLAIN && c.ntiles > 0) {
-        // built-in rule: about 65536 work units, chunks of 2..16 tiles; from 256 tiles on,
-        // bands of four rows under the contact law and of two under eqs. (4)-(6) (measured
-        // faster there, with a quarter or half of the reaction partials; the eqs. (4)-(6)
-        // kernel spills at four), one row below
+        // built-in rule: about 65536 work units, chunks of 2..16 tiles; one row below 256 tiles,
+        // above, bands of four rows under the contact law (an evaluation at 1,048,576 elements
+        // 163.2 ms against 164.0 with two, with half the reaction partials; the tuned table, which
+        // ends at 524,287, takes two from 32,768 on) and of two under eqs. (4)-(6) (198.7 ms
+        // there against 205.0 with one)
         const int64_t per = (int64_t)c.ntiles * c.n_iblocks / 65536;
         const int tpc = (int)std::min<int64_t>(16, std::max<int64_t>(2, per));
         ns = std::max(1, (c.ntiles + tpc / 2) / tpc);
