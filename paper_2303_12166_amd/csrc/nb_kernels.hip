@@ -5,7 +5,7 @@
 // the pair sum is not a dense contraction, so there is no MFMA here. The kernels that evaluate it:
 //   - k_force_rows<T, LAW, R, BAND> (FP32 Kahan and FP64 modes): each unordered pair once, 4 R i elements
 //     per lane in registers and the j sums rotating across the wave (see below);
-//   - k_force_one_sided<T, LAW, STEP> (the same modes, small systems): every ordered pair, in element
+//   - k_force_one_sided<T, LAW, STEP, LOOP> (the same modes, small systems): every ordered pair, in element
 //     order, and in a step everything else of it; k_force_mixed runs both in one launch;
 //   - k_force_f32 (FP32, plain mode): one-sided, one i element per lane, the block streams
 //     256-element SoA j tiles through LDS (broadcast ds_read_b128), one FP32 running sum.
